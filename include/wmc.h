@@ -241,6 +241,17 @@ wmc_status wmc_plan_node(const wmc_plan_t *plan, int64_t i, int64_t *a, int64_t 
                          int32_t *node_class);
 wmc_status wmc_plan_image(const wmc_plan_t *plan, void *dst, uint64_t dst_bytes, uint64_t *needed,
                           int64_t *info /* 13 entries */);
+/* The program wmc_contract runs when consecutive nodes of the plan are fused
+ * into chains: [leaf descriptors][node descriptors][matrix-node
+ * descriptors][chain words (u32)][workgroup records (4 x u32)][8 x int32 per
+ * launch: type (0 step of small nodes and chains, 1 one node alone, 2 one
+ * matrix node), first node, nodes, first chain, chains, matrix node, first
+ * record, records][first word of each chain (u32)][arena offset of each
+ * tensor (int64, -1: never stored)].  info[0..8] = {n_leaves, n_nodes,
+ * n_gemms, n_words, n_records, n_launches, n_chains, n_tensors,
+ * arena_elems}; n_launches 0: the plan's launch list runs as it is. */
+wmc_status wmc_plan_program(const wmc_plan_t *plan, void *dst, uint64_t dst_bytes, uint64_t *needed,
+                            int64_t *info /* 9 entries */);
 
 /* ------------------------------------------------------------------ */
 /* Execution stage (Algorithm 2 over the slices of Algorithm 3)         */
@@ -330,7 +341,8 @@ enum {
     WMC_KERNEL_STREAM2 = 6,       /* k_stream2: register-tiled streaming node */
     WMC_KERNEL_STREAM2_SPLIT = 7, /* k_stream2_split: summed index split over lane groups */
     WMC_KERNEL_FINISH = 8,        /* k_finish: slice accumulation */
-    WMC_KERNEL_STREAM2_VEC = 9    /* k_stream2_vec: K = 1 streaming node, output pairs per thread */
+    WMC_KERNEL_STREAM2_VEC = 9,   /* k_stream2_vec: K = 1 streaming node, output pairs per thread */
+    WMC_KERNEL_CHAIN = 10         /* k_chain: consecutive nodes with their intermediates in LDS, and small nodes */
 };
 wmc_status wmc_plan_kernels(const wmc_plan_t *plan, int32_t *kernel, int64_t cap, int64_t *n_out);
 

@@ -136,6 +136,7 @@ def lib():
             "wmc_plan_tensor": [P, i64, P, P, P, P],
             "wmc_plan_node": [P, i64, P, P, P, P],
             "wmc_plan_image": [P, P, u64, P, P],
+            "wmc_plan_program": [P, P, u64, P, P],
             "wmc_contract": [P, P, P, u64, P, ctypes.POINTER(wmc_value)],
             "wmc_contract_slices": [P, P, P, u64, P, i64, i64, ctypes.POINTER(wmc_value), P],
             "wmc_contract_resume": [P, P, P, u64, P, i64, ctypes.POINTER(wmc_slice_state), ctypes.POINTER(wmc_value)],
@@ -377,6 +378,18 @@ class Plan:
                 "elem", "leaf_desc_bytes", "node_desc_bytes", "launch_bytes", "n_gemms", "gemm_desc_bytes"]
         return bytes(buf)[: int(need.value)], dict(zip(keys, list(info)))
 
+    def program(self):
+        """Raw image of the fused program: (bytes, info dict); info
+        ["n_launches"] is 0 when the launch list runs as it is."""
+        need = ctypes.c_uint64()
+        info = (ctypes.c_int64 * 9)()
+        _check(lib().wmc_plan_program(self._h, None, 0, ctypes.byref(need), info))
+        buf = (ctypes.c_uint8 * max(int(need.value), 1))()
+        _check(lib().wmc_plan_program(self._h, buf, int(need.value), ctypes.byref(need), info))
+        keys = ["n_leaves", "n_nodes", "n_gemms", "n_words", "n_recs", "n_launches", "n_chains", "n_tensors",
+                "arena_elems"]
+        return bytes(buf)[: int(need.value)], dict(zip(keys, list(info)))
+
     def __del__(self):
         h = getattr(self, "_h", None)
         if h is not None and h.value and _lib is not None:
@@ -537,7 +550,7 @@ def plan_launches(plan: Plan):
 
 
 KERNEL_NAMES = ["k_begin", "k_leaves", "k_nodes", "k_gemm_p", "k_gemm", "k_stream_mfma", "k_stream2",
-                "k_stream2_split", "k_finish", "k_stream2_vec"]
+                "k_stream2_split", "k_finish", "k_stream2_vec", "k_chain"]
 
 
 def plan_kernels(plan: Plan) -> np.ndarray:

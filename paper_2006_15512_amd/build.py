@@ -22,7 +22,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
-HOST_SOURCES = ["wmc_host.cpp"]
+HOST_SOURCES = ["wmc_host.cpp", "wmc_fuse.cpp"]
 DEVICE_SOURCES = ["wmc_device.hip", "wmc_batch.hip", "wmc_serve.hip"]
 
 
@@ -46,12 +46,12 @@ def build_sanitized(verbose: bool = False) -> str:
     os.makedirs(SAN_DIR, exist_ok=True)
     inc = ["-I", CSRC, "-I", os.path.join(ROOT, "include")]
     san = ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-fno-omit-frame-pointer"]
-    host_o = os.path.join(SAN_DIR, "wmc_host.cpp.o")
-    _run(["g++", "-std=c++17", "-O1", "-g", *san, "-fPIC", *inc, "-c", os.path.join(CSRC, "wmc_host.cpp"),
-          "-o", host_o], verbose)
+    host_o = [os.path.join(SAN_DIR, h + ".o") for h in HOST_SOURCES]
+    for h, o in zip(HOST_SOURCES, host_o):
+        _run(["g++", "-std=c++17", "-O1", "-g", *san, "-fPIC", *inc, "-c", os.path.join(CSRC, h), "-o", o], verbose)
     dev_o = [os.path.join(BUILD_DIR, s + ".o") for s in DEVICE_SOURCES]
     rocm = os.path.dirname(os.path.dirname(HIPCC))
-    _run(["g++", "-shared", *san, host_o, *dev_o, "-L", os.path.join(rocm, "lib"), "-lamdhip64",
+    _run(["g++", "-shared", *san, *host_o, *dev_o, "-L", os.path.join(rocm, "lib"), "-lamdhip64",
           "-Wl,-rpath," + os.path.join(rocm, "lib"), "-o", SAN_LIB], verbose)
     return SAN_LIB
 

@@ -3,7 +3,7 @@
 // and their numerics are in wmc_kernels.h.
 #include <mutex>
 
-#include "wmc_kernels.h"
+#include "wmc_chain.h"
 
 // Optional per-launch timing: an event is recorded on the stream after every
 // launch; ms[k] accumulates launch k's duration over the slices.
@@ -39,16 +39,13 @@ static inline int split_lanes_of(const wmc_plan_t &P, int nk) {
     return sizeof(T) == 8 && nk >= 4 && nk <= 5 ? P.tune.split_lanes : 0;
 }
 
-// Kernel family that runs node launch k (1 <= k < P.launches.size()) of a
-// solo plan, with the streaming kernels' arguments filled in when one of
-// them is chosen.  The executor and wmc_plan_kernels share this choice.
+// Kernel family that runs a single node alone (mat: its matrix descriptor,
+// or null), with the streaming kernels' arguments filled in when one of them
+// is chosen.  The executor and wmc_plan_kernels share this choice.
 template <typename T>
-static int solo_kernel(const wmc_plan_t &P, size_t k, Stream2Tab *tb, StreamMfmaArgs *ma) {
-    const Launch &Ln = P.launches[k];
-    if (Ln.type == LAUNCH_GEMM)
-        return gemm_persistent<T>(P.gemms[(size_t)Ln.pad]) ? WMC_KERNEL_GEMM_P : WMC_KERNEL_GEMM;
-    if (Ln.count == 1 && P.nodes[(size_t)Ln.first].cls == WMC_CLASS_STREAM) {
-        const NodeDesc &d = P.nodes[(size_t)Ln.first];
+static int node_kernel(const wmc_plan_t &P, const NodeDesc &d, const GemmDesc *mat, Stream2Tab *tb, StreamMfmaArgs *ma) {
+    if (mat) return gemm_persistent<T>(*mat) ? WMC_KERNEL_GEMM_P : WMC_KERNEL_GEMM;
+    if (d.cls == WMC_CLASS_STREAM) {
         const wmc_tuning &tu = P.tune;
         if (tu.stream_mfma_min_bits > 0 && stream_mfma_args(d, ma, tu.stream_mfma_min_bits)) return WMC_KERNEL_STREAM_MFMA;
         if (stream2_args(d, &tb->a, tu.stream2_tile_bits, tu.stream2_min_thread_bits, tu.stream2_low_bits,
@@ -62,18 +59,113 @@ static int solo_kernel(const wmc_plan_t &P, size_t k, Stream2Tab *tb, StreamMfma
     return WMC_KERNEL_NODES;
 }
 
+// The same for node launch k (1 <= k < P.launches.size()) of the plan's
+// general launch list.
 template <typename T>
-static wmc_status run_slices(const wmc_plan_t &P, char *ws, hipStream_t st, long long b, long long e,
-                             wmc_value *per_slice, LaunchTimer *tm = nullptr, bool keep_sum = false) {
-    wmc_meta *meta = (wmc_meta *)(ws + P.off_meta);
-    wmc_acc *acc = (wmc_acc *)(ws + P.off_acc);
-    const double *w = (const double *)(ws + P.off_w);
-    const LeafDesc *L = (const LeafDesc *)(ws + P.off_leaf);
+static int solo_kernel(const wmc_plan_t &P, size_t k, Stream2Tab *tb, StreamMfmaArgs *ma) {
+    const Launch &Ln = P.launches[k];
+    if (Ln.type != LAUNCH_GEMM && Ln.count != 1) return WMC_KERNEL_NODES;
+    return node_kernel<T>(P, P.nodes[(size_t)Ln.first], Ln.type == LAUNCH_GEMM ? &P.gemms[(size_t)Ln.pad] : nullptr, tb,
+                          ma);
+}
+
+// Launches one node alone on the kernel family `kern`; false if no instance
+// covers it (nothing launched).
+template <typename T>
+static bool launch_node(const wmc_plan_t &P, int kern, const NodeDesc &d, const GemmDesc *mat, const GemmDesc *mat_dev,
+                        const Stream2Tab &sa, const StreamMfmaArgs &ma, T *arena, wmc_meta *meta, hipStream_t st,
+                        const SliceGroup sg, unsigned nz) {
+    switch (kern) {
+    case WMC_KERNEL_GEMM_P:
+    case WMC_KERNEL_GEMM:
+        launch_gemm<T>(*mat, mat_dev, arena, meta, st, sg, nz, GemmShape{P.tune.gemm_tpw_max_nt, P.tune.gemm_orient});
+        return true;
+    case WMC_KERNEL_STREAM_MFMA:
+        launch_stream_mfma<T>(ma, d.nk, arena, meta, st, (unsigned)P.tune.stream_mfma_grid_cap, sg, nz);
+        return true;
+    case WMC_KERNEL_STREAM2:
+    case WMC_KERNEL_STREAM2_SPLIT:
+    case WMC_KERNEL_STREAM2_VEC:
+        return launch_stream2<T>(sa, d.nk, arena, meta, st,
+                                 kern == WMC_KERNEL_STREAM2_SPLIT ? split_lanes_of<T>(P, d.nk) : 0, sg, nz,
+                                 (unsigned)P.tune.stream2_grid_cap);
+    default: return false;
+    }
+}
+
+// Node launches of the plan's general launch list on one slice group.
+template <typename T>
+static void general_launches(const wmc_plan_t &P, char *ws, T *arena, wmc_meta *meta, hipStream_t st,
+                             const SliceGroup sg, unsigned nz, LaunchTimer *tm) {
     const NodeDesc *D = (const NodeDesc *)(ws + P.off_node);
     const GemmDesc *Gd = (const GemmDesc *)(ws + P.off_gemm);
     const int *TB = (const int *)(ws + P.off_tab);
+    for (size_t k = 1; k < P.launches.size(); ++k) {
+        const Launch &Ln = P.launches[k];
+        Stream2Tab sa;
+        StreamMfmaArgs ma;
+        const int kern = solo_kernel<T>(P, k, &sa, &ma);
+        const bool mat = Ln.type == LAUNCH_GEMM;
+        if (!launch_node<T>(P, kern, P.nodes[(size_t)Ln.first], mat ? &P.gemms[(size_t)Ln.pad] : nullptr,
+                            mat ? Gd + Ln.pad : nullptr, sa, ma, arena, meta, st, sg, nz))
+            hipLaunchKernelGGL(k_nodes<T>, dim3(grid_for(Ln.work), 1, nz), dim3(WMC_BLOCK), 0, st, D + Ln.first,
+                               Ln.count, (long long)Ln.work, arena, meta, sg,
+                               P.tab_off[k] >= 0 ? TB + P.tab_off[k] : nullptr);
+        if (tm) tm->mark();
+    }
+}
+
+// Launches of the fused program on one slice group.
+template <typename T>
+static void fused_launches(const wmc_plan_t &P, char *ws, T *arena, wmc_meta *meta, hipStream_t st,
+                           const SliceGroup sg, unsigned nz, LaunchTimer *tm) {
+    const FusedProgram &F = P.fused;
+    char *img = ws + P.off_leaf;
+    const NodeDesc *D = (const NodeDesc *)(img + F.o_node);
+    const GemmDesc *Gd = (const GemmDesc *)(img + F.o_gemm);
+    const int *TB = (const int *)(img + F.o_tab);
+    for (const FusedLaunch &Ln : F.launches) {
+        bool launched = false;
+        if (Ln.type == FUSED_NODE || Ln.type == FUSED_GEMM) {
+            Stream2Tab sa;
+            StreamMfmaArgs ma;
+            const NodeDesc &d = F.nodes[(size_t)Ln.node_first];
+            const GemmDesc *mat = Ln.type == FUSED_GEMM ? &F.gemms[(size_t)Ln.gemm] : nullptr;
+            launched = launch_node<T>(P, node_kernel<T>(P, d, mat, &sa, &ma), d, mat, mat ? Gd + Ln.gemm : nullptr, sa,
+                                      ma, arena, meta, st, sg, nz);
+        }
+        if (!launched) {
+            FusedStepArgs a{};
+            a.recs = (const ChainRec *)(img + F.o_recs) + Ln.rec_first;
+            a.words = (const unsigned *)(img + F.o_words);
+            a.cblocks = (unsigned)Ln.rec_count;
+            a.nodes = D + Ln.node_first;
+            a.nnodes = Ln.node_count;
+            a.node_work = Ln.node_work;
+            a.wave_node = Ln.tab >= 0 ? TB + Ln.tab : nullptr;
+            a.nblocks = Ln.node_count ? chain_node_blocks(Ln.node_work) : 0;
+            if (Ln.type == FUSED_CHAIN) launch_chain_big<T>(a, Ln.lds, arena, meta, st, sg, nz);
+            else launch_fused_step<T>(a, Ln.lds, arena, meta, st, sg, nz);
+        }
+        if (tm) tm->mark();
+    }
+}
+
+template <typename T>
+static wmc_status run_slices(const wmc_plan_t &P, char *ws, hipStream_t st, long long b, long long e,
+                             wmc_value *per_slice, bool fused, LaunchTimer *tm = nullptr, bool keep_sum = false) {
+    const FusedProgram &F = P.fused;
+    wmc_meta *meta = (wmc_meta *)(ws + P.off_meta);
+    wmc_acc *acc = (wmc_acc *)(ws + P.off_acc);
+    const double *w = (const double *)(ws + P.off_w);
+    char *img = ws + P.off_leaf;
+    const LeafDesc *L = (const LeafDesc *)(fused ? img + F.o_leaf : img);
+    const int *TB = (const int *)(fused ? img + F.o_tab : ws + P.off_tab);
+    const int64_t leaf_tab = fused ? F.leaf_tab : P.leaf_tab;
     T *arena = (T *)(ws + P.off_arena);
     const int nt = (int)P.T.size();
+    const int nmasks = fused ? (int)F.masks.size() : 0;
+    const long long root_off = fused ? (long long)F.off[(size_t)P.root] : (long long)P.T[(size_t)P.root].off;
     // slices run in groups of up to P.group, side by side in every launch
     // (grid dimension z); per-slice results need one slice at a time
     const long long G = per_slice ? 1 : (long long)P.group;
@@ -91,31 +183,12 @@ static wmc_status run_slices(const wmc_plan_t &P, char *ws, hipStream_t st, long
         if (!P.leaves.empty())
             hipLaunchKernelGGL(k_leaves<T>, dim3(grid_for(P.leaf_work), 1, nz), dim3(WMC_BLOCK), 0, st, L,
                                (int)P.leaves.size(), (long long)P.leaf_work, w, arena, meta, sg,
-                               (unsigned long long)eta, P.leaf_tab >= 0 ? TB + P.leaf_tab : nullptr);
+                               (unsigned long long)eta, leaf_tab >= 0 ? TB + leaf_tab : nullptr);
         if (tm) tm->mark();
-        for (size_t k = 1; k < P.launches.size(); ++k) {
-            const Launch &Ln = P.launches[k];
-            Stream2Tab sa;
-            StreamMfmaArgs ma;
-            const int kern = solo_kernel<T>(P, k, &sa, &ma);
-            if (kern == WMC_KERNEL_GEMM_P || kern == WMC_KERNEL_GEMM)
-                launch_gemm<T>(P.gemms[(size_t)Ln.pad], Gd + Ln.pad, arena, meta, st, sg, nz,
-                               GemmShape{P.tune.gemm_tpw_max_nt, P.tune.gemm_orient});
-            else if (kern == WMC_KERNEL_STREAM_MFMA)
-                launch_stream_mfma<T>(ma, P.nodes[(size_t)Ln.first].nk, arena, meta, st,
-                                      (unsigned)P.tune.stream_mfma_grid_cap, sg, nz);
-            else if ((kern == WMC_KERNEL_STREAM2 || kern == WMC_KERNEL_STREAM2_SPLIT || kern == WMC_KERNEL_STREAM2_VEC) &&
-                     launch_stream2<T>(sa, P.nodes[(size_t)Ln.first].nk, arena, meta, st,
-                                      kern == WMC_KERNEL_STREAM2_SPLIT ? split_lanes_of<T>(P, P.nodes[(size_t)Ln.first].nk) : 0,
-                                      sg, nz, (unsigned)P.tune.stream2_grid_cap)) {
-            } else
-                hipLaunchKernelGGL(k_nodes<T>, dim3(grid_for(Ln.work), 1, nz), dim3(WMC_BLOCK), 0, st, D + Ln.first,
-                                   Ln.count, (long long)Ln.work, arena, meta, sg,
-                                   P.tab_off[k] >= 0 ? TB + P.tab_off[k] : nullptr);
-            if (tm) tm->mark();
-        }
-        hipLaunchKernelGGL(k_finish<T>, dim3(1), dim3(1), 0, st, arena, (long long)P.T[(size_t)P.root].off, meta,
-                           P.root, acc, (int)nz, sg.astride, sg.mstride);
+        if (fused) fused_launches<T>(P, ws, arena, meta, st, sg, nz, tm);
+        else general_launches<T>(P, ws, arena, meta, st, sg, nz, tm);
+        hipLaunchKernelGGL(k_finish<T>, dim3(1), dim3(nmasks ? WMC_BLOCK : 1), 0, st, arena, root_off, meta, P.root, acc,
+                           (int)nz, sg.astride, sg.mstride, (const int *)(img + F.o_masks), nmasks);
         if (tm) tm->mark();
         HIP_TRY(hipGetLastError());
         if (tm) {
@@ -134,6 +207,28 @@ static wmc_status run_slices(const wmc_plan_t &P, char *ws, hipStream_t st, long
         }
     }
     return WMC_OK;
+}
+
+// Slices [b, e) with the weights and the running sum *init (null: zero),
+// into *h: on the fused program, and once more on the general launch list if
+// one of its chains left its range.
+static wmc_status contract_range(const wmc_plan_t &P, const double *weights, char *ws, hipStream_t st, long long b,
+                                 long long e, wmc_value *per_slice, const wmc_acc *init, wmc_acc *h,
+                                 LaunchTimer *tm = nullptr) {
+    // a profile times the launch list it reports, node by node
+    for (bool fused = P.fused.on && !tm;; fused = false) {
+        HIP_TRY(upload_weights(P, weights, ws, st));
+        const std::vector<uint8_t> &img = fused ? P.fused.image : P.desc_image;
+        HIP_TRY(hipMemcpyAsync(ws + P.off_leaf, img.data(), img.size(), hipMemcpyHostToDevice, st));
+        if (init) HIP_TRY(hipMemcpyAsync(ws + P.off_acc, init, sizeof *init, hipMemcpyHostToDevice, st));
+        const wmc_status s = P.precision == WMC_FP64
+                                 ? run_slices<double>(P, ws, st, b, e, per_slice, fused, tm, init != nullptr)
+                                 : run_slices<float>(P, ws, st, b, e, per_slice, fused, tm, init != nullptr);
+        if (s != WMC_OK) return s;
+        HIP_TRY(hipMemcpyAsync(h, ws + P.off_acc, sizeof *h, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        if (!fused || !h->pad[0]) return WMC_OK;
+    }
 }
 
 extern "C" wmc_status wmc_contract_slices(const wmc_plan_t *plan, const double *weights, void *workspace,
@@ -177,14 +272,9 @@ extern "C" wmc_status wmc_contract_slices(const wmc_plan_t *plan, const double *
     }
     hipStream_t st = (hipStream_t)stream;
     char *ws = (char *)workspace;
-    HIP_TRY(upload_weights(P, weights, ws, st));
-    HIP_TRY(hipMemcpyAsync(ws + P.off_leaf, P.desc_image.data(), P.desc_bytes, hipMemcpyHostToDevice, st));
-    wmc_status s = P.precision == WMC_FP64 ? run_slices<double>(P, ws, st, slice_begin, slice_end, per_slice)
-                                           : run_slices<float>(P, ws, st, slice_begin, slice_end, per_slice);
-    if (s != WMC_OK) return s;
     wmc_acc h;
-    HIP_TRY(hipMemcpyAsync(&h, ws + P.off_acc, sizeof h, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    const wmc_status s = contract_range(P, weights, ws, st, slice_begin, slice_end, per_slice, nullptr, &h);
+    if (s != WMC_OK) return s;
     if (h.s == 0.0 && h.c == 0.0) {
         *out = make_value(0.0, 0);
     } else {
@@ -234,14 +324,9 @@ extern "C" wmc_status wmc_contract_resume(const wmc_plan_t *plan, const double *
         h.s = state->s;
         h.c = state->c;
         h.e = state->e;
-        HIP_TRY(upload_weights(P, weights, ws, st));
-        HIP_TRY(hipMemcpyAsync(ws + P.off_leaf, P.desc_image.data(), P.desc_bytes, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(ws + P.off_acc, &h, sizeof h, hipMemcpyHostToDevice, st));
-        wmc_status s = P.precision == WMC_FP64 ? run_slices<double>(P, ws, st, b, e, nullptr, nullptr, true)
-                                               : run_slices<float>(P, ws, st, b, e, nullptr, nullptr, true);
+        const wmc_acc init = h;
+        const wmc_status s = contract_range(P, weights, ws, st, b, e, nullptr, &init, &h);
         if (s != WMC_OK) return s;
-        HIP_TRY(hipMemcpyAsync(&h, ws + P.off_acc, sizeof h, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
         state->s = h.s;
         state->c = h.c;
         state->e = h.e;
@@ -292,23 +377,10 @@ extern "C" wmc_status wmc_contract_profile(const wmc_plan_t *plan, const double 
     tm.ev.resize((size_t)n + 1);
     for (auto &e : tm.ev) HIP_TRY(hipEventCreate(&e));
     for (int64_t k = 0; k < cap; ++k) ms[k] = 0.f;
-    wmc_status s = WMC_OK;
-    if (upload_weights(P, weights, ws, st) != hipSuccess) s = WMC_ERR_DEVICE;
-    if (s == WMC_OK && hipMemcpyAsync(ws + P.off_leaf, P.desc_image.data(), P.desc_bytes, hipMemcpyHostToDevice, st) != hipSuccess)
-        s = WMC_ERR_DEVICE;
-    const long long ns = 1ll << P.sliced.size();
-    if (s == WMC_OK)
-        s = P.precision == WMC_FP64 ? run_slices<double>(P, ws, st, 0, ns, nullptr, &tm)
-                                    : run_slices<float>(P, ws, st, 0, ns, nullptr, &tm);
     wmc_acc h;
-    if (s == WMC_OK && (hipMemcpyAsync(&h, ws + P.off_acc, sizeof h, hipMemcpyDeviceToHost, st) != hipSuccess ||
-                        hipStreamSynchronize(st) != hipSuccess))
-        s = WMC_ERR_DEVICE;
+    const wmc_status s = contract_range(P, weights, ws, st, 0, 1ll << P.sliced.size(), nullptr, nullptr, &h, &tm);
     for (auto &e : tm.ev) (void)hipEventDestroy(e);
-    if (s != WMC_OK) {
-        if (s == WMC_ERR_DEVICE) wmc_set_error("wmc_contract_profile: HIP failure");
-        return s;
-    }
+    if (s != WMC_OK) return s;
     *out = (h.s == 0.0 && h.c == 0.0) ? make_value(0.0, 0) : make_value(h.s + h.c, h.e);
     return WMC_OK;
 }
@@ -331,11 +403,10 @@ extern "C" wmc_status wmc_plan_kernels(const wmc_plan_t *plan, int32_t *kernel, 
     }
     kernel[0] = WMC_KERNEL_BEGIN;
     kernel[1] = WMC_KERNEL_LEAVES;
-    for (size_t k = 1; k < P.launches.size(); ++k) {
-        Stream2Tab sa;
-        StreamMfmaArgs ma;
+    Stream2Tab sa;
+    StreamMfmaArgs ma;
+    for (size_t k = 1; k < P.launches.size(); ++k)
         kernel[k + 1] = P.precision == WMC_FP64 ? solo_kernel<double>(P, k, &sa, &ma) : solo_kernel<float>(P, k, &sa, &ma);
-    }
     kernel[n - 1] = WMC_KERNEL_FINISH;
     return WMC_OK;
 }
@@ -436,7 +507,8 @@ static bool validate_t(const wmc_plan_t &P, std::string *why) {
 }
 
 bool wmc_validate_launches(const wmc_plan_t &P, std::string *why) {
-    return P.precision == WMC_FP64 ? validate_t<double>(P, why) : validate_t<float>(P, why);
+    return (P.precision == WMC_FP64 ? validate_t<double>(P, why) : validate_t<float>(P, why)) &&
+           wmc_validate_fused(P, why);
 }
 
 // ---------------------------------------------------------------------------

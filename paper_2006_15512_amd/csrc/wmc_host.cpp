@@ -871,10 +871,16 @@ static uint64_t place_arena(const std::vector<TNode> &T, const Schedule &S, cons
     const int32_t NL = (int32_t)S.launches.size() + 1;
     for (size_t i = 0; i < NT; ++i) death[i] = (T[i].parent < 0) ? NL : birth[(size_t)T[i].parent];
     const uint64_t align_elems = 256 / (uint64_t)elem;
-    std::vector<int32_t> by_size(NT);
-    std::iota(by_size.begin(), by_size.end(), 0);
     std::vector<uint64_t> elems(NT);
     for (size_t i = 0; i < NT; ++i) elems[i] = align_up((uint64_t)1 << srank(T[i], sl), align_elems);
+    return wmc_place(birth, death, elems, offs) * (uint64_t)elem;
+}
+
+uint64_t wmc_place(const std::vector<int32_t> &birth, const std::vector<int32_t> &death,
+                   const std::vector<uint64_t> &elems, std::vector<int64_t> *offs) {
+    const size_t NT = elems.size();
+    std::vector<int32_t> by_size(NT);
+    std::iota(by_size.begin(), by_size.end(), 0);
     std::stable_sort(by_size.begin(), by_size.end(), [&](int32_t a, int32_t b) {
         if (elems[(size_t)a] != elems[(size_t)b]) return elems[(size_t)a] > elems[(size_t)b];
         return birth[(size_t)a] < birth[(size_t)b];
@@ -900,7 +906,7 @@ static uint64_t place_arena(const std::vector<TNode> &T, const Schedule &S, cons
         placed.push_back(t);
     }
     if (offs) offs->swap(off);
-    return arena_elems * (uint64_t)elem;
+    return arena_elems;
 }
 
 // Peak of live tensor bytes, sizes 256-byte aligned, over the schedule the
@@ -1387,6 +1393,19 @@ static wmc_status finalize_plan(const wmc_network &net, const wmc_plan_options &
         std::memcpy(P.desc_image.data() + (P.off_tab - P.off_leaf), tabs.data(), sizeof(int32_t) * tabs.size());
     P.arena_stride = align_up(P.arena_bytes, 256);
     P.workspace_bytes = P.off_arena + (uint64_t)P.group * P.arena_stride;
+    // the fused program's image shares the descriptor region and its tensors
+    // the arena; a plan that fits the static scratch keeps fitting it
+    wmc_fuse(P);
+    if (P.fused.on) {
+        const uint64_t more = P.off_leaf + P.fused.image.size() > P.off_arena
+                                  ? P.off_leaf + P.fused.image.size() - P.off_arena : 0;
+        if (P.workspace_bytes <= WMC_NOALLOC_SCRATCH_BYTES && P.workspace_bytes + more > WMC_NOALLOC_SCRATCH_BYTES) {
+            P.fused = FusedProgram();
+        } else {
+            P.off_arena += more;
+            P.workspace_bytes += more;
+        }
+    }
 
     // ---- statistics
     wmc_plan_info &I = P.info;

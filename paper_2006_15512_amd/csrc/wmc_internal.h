@@ -62,6 +62,57 @@ struct Launch {
 };
 static_assert(sizeof(Launch) == 24, "Launch layout");
 
+// A chain of the fused program (the words the kernel reads are in
+// FusedProgram::words from `desc` on).
+struct ChainTask {
+    std::vector<int32_t> nodes;  // the stages' output tensors; the last is stored
+    int32_t f = -1;              // F_0
+    std::vector<int32_t> g;      // G_i per stage
+    unsigned desc = 0;
+    int32_t tile_bits = 0;       // log2 of the number of tiles
+    int32_t lds = 0;             // LDS entries of the storage type
+    double work = 0;             // summed products over all stages and tiles
+    bool big = false;            // of many tiles: runs alone, register-tiled
+};
+
+// Launch of the fused program: small nodes and short chains together (STEP),
+// one node on its own kernel (NODE), one matrix node (GEMM), or one chain of
+// many tiles (CHAIN).
+enum { FUSED_STEP = 0, FUSED_NODE = 1, FUSED_GEMM = 2, FUSED_CHAIN = 3 };
+struct FusedLaunch {
+    int32_t type = FUSED_STEP;
+    int32_t node_first = 0, node_count = 0;
+    int64_t node_work = 0;
+    int32_t chain_first = 0, chain_count = 0;
+    int32_t gemm = -1;
+    int32_t lds = 0;                      // entries of the storage type
+    int32_t rec_first = 0, rec_count = 0; // solo launch: workgroup records
+    int64_t tab = -1;                     // wave -> node table, -1 where the kernel searches
+};
+
+// The program wmc_contract, batches and servers run: the plan's nodes with
+// chains of them fused, placed on its own in the same arena.  The plan's
+// launch list remains the general form, run instead when a chain reports
+// that an intermediate left the range its tiles can hold.
+struct FusedProgram {
+    bool on = false;
+    std::vector<int64_t> off;             // arena offset per tensor (-1: never stored)
+    std::vector<LeafDesc> leaves;
+    std::vector<NodeDesc> nodes;
+    std::vector<GemmDesc> gemms;
+    std::vector<ChainTask> chains;
+    std::vector<unsigned> words;
+    std::vector<FusedLaunch> launches;
+    std::vector<ChainRec> recs;
+    std::vector<int32_t> masks;           // meta entries to check after a run
+    std::vector<int32_t> tabs;
+    int64_t leaf_tab = -1;
+    uint64_t arena_bytes = 0;
+    // image, offsets relative to the plan's descriptor region
+    uint64_t o_leaf = 0, o_node = 0, o_gemm = 0, o_words = 0, o_recs = 0, o_tab = 0, o_masks = 0;
+    std::vector<uint8_t> image;
+};
+
 struct wmc_plan_t {
     int32_t n = 0;                    // variables, auxiliary ones included
     int32_t n_user = 0;               // weights a caller passes: 2 * n_user
@@ -96,7 +147,16 @@ struct wmc_plan_t {
     uint64_t arena_stride = 0;   // bytes, 256-aligned
     int64_t meta_stride = 0;     // wmc_meta entries
     wmc_plan_info info{};
+    FusedProgram fused;
 };
+
+// Static placement of intervals [birth, death] of `elems` entries each,
+// largest first; returns the arena's entries (wmc_host.cpp).
+uint64_t wmc_place(const std::vector<int32_t> &birth, const std::vector<int32_t> &death,
+                   const std::vector<uint64_t> &elems, std::vector<int64_t> *offs);
+// Builds P.fused from the finished launch list (wmc_fuse.cpp).
+void wmc_fuse(wmc_plan_t &P);
+bool wmc_validate_fused(const wmc_plan_t &P, std::string *why);
 
 void wmc_set_error(const char *fmt, ...);
 // Bounds of every launch of a finished plan, proved on the host before

@@ -147,6 +147,7 @@ static __global__ __attribute__((unused)) void k_begin(wmc_meta *meta, int nt, w
         acc->n_added = 0;
         acc->last_m = 0.0;
         acc->last_e = 0;
+        acc->pad[0] = 0;
     }
 }
 
@@ -2021,10 +2022,24 @@ template <typename T>
 __device__ void finish_one(const T *__restrict__ arena, long long root_off, const wmc_meta *meta, int root,
                            wmc_acc *acc);
 
+// True if a chain's range bits (two per stage: an ordinary entry, a nonzero
+// entry) name a stage whose intermediate was nonzero but nowhere ordinary.
+__device__ __forceinline__ bool chain_out_of_range(unsigned long long mask) {
+    const unsigned m = (unsigned)mask;
+    return (((m >> 1) & ~m) & 0x55555555u) != 0u;
+}
+
 template <typename T>
 __global__ void k_finish(const T *__restrict__ arena, long long root_off, const wmc_meta *meta, int root,
-                         wmc_acc *acc, int nz, long long astride, int mstride) {
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+                         wmc_acc *acc, int nz, long long astride, int mstride, const int *__restrict__ masks = nullptr,
+                         int nmasks = 0) {
+    if (blockIdx.x != 0) return;
+    // chains of the fused program: one out of range marks the whole sum
+    bool bad = false;
+    for (int i = (int)threadIdx.x; i < nmasks * nz; i += (int)blockDim.x)
+        bad |= chain_out_of_range(meta[(long long)(i / nmasks) * mstride + masks[i % nmasks]].maxbits);
+    if (bad) acc->pad[0] = 1;
+    if (threadIdx.x != 0) return;
     for (int z = 0; z < nz; ++z)
         finish_one<T>(arena + (long long)z * astride, root_off, meta + (long long)z * mstride, root, acc);
 }
