@@ -18,7 +18,7 @@
 #include <array>
 #include <mutex>
 
-#include "wmc_kernels.h"
+#include "wmc_chain.h"
 
 struct BatchRes {
     double m;
@@ -26,11 +26,21 @@ struct BatchRes {
 };
 
 
+// One wave per instance: its root's value, and whether one of its chains
+// (meta entries masks[mask_first[i]] ...) left its range.
+#define WMC_BATCH_RERUN (-0x7fffffffffffffffll)
 template <typename T>
 __global__ void k_finish_batch(const T *__restrict__ arena, const long long *__restrict__ root_off,
-                               const int *__restrict__ root, const wmc_meta *meta, int n, BatchRes *out) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+                               const int *__restrict__ root, const wmc_meta *meta, int n, BatchRes *out,
+                               const int *__restrict__ mask_first, const int *__restrict__ masks) {
+    const int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) / WMC_WAVE), lane = (int)(threadIdx.x % WMC_WAVE);
     if (i >= n) return;
+    bool bad = false;
+    if (mask_first)
+        for (int q = mask_first[i] + lane; q < mask_first[i + 1]; q += WMC_WAVE)
+            bad |= chain_out_of_range(meta[masks[q]].maxbits);
+    bad = __any(bad);
+    if (lane != 0) return;
     if (root[i] < 0) {  // no variables and no clauses: the empty product
         out[i].m = 0.5;
         out[i].e = 1;
@@ -46,8 +56,42 @@ __global__ void k_finish_batch(const T *__restrict__ arena, const long long *__r
         e = 0;
     }
     out[i].m = v;
-    out[i].e = e;
+    out[i].e = bad ? WMC_BATCH_RERUN : e;
 }
+
+// A merged step of the fused programs: short chains and small nodes in one
+// launch, short chains that need more LDS than eight workgroups of a compute
+// unit can share in one (every workgroup of a launch reserves the most any of
+// them needs), chains of many tiles in one, streaming tasks in one, matrix
+// nodes one by one.
+const int kBatchLds = 19 * 1024;
+struct BatchStep {
+    int64_t rec_first = 0, rec_count = 0, wide_first = 0, wide_count = 0, big_first = 0, big_count = 0;
+    int lds = 0, wide_lds = 0, big_lds = 0;
+    int64_t node_first = 0, node_count = 0, node_work = 0, wave_off = 0;
+    int64_t task_first = 0, btask_off = 0;
+    std::array<int, 5> task_nk{{0, 0, 0, 0, 0}};
+    std::vector<int> gemms;
+};
+
+// The instances' fused programs merged by launch index, with an image of
+// their own that takes the place of the launch lists' one.
+struct BatchFused {
+    bool on = false;
+    std::vector<LeafDesc> leaves;
+    std::vector<NodeDesc> nodes;
+    std::vector<GemmDesc> gemms;
+    std::vector<StreamTask> tasks;
+    std::vector<unsigned> words;
+    std::vector<ChainRec> recs;
+    std::vector<int> tables, mask_first, masks;
+    std::vector<long long> root_off;
+    std::vector<BatchStep> steps;
+    // offsets from the descriptor region's start
+    uint64_t o_leaf = 0, o_node = 0, o_gemm = 0, o_tasks = 0, o_words = 0, o_recs = 0, o_tables = 0, o_mask_first = 0,
+             o_masks = 0, o_roots = 0, o_rootoff = 0, o_leaf_eta = 0;
+    std::vector<uint8_t> image;
+};
 
 struct wmc_batch {
     int32_t precision = WMC_FP64;
@@ -89,7 +133,9 @@ struct wmc_batch {
     std::vector<uint8_t> image;  // [off_leaf, off_arena) of the workspace
     std::mutex mu;
     void *graph_ws = nullptr;
-    void *image_ws = nullptr;  // workspace the descriptor image was last uploaded to
+    void *image_ws = nullptr;  // workspace a descriptor image was last uploaded to
+    bool image_fused = false;  // which one: the fused programs' or the launch lists'
+    BatchFused fused;
     // persistent form: the merged steps' arguments (absolute pointers into a
     // workspace, so kept after the arena and rebuilt for a new workspace)
     uint64_t off_steps = 0;
@@ -104,6 +150,128 @@ struct wmc_batch {
 };
 
 static uint64_t bal(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
+
+// Merges the plans' fused programs (iplan, ieta: plan and slice of each
+// instance; abase, mbase: its arena and meta base).
+static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::vector<int64_t> &iplan,
+                       const std::vector<int64_t> &abase, const std::vector<int64_t> &mbase) {
+    BatchFused &F = B.fused;
+    bool any = false;
+    for (int64_t i = 0; i < B.n; ++i) any = any || plans[i]->fused.on;
+    if (!any) return;
+    std::vector<FusedProgram> prog;
+    size_t kmax = 0;
+    for (int64_t i = 0; i < B.n; ++i) {
+        prog.push_back(wmc_program_of(*plans[i]));
+        kmax = std::max(kmax, prog.back().launches.size());
+    }
+    const size_t ni = iplan.size();
+    // leaves keep the launch lists' numbering; only their places differ
+    F.leaves = B.leaves;
+    for (size_t j = 0, q = 0; j < ni; ++j) {
+        const FusedProgram &G = prog[(size_t)iplan[j]];
+        for (const LeafDesc &d : G.leaves) F.leaves[q++].out = d.out + abase[j];
+        const wmc_plan_t &P = *plans[iplan[j]];
+        F.root_off.push_back(P.root < 0 ? 0 : (long long)(G.off[(size_t)P.root] + abase[j]));
+        F.mask_first.push_back((int)F.masks.size());
+        for (int32_t m : G.masks) F.masks.push_back(m + (int)mbase[j]);
+    }
+    F.mask_first.push_back((int)F.masks.size());
+    F.tables.assign(B.tables.begin() + B.leaf_tab_off, B.tables.begin() + B.leaf_tab_off + B.leaf_work / WMC_WAVE);
+    std::vector<int> tab;
+    for (size_t k = 0; k < kmax; ++k) {
+        BatchStep S;
+        std::vector<NodeDesc> small, stream;
+        std::vector<ChainRec> wide, big;
+        S.rec_first = (int64_t)F.recs.size();
+        for (size_t j = 0; j < ni; ++j) {
+            const FusedProgram &G = prog[(size_t)iplan[j]];
+            if (k >= G.launches.size()) continue;
+            const FusedLaunch &L = G.launches[k];
+            for (int32_t q = 0; q < L.node_count && L.type != FUSED_GEMM; ++q) {
+                NodeDesc d = G.nodes[(size_t)(L.node_first + q)];
+                for (long long *o : {&d.a, &d.b, &d.c}) *o += abase[j];
+                for (int *t : {&d.ta, &d.tb, &d.tc}) *t += (int)mbase[j];
+                (L.type == FUSED_NODE ? stream : small).push_back(d);
+            }
+            if (L.type == FUSED_GEMM) {
+                GemmDesc g = G.gemms[(size_t)L.gemm];
+                for (long long *o : {&g.a, &g.b, &g.c}) *o += abase[j];
+                for (int *t : {&g.ta, &g.tb, &g.tc}) *t += (int)mbase[j];
+                S.gemms.push_back((int)F.gemms.size());
+                F.gemms.push_back(g);
+            }
+            int32_t r = L.rec_first;
+            for (int32_t q = 0; q < L.chain_count; ++q) {
+                const ChainTask &t = G.chains[(size_t)(L.chain_first + q)];
+                const unsigned words = G.recs[(size_t)r].words;
+                const unsigned at = wmc_shift_chain(G, t, words, (long long)abase[j], (int)mbase[j], F.words);
+                const int lds = t.lds + (t.big ? 0 : (int)((words * 4 + 1023) / 1024 * 1024 / (unsigned)B.elem));
+                const bool is_wide = !t.big && lds * B.elem > kBatchLds;
+                for (; r < L.rec_first + L.rec_count && G.recs[(size_t)r].desc == t.desc; ++r) {
+                    ChainRec x = G.recs[(size_t)r];
+                    x.desc = at;
+                    (t.big ? big : is_wide ? wide : F.recs).push_back(x);
+                }
+                int &most = t.big ? S.big_lds : is_wide ? S.wide_lds : S.lds;
+                most = std::max(most, lds);
+            }
+        }
+        S.rec_count = (int64_t)F.recs.size() - S.rec_first;
+        S.wide_first = (int64_t)F.recs.size();
+        S.wide_count = (int64_t)wide.size();
+        F.recs.insert(F.recs.end(), wide.begin(), wide.end());
+        S.big_first = (int64_t)F.recs.size();
+        S.big_count = (int64_t)big.size();
+        F.recs.insert(F.recs.end(), big.begin(), big.end());
+        // big nodes become streaming tasks where the task kernel takes them,
+        // small nodes otherwise
+        std::vector<StreamTask> tasks;
+        std::vector<int> nkf;
+        int64_t work = 0;
+        split_stream(stream, tasks, nkf, work, plans[0]->tune.multi_min_rank);
+        small.insert(small.end(), stream.begin(), stream.end());
+        work = 0;
+        for (NodeDesc &d : small) {
+            d.work_begin = work;
+            work += (int64_t)bal(1ull << d.rc, WMC_WAVE);
+        }
+        S.node_first = (int64_t)F.nodes.size();
+        S.node_count = (int64_t)small.size();
+        S.node_work = work;
+        F.nodes.insert(F.nodes.end(), small.begin(), small.end());
+        S.wave_off = (int64_t)F.tables.size();
+        wave_node_table(small, work, tab);
+        F.tables.insert(F.tables.end(), tab.begin(), tab.end());
+        S.task_first = (int64_t)F.tasks.size();
+        S.task_nk = {nkf[0], nkf[1], nkf[2], nkf[3], nkf[4]};
+        S.btask_off = (int64_t)F.tables.size();
+        block_task_table(tasks, nkf, tab);
+        F.tables.insert(F.tables.end(), tab.begin(), tab.end());
+        F.tasks.insert(F.tasks.end(), tasks.begin(), tasks.end());
+        F.steps.push_back(std::move(S));
+    }
+    uint64_t o = 0;
+    auto part = [&](uint64_t &at, const void *src, size_t bytes) {
+        at = o;
+        F.image.resize((size_t)bal(o + std::max<size_t>(bytes, 1), 256), 0);
+        if (bytes) std::memcpy(F.image.data() + o, src, bytes);
+        o = F.image.size();
+    };
+    part(F.o_leaf, F.leaves.data(), sizeof(LeafDesc) * F.leaves.size());
+    part(F.o_node, F.nodes.data(), sizeof(NodeDesc) * F.nodes.size());
+    part(F.o_gemm, F.gemms.data(), sizeof(GemmDesc) * F.gemms.size());
+    part(F.o_tasks, F.tasks.data(), sizeof(StreamTask) * F.tasks.size());
+    part(F.o_words, F.words.data(), sizeof(unsigned) * F.words.size());
+    part(F.o_recs, F.recs.data(), sizeof(ChainRec) * F.recs.size());
+    part(F.o_tables, F.tables.data(), sizeof(int) * F.tables.size());
+    part(F.o_mask_first, F.mask_first.data(), sizeof(int) * F.mask_first.size());
+    part(F.o_masks, F.masks.data(), sizeof(int) * F.masks.size());
+    part(F.o_roots, B.roots.data(), sizeof(int) * B.roots.size());
+    part(F.o_rootoff, F.root_off.data(), sizeof(long long) * F.root_off.size());
+    part(F.o_leaf_eta, B.leaf_eta.data(), sizeof(unsigned long long) * B.leaf_eta.size());
+    F.on = true;
+}
 
 extern "C" wmc_status wmc_batch_create(const wmc_plan_t *const *plans, int64_t n, wmc_batch **out) {
     if (!out) {
@@ -165,7 +333,7 @@ extern "C" wmc_status wmc_batch_create(const wmc_plan_t *const *plans, int64_t n
             const wmc_plan_t &P = *plans[iplan[(size_t)j]];
             abase[(size_t)j] = arena_elems;
             mbase[(size_t)j] = meta;
-            arena_elems += (int64_t)bal(P.arena_bytes / (uint64_t)P.elem, 64);
+            arena_elems += (int64_t)bal(std::max(P.arena_bytes, P.fused.arena_bytes) / (uint64_t)P.elem, 64);
             meta += (int64_t)P.T.size();
         }
         B->n_vars_total = vars;
@@ -284,12 +452,14 @@ extern "C" wmc_status wmc_batch_create(const wmc_plan_t *const *plans, int64_t n
         off += bal(sizeof(unsigned long long) * std::max<size_t>(B->leaf_eta.size(), 1), 256);
         B->off_tables = off;
         off += bal(sizeof(int) * std::max<size_t>(B->tables.size(), 1), 256);
+        B->desc_bytes = off - B->off_leaf;
+        fuse_batch(*B, plans, iplan, abase, mbase);
+        off = std::max(off, B->off_leaf + bal(B->fused.image.size(), 256));
         B->off_arena = off;
         B->arena_bytes = (uint64_t)arena_elems * (uint64_t)B->elem;
         B->off_steps = off + bal(B->arena_bytes, 256);
         // [barrier counter, flag][step arguments]
         B->workspace_bytes = B->off_steps + 256 + bal(sizeof(StepArgs) * B->launches.size(), 256);
-        B->desc_bytes = B->off_arena - B->off_leaf;
         B->image.assign(B->desc_bytes, 0);
         uint8_t *img = B->image.data();
         auto put = [&](uint64_t o, const void *src, size_t bytes) {
@@ -368,9 +538,57 @@ static void batch_launches(const wmc_batch &B, char *ws, hipStream_t st) {
         // the merged step's small nodes and streaming tasks in one launch
         launch_step<T>(step_args(B, ws, k), arena, meta, st);
     }
-    hipLaunchKernelGGL(k_finish_batch<T>, dim3((unsigned)((B.n_inst + 255) / 256)), dim3(256), 0, st, arena,
+    hipLaunchKernelGGL(k_finish_batch<T>, dim3((unsigned)((B.n_inst + 3) / 4)), dim3(4 * WMC_WAVE), 0, st, arena,
                        (const long long *)(ws + B.off_rootoff), (const int *)(ws + B.off_roots), meta, (int)B.n_inst,
-                       (BatchRes *)(ws + B.off_res));
+                       (BatchRes *)(ws + B.off_res), (const int *)nullptr, (const int *)nullptr);
+}
+
+template <typename T>
+static void batch_fused_launches(const wmc_batch &B, char *ws, hipStream_t st) {
+    const BatchFused &F = B.fused;
+    wmc_meta *meta = (wmc_meta *)(ws + B.off_meta);
+    char *img = ws + B.off_leaf;
+    T *arena = (T *)(ws + B.off_arena);
+    const int *tabs = (const int *)(img + F.o_tables);
+    const int nt = (int)B.meta_total;
+    hipLaunchKernelGGL(k_begin, dim3((nt + WMC_BLOCK - 1) / WMC_BLOCK), dim3(WMC_BLOCK), 0, st, meta, nt,
+                       (wmc_acc *)nullptr, 0);
+    if (!F.leaves.empty())
+        hipLaunchKernelGGL(k_leaves<T>, dim3(grid_for(B.leaf_work)), dim3(WMC_BLOCK), 0, st,
+                           (const LeafDesc *)(img + F.o_leaf), (int)F.leaves.size(), (long long)B.leaf_work,
+                           (const double *)(ws + B.off_w), arena, meta, SliceGroup{0, 0, 0}, 0ull, tabs,
+                           (const unsigned long long *)(img + F.o_leaf_eta));
+    for (const BatchStep &S : F.steps) {
+        FusedStepArgs a{};
+        a.recs = (const ChainRec *)(img + F.o_recs) + S.big_first;
+        a.words = (const unsigned *)(img + F.o_words);
+        a.cblocks = (unsigned)S.big_count;
+        if (S.big_count) launch_chain_big<T>(a, S.big_lds, arena, meta, st);
+        if (S.task_nk[4] > 0) {
+            StepArgs t{};
+            step_stream_part(t, (const StreamTask *)(img + F.o_tasks) + S.task_first, F.tasks.data() + S.task_first,
+                             S.task_nk.data(), tabs + S.btask_off);
+            launch_step<T>(t, arena, meta, st);
+        }
+        a.recs = (const ChainRec *)(img + F.o_recs) + S.wide_first;
+        a.cblocks = (unsigned)S.wide_count;
+        launch_fused_step<T, WMC_CHAIN_LANE_MANY>(a, S.wide_lds, arena, meta, st);
+        a.recs = (const ChainRec *)(img + F.o_recs) + S.rec_first;
+        a.cblocks = (unsigned)S.rec_count;
+        a.nodes = (const NodeDesc *)(img + F.o_node) + S.node_first;
+        a.nnodes = (int)S.node_count;
+        a.node_work = S.node_work;
+        a.wave_node = tabs + S.wave_off;
+        a.nblocks = S.node_count ? chain_node_blocks<WMC_CHAIN_LANE_MANY>(S.node_work) : 0;
+        launch_fused_step<T, WMC_CHAIN_LANE_MANY>(a, S.lds, arena, meta, st);
+        for (int g : S.gemms)
+            launch_gemm<T>(F.gemms[(size_t)g], (const GemmDesc *)(img + F.o_gemm) + g, arena, meta, st,
+                           SliceGroup{0, 0, 0}, 1, B.gemm_shape);
+    }
+    hipLaunchKernelGGL(k_finish_batch<T>, dim3((unsigned)((B.n_inst + 3) / 4)), dim3(4 * WMC_WAVE), 0, st, arena,
+                       (const long long *)(img + F.o_rootoff), (const int *)(img + F.o_roots), meta, (int)B.n_inst,
+                       (BatchRes *)(ws + B.off_res), (const int *)(img + F.o_mask_first),
+                       (const int *)(img + F.o_masks));
 }
 
 // Every merged step in one cooperative launch (batches without matrix
@@ -432,9 +650,9 @@ static wmc_status batch_persistent(wmc_batch &B, char *ws, hipStream_t st, bool 
                         (void *)&wait_ticks};
         HIP_TRY(hipLaunchCooperativeKernel((const void *)k_steps_persistent<T>, dim3(grid), dim3(256), args, 0, st));
     }
-    hipLaunchKernelGGL(k_finish_batch<T>, dim3((unsigned)((B.n_inst + 255) / 256)), dim3(256), 0, st, arena,
+    hipLaunchKernelGGL(k_finish_batch<T>, dim3((unsigned)((B.n_inst + 3) / 4)), dim3(4 * WMC_WAVE), 0, st, arena,
                        (const long long *)(ws + B.off_rootoff), (const int *)(ws + B.off_roots), meta, (int)B.n_inst,
-                       (BatchRes *)(ws + B.off_res));
+                       (BatchRes *)(ws + B.off_res), (const int *)nullptr, (const int *)nullptr);
     return WMC_OK;
 }
 
@@ -476,51 +694,62 @@ extern "C" wmc_status wmc_batch_contract(wmc_batch *b, const double *weights, vo
     }
     if (B.n_vars_total > 0)
         HIP_TRY(hipMemcpyAsync(ws + B.off_w, w, sizeof(double) * 2 * (size_t)B.n_vars_total, hipMemcpyHostToDevice, st));
-    // the image goes up unless the caller says it is there already and this
-    // batch did put it into this workspace (a first call on a workspace
-    // always uploads, whatever the flags say)
-    if (!(flags & WMC_BATCH_RESIDENT) || B.image_ws != workspace) {
-        HIP_TRY(hipMemcpyAsync(ws + B.off_leaf, B.image.data(), B.desc_bytes, hipMemcpyHostToDevice, st));
-        B.image_ws = workspace;
-    }
     const bool persistent = (flags & WMC_BATCH_PERSISTENT) && B.gemms.empty() && B.launches.size() > 1;
-    if (persistent) {
-        const bool resident = (flags & WMC_BATCH_RESIDENT) != 0;
-        const wmc_status ps = B.precision == WMC_FP64 ? batch_persistent<double>(B, ws, st, resident)
-                                                      : batch_persistent<float>(B, ws, st, resident);
-        if (ps != WMC_OK) return ps;
-    } else if (flags & WMC_BATCH_GRAPH) {
-        if (B.exec && B.graph_ws != workspace) {
-            HIP_TRY(hipGraphExecDestroy(B.exec));
-            B.exec = nullptr;
-        }
-        if (!B.exec) {
-            if (!B.cap_stream) HIP_TRY(hipStreamCreateWithFlags(&B.cap_stream, hipStreamNonBlocking));
-            hipGraph_t graph = nullptr;
-            HIP_TRY(hipStreamBeginCapture(B.cap_stream, hipStreamCaptureModeThreadLocal));
-            if (B.precision == WMC_FP64) batch_launches<double>(B, ws, B.cap_stream);
-            else batch_launches<float>(B, ws, B.cap_stream);
-            HIP_TRY(hipStreamEndCapture(B.cap_stream, &graph));
-            hipError_t e = hipGraphInstantiate(&B.exec, graph, nullptr, nullptr, 0);
-            (void)hipGraphDestroy(graph);
-            if (e != hipSuccess) {
-                B.exec = nullptr;
-                wmc_set_error("hipGraphInstantiate failed: %s", hipGetErrorString(e));
-                return WMC_ERR_DEVICE;
-            }
-            B.graph_ws = workspace;
-        }
-        HIP_TRY(hipGraphLaunch(B.exec, st));
-    } else {
-        if (B.precision == WMC_FP64) batch_launches<double>(B, ws, st);
-        else batch_launches<float>(B, ws, st);
-    }
-    HIP_TRY(hipGetLastError());
     std::vector<BatchRes> h((size_t)B.n_inst);
-    HIP_TRY(hipMemcpyAsync(h.data(), ws + B.off_res, sizeof(BatchRes) * (size_t)B.n_inst, hipMemcpyDeviceToHost, st));
     unsigned gave_up = 0;
-    if (persistent) HIP_TRY(hipMemcpyAsync(&gave_up, ws + B.off_steps + 4, 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
+    // the fused programs, and once more the launch lists if a chain left its
+    // range (the persistent form runs the launch lists)
+    for (bool fused = B.fused.on && !persistent;; fused = false) {
+        // the image goes up unless the caller says it is there already and
+        // this batch did put it into this workspace (a first call on a
+        // workspace always uploads, whatever the flags say)
+        if (!(flags & WMC_BATCH_RESIDENT) || B.image_ws != workspace || B.image_fused != fused) {
+            const std::vector<uint8_t> &img = fused ? B.fused.image : B.image;
+            HIP_TRY(hipMemcpyAsync(ws + B.off_leaf, img.data(), img.size(), hipMemcpyHostToDevice, st));
+            B.image_ws = workspace;
+            B.image_fused = fused;
+        }
+        auto launch = [&](hipStream_t to) {
+            if (B.precision == WMC_FP64) fused ? batch_fused_launches<double>(B, ws, to) : batch_launches<double>(B, ws, to);
+            else fused ? batch_fused_launches<float>(B, ws, to) : batch_launches<float>(B, ws, to);
+        };
+        if (persistent) {
+            const bool resident = (flags & WMC_BATCH_RESIDENT) != 0;
+            const wmc_status ps = B.precision == WMC_FP64 ? batch_persistent<double>(B, ws, st, resident)
+                                                          : batch_persistent<float>(B, ws, st, resident);
+            if (ps != WMC_OK) return ps;
+        } else if ((flags & WMC_BATCH_GRAPH) && fused == B.fused.on) {
+            if (B.exec && B.graph_ws != workspace) {
+                HIP_TRY(hipGraphExecDestroy(B.exec));
+                B.exec = nullptr;
+            }
+            if (!B.exec) {
+                if (!B.cap_stream) HIP_TRY(hipStreamCreateWithFlags(&B.cap_stream, hipStreamNonBlocking));
+                hipGraph_t graph = nullptr;
+                HIP_TRY(hipStreamBeginCapture(B.cap_stream, hipStreamCaptureModeThreadLocal));
+                launch(B.cap_stream);
+                HIP_TRY(hipStreamEndCapture(B.cap_stream, &graph));
+                hipError_t e = hipGraphInstantiate(&B.exec, graph, nullptr, nullptr, 0);
+                (void)hipGraphDestroy(graph);
+                if (e != hipSuccess) {
+                    B.exec = nullptr;
+                    wmc_set_error("hipGraphInstantiate failed: %s", hipGetErrorString(e));
+                    return WMC_ERR_DEVICE;
+                }
+                B.graph_ws = workspace;
+            }
+            HIP_TRY(hipGraphLaunch(B.exec, st));
+        } else {
+            launch(st);
+        }
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipMemcpyAsync(h.data(), ws + B.off_res, sizeof(BatchRes) * (size_t)B.n_inst, hipMemcpyDeviceToHost, st));
+        if (persistent) HIP_TRY(hipMemcpyAsync(&gave_up, ws + B.off_steps + 4, 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        bool again = false;
+        for (const BatchRes &r : h) again = again || r.e == WMC_BATCH_RERUN;
+        if (!fused || !again) break;
+    }
     if (gave_up) {
         wmc_set_error("wmc_batch_contract: a grid barrier of the persistent launch timed out");
         return WMC_ERR_DEVICE;

@@ -13,8 +13,8 @@
 // only the power of two an intermediate is stored with differs (it cannot
 // be brought to [0.5, 1) before all its tiles exist).  Each stage therefore
 // reports whether it had an entry of ordinary size: if an intermediate was
-// nonzero but everywhere below WMC_CHAIN_TINY, the caller runs the general
-// launch list instead.
+// nonzero but everywhere below chain_tiny, the caller runs the general launch
+// list instead.
 #pragma once
 #include "wmc_kernels.h"
 
@@ -25,12 +25,16 @@ __device__ __forceinline__ chain_words const_words(const unsigned *p) {
     return (chain_words)(unsigned long long)p;
 }
 
-// Smallest magnitude of an intermediate's largest entry that still leaves
-// the type's range below it: 2^-32 for FP32 (2^-94 below it before the
-// smallest normal number), 2^-128 for FP64.
+// FP32 intermediates are kept 2^64 larger (at most 2^(64 + 45) after 15
+// stages of 8 terms each), so that an intermediate may lose 96 bits of
+// magnitude against F_0 before its largest entry falls below chain_tiny, and
+// 94 more bits of entries below that one are still normal numbers.  The last
+// stage takes the 2^64 back.
 template <typename T>
-__device__ __forceinline__ constexpr double chain_tiny() {
-    return sizeof(T) == 4 ? 0x1p-32 : 0x1p-128;
+__device__ __forceinline__ constexpr int chain_lift() { return sizeof(T) == 4 ? 64 : 0; }
+template <typename T>
+__device__ __forceinline__ constexpr double chain_tiny(bool last) {
+    return sizeof(T) == 4 ? (last ? 0x1p-64 : 0x1p-32) : (last ? 0x1p-512 : 0x1p-128);
 }
 
 // LDS entry e sits at slot chain_slot(e): 16-byte units XOR-ed with the
@@ -74,19 +78,21 @@ __device__ __forceinline__ void chain_row(const T *lds, unsigned slot, double *v
 // Copies the part of an operand that a tile reads into LDS, where entry q
 // goes to slot q: memory to LDS directly, without a register in between, so
 // that all copies of a tile are in flight together (the caller waits for
-// them).  x: the operand's CX_ words; src: its first entry for the tile; the
-// calling waves take runs wave, wave + WAVES, ... of 64 pieces.
-template <typename T, int WAVES, typename WP>
-__device__ __forceinline__ void chain_copy(WP x, const T *src, T *lds, unsigned wave) {
+// them).  ch: the chain's words; x: the operand's; src: its first entry for
+// the tile; the calling waves take runs wave, wave + WAVES, ... of 64 pieces.
+template <typename T, int WAVES>
+__device__ __forceinline__ void chain_copy(const unsigned *ch, const unsigned *x, const T *src, T *lds, unsigned wave) {
     typedef const __attribute__((address_space(1))) unsigned *gp;
     typedef __attribute__((address_space(3))) unsigned *lp;
     constexpr unsigned EW = sizeof(T) / 4, VE = 16 / sizeof(T);  // words per entry, entries per 16 bytes
-    const unsigned nb = __builtin_amdgcn_readfirstlane(x[CX_BITS]), low = __builtin_amdgcn_readfirstlane(x[CX_LOW]);
-    T *dst = lds + __builtin_amdgcn_readfirstlane(x[CX_LDS]);
+    const uint4 xv = *(const uint4 *)x;
+    const unsigned nb = __builtin_amdgcn_readfirstlane(xv.x), low = __builtin_amdgcn_readfirstlane(xv.y);
+    T *dst = lds + __builtin_amdgcn_readfirstlane(xv.z);
+    const unsigned *list = ch + __builtin_amdgcn_readfirstlane(xv.w);
     const unsigned lane = threadIdx.x & 63u;
     auto offset = [&](unsigned q) {
         unsigned o = q & ((1u << low) - 1u);
-        for (unsigned b = low; b < nb; ++b) o |= (0u - ((q >> b) & 1u)) & x[CX_OFF + b];
+        for (unsigned b = low; b < nb; ++b) o |= (0u - ((q >> b) & 1u)) & list[b - low];
         return o;
     };
     if ((1u << low) >= VE) {  // runs of 16 bytes
@@ -110,11 +116,12 @@ __device__ __forceinline__ void chain_copy(WP x, const T *src, T *lds, unsigned 
 // the tiles' and copies' memory, w the stage's words (in LDS, 16-byte
 // aligned).  Without register bits the entry index of an LDS output is the
 // thread and entry index itself.
-template <typename T, int NK, bool SG, bool DG>
-__device__ __forceinline__ void chain_stage_short(const unsigned *w, unsigned tb, const T *__restrict__ S,
+template <typename T, int LB, int NK, bool SG, bool DG>
+__device__ __forceinline__ void chain_stage_short(const unsigned *ch, const unsigned *w, unsigned tb,
+                                                  const T *__restrict__ S,
                                                   T *__restrict__ C, T *lds, const unsigned *mask, int se,
                                                   double &vmax) {
-    constexpr int K = 1 << NK, LB = WMC_CHAIN_LANE;
+    constexpr int K = 1 << NK;
     const uint4 head = *(const uint4 *)(w + 4);  // CS_TG, CS_SRC, CS_DST
     const unsigned sbase = __builtin_amdgcn_readfirstlane(head.y), dbase = __builtin_amdgcn_readfirstlane(head.z);
     const unsigned gbase = __builtin_amdgcn_readfirstlane(w[CS_X + CX_LDS]);
@@ -133,19 +140,26 @@ __device__ __forceinline__ void chain_stage_short(const unsigned *w, unsigned tb
         for (int b = 0; b < LB; ++b) r |= mask[b] & v[b];
         return r;
     };
-    unsigned src = map(w + CS_BIT_S), g = map(w + CS_BIT_G), out = DG ? map(w + CS_BIT_O) : threadIdx.x;
+    // source and G together: their indices fit half words, and slots, starts
+    // and bit steps act on both halves at once
+    unsigned sg = map(w + CS_BIT_SG), src = 0, out = threadIdx.x;
+    if constexpr (SG) src = map(ch + CH_SRC);
+    if constexpr (DG) out = map(ch + CH_OUT);
+    const unsigned bases = sbase | (gbase << 16);
+    constexpr unsigned swz = sizeof(T) == 8 ? 0x000E000Eu : 0x001C001Cu;
     if (tb < LB && threadIdx.x >> tb) return;
     const unsigned nh = tb > LB ? 1u << (tb - LB) : 1u;
 #pragma clang loop unroll(disable)
     for (unsigned h = 0;;) {
         double sv[K], gv[K];
-        chain_row<T, K>(lds, chain_slot<T>(g) ^ gbase, gv);
+        const unsigned slots = sg ^ ((sg >> 3) & swz) ^ bases;
+        chain_row<T, K>(lds, slots >> 16, gv);
         if constexpr (SG) {
             constexpr int KC = K < 4 ? K : 4;
 #pragma unroll
             for (int kc = 0; kc < K; kc += KC) load_chunk<T, KC>(S + src + kc, sv + kc);
         } else {
-            chain_row<T, K>(lds, chain_slot<T>(src) ^ sbase, sv);
+            chain_row<T, K>(lds, slots & 0xFFFFu, sv);
         }
         double acc = 0.0;
 #pragma unroll
@@ -162,25 +176,25 @@ __device__ __forceinline__ void chain_stage_short(const unsigned *w, unsigned tb
         if (++h == nh) break;
         // entry index in Gray order: one bit changes
         const unsigned b = LB + __builtin_ctz(h);
-        src ^= w[CS_BIT_S + b];
-        g ^= w[CS_BIT_G + b];
-        if constexpr (DG) out ^= w[CS_BIT_O + b];
+        sg ^= w[CS_BIT_SG + b];
+        if constexpr (SG) src ^= ch[CH_SRC + b];
+        if constexpr (DG) out ^= ch[CH_OUT + b];
         else out ^= 1u << b;
     }
 }
 
-template <typename T, bool SG, bool DG>
-__device__ __forceinline__ void chain_stage_short_any(const unsigned *w, unsigned wave, const T *S, T *C, T *lds,
-                                                      const unsigned *mask, int se, double &vmax) {
+template <typename T, int LB, bool SG, bool DG>
+__device__ __forceinline__ void chain_stage_short_any(const unsigned *ch, const unsigned *w, unsigned wave, const T *S,
+                                                      T *C, T *lds, const unsigned *mask, int se, double &vmax) {
     const uint2 head = *(const uint2 *)w;  // CS_SHAPE, CS_TBITS
     const unsigned nk = __builtin_amdgcn_readfirstlane(head.x), tb = __builtin_amdgcn_readfirstlane(head.y);
     // waves past a small tile's last entry have nothing to do
-    if (tb < WMC_CHAIN_LANE && (wave << 6) >> tb) return;
+    if (tb < LB && (wave << 6) >> tb) return;
     switch (nk) {
-    case 0: chain_stage_short<T, 0, SG, DG>(w, tb, S, C, lds, mask, se, vmax); break;
-    case 1: chain_stage_short<T, 1, SG, DG>(w, tb, S, C, lds, mask, se, vmax); break;
-    case 2: chain_stage_short<T, 2, SG, DG>(w, tb, S, C, lds, mask, se, vmax); break;
-    default: chain_stage_short<T, 3, SG, DG>(w, tb, S, C, lds, mask, se, vmax); break;
+    case 0: chain_stage_short<T, LB, 0, SG, DG>(ch, w, tb, S, C, lds, mask, se, vmax); break;
+    case 1: chain_stage_short<T, LB, 1, SG, DG>(ch, w, tb, S, C, lds, mask, se, vmax); break;
+    case 2: chain_stage_short<T, LB, 2, SG, DG>(ch, w, tb, S, C, lds, mask, se, vmax); break;
+    default: chain_stage_short<T, LB, 3, SG, DG>(ch, w, tb, S, C, lds, mask, se, vmax); break;
     }
 }
 
@@ -336,17 +350,17 @@ struct ChainLanes {
 };
 
 // The loads of the scale data are not waited for here.
-template <typename WP>
+template <int STRIDE, typename WP>
 __device__ __forceinline__ ChainLanes chain_lanes(WP ch, unsigned L, unsigned ob, unsigned tile, const wmc_meta *meta) {
     const unsigned lane = threadIdx.x & 63u;
     ChainLanes c{0, 0, 0};
     if (lane <= L) {
-        const wmc_meta *m = meta + ch[lane < L ? CH_WORDS + lane * CS_WORDS + CS_TG : CH_TF];
+        const wmc_meta *m = meta + ch[lane < L ? CH_WORDS + lane * STRIDE + CS_TG : CH_TF];
         c.maxbits = m->maxbits;
         c.exp = m->exp;
     }
     if (lane < L + 2) {
-        const unsigned tab = CH_WORDS + L * CS_WORDS + lane * ob;
+        const unsigned tab = CH_WORDS + L * STRIDE + lane * ob;
         for (unsigned b = 0; b < ob; ++b) c.off ^= (0u - ((tile >> b) & 1u)) & ch[tab + b];
     }
     return c;
@@ -354,7 +368,8 @@ __device__ __forceinline__ ChainLanes chain_lanes(WP ch, unsigned L, unsigned ob
 
 // In lane i, the power of two stage i's products are scaled by; the first
 // workgroup also publishes the chain's exponent.
-__device__ __forceinline__ int chain_shifts(const ChainLanes &c, unsigned L, wmc_meta *meta, unsigned tc, bool first) {
+__device__ __forceinline__ int chain_shifts(const ChainLanes &c, unsigned L, wmc_meta *meta, unsigned tc, bool first,
+                                            int lift) {
     const unsigned lane = threadIdx.x & 63u;
     const int own = lane <= L ? scale_exp(c.maxbits) : 0;
     if (first && threadIdx.x < 64) {
@@ -363,14 +378,14 @@ __device__ __forceinline__ int chain_shifts(const ChainLanes &c, unsigned L, wmc
         if (lane == 0) meta[tc].exp = e;
     }
     const int f = __builtin_amdgcn_readlane(own, L);
-    return lane == 0 ? -own - f : -own;
+    return (lane == 0 ? lift - own - f : -own) - (lane + 1 == L ? lift : 0);
 }
 
 // Range bits of stage s's intermediate, whose largest magnitude in this
 // thread is v: an ordinary entry, a nonzero entry.
 template <typename T>
-__device__ __forceinline__ unsigned chain_range(double v, unsigned s) {
-    return ((v >= chain_tiny<T>() ? 1u : 0u) | (v > 0.0 ? 2u : 0u)) << (2 * s);
+__device__ __forceinline__ unsigned chain_range(double v, unsigned s, bool last) {
+    return ((v >= chain_tiny<T>(last) ? 1u : 0u) | (v > 0.0 ? 2u : 0u)) << (2 * s);
 }
 
 __device__ __forceinline__ void chain_end(wmc_meta *meta, unsigned tmask, unsigned tc, unsigned range, double vmax) {
@@ -387,46 +402,49 @@ __device__ __forceinline__ long long chain_base(unsigned lo, unsigned hi) {
     return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
-// One tile of a short chain.  smem: the chain's words, then (from the next
+// One tile of a short chain, by a workgroup of 2^LB threads: 2^9 where a call
+// waits for it, 2^8 where many chains share the device and each wave's fixed
+// instructions count.  smem: the chain's words, then (from the next
 // 1024-byte boundary) its LDS entries.
-template <typename T>
+template <typename T, int LB>
 __device__ __forceinline__ void chain_run_short(const unsigned *__restrict__ words, unsigned nwords, unsigned tile,
                                                 T *__restrict__ arena, wmc_meta *meta, char *smem) {
     const unsigned tid = threadIdx.x;
     unsigned *ch = (unsigned *)smem;
     T *lds = (T *)(smem + ((nwords * 4u + 1023u) & ~1023u));
     {
-        unsigned v[3];
+        constexpr unsigned NV = (3u << WMC_CHAIN_LANE) >> LB;  // words are at most 3 << WMC_CHAIN_LANE
+        unsigned v[NV];
 #pragma unroll
-        for (unsigned j = 0; j < 3; ++j)
-            if (tid + (j << WMC_CHAIN_LANE) < nwords) v[j] = words[tid + (j << WMC_CHAIN_LANE)];
+        for (unsigned j = 0; j < NV; ++j)
+            if (tid + (j << LB) < nwords) v[j] = words[tid + (j << LB)];
 #pragma unroll
-        for (unsigned j = 0; j < 3; ++j)
-            if (tid + (j << WMC_CHAIN_LANE) < nwords) ch[tid + (j << WMC_CHAIN_LANE)] = v[j];
+        for (unsigned j = 0; j < NV; ++j)
+            if (tid + (j << LB) < nwords) ch[tid + (j << LB)] = v[j];
     }
     __syncthreads();
     auto uni = [](unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane(x); };
     const unsigned L = uni(ch[CH_STAGES]), ob = uni(ch[CH_TILE_BITS]), wave = uni(tid >> 6);
-    const ChainLanes cl = chain_lanes(ch, L, ob, tile, meta);
+    const ChainLanes cl = chain_lanes<CS_WORDS>(ch, L, ob, tile, meta);
     const T *F0 = arena + chain_base(uni(ch[CH_F]), uni(ch[CH_F_HI])) + (unsigned)__builtin_amdgcn_readlane(cl.off, 0);
     T *C = arena + chain_base(uni(ch[CH_C]), uni(ch[CH_C_HI])) + (unsigned)__builtin_amdgcn_readlane(cl.off, 1);
     const bool fcopy = uni(ch[CH_FCOPY]) != 0u;
-    constexpr int WAVES = 1 << (WMC_CHAIN_LANE - 6);
-    if (fcopy) chain_copy<T, WAVES>(ch + CH_X, F0, lds, wave);
+    constexpr int WAVES = 1 << (LB - 6);
+    if (fcopy) chain_copy<T, WAVES>(ch, ch + CH_X, F0, lds, wave);
     // the G_i are small: one wave copies each
 #pragma clang loop unroll(disable)
     for (unsigned s = wave; s < L; s += WAVES) {
         const unsigned *w = ch + CH_WORDS + s * CS_WORDS;
-        chain_copy<T, 1>(w + CS_X,
+        chain_copy<T, 1>(ch, w + CS_X,
                          arena + chain_base(uni(w[CS_G]), uni(w[CS_G_HI])) +
                              (unsigned)__builtin_amdgcn_readlane(cl.off, 2 + s),
                          lds, 0u);
     }
-    unsigned mask[WMC_CHAIN_LANE];
+    unsigned mask[LB];
 #pragma unroll
-    for (int b = 0; b < WMC_CHAIN_LANE; ++b) mask[b] = 0u - ((tid >> b) & 1u);
+    for (int b = 0; b < LB; ++b) mask[b] = 0u - ((tid >> b) & 1u);
     const unsigned tc = uni(ch[CH_TC]);
-    const int shift = chain_shifts(cl, L, meta, tc, tile == 0u);
+    const int shift = chain_shifts(cl, L, meta, tc, tile == 0u, chain_lift<T>());
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     unsigned range = 0;
@@ -437,11 +455,12 @@ __device__ __forceinline__ void chain_run_short(const unsigned *__restrict__ wor
         const int se = __builtin_amdgcn_readlane(shift, s);
         double v = 0.0;
         if (s + 1 == L) {
-            chain_stage_short_any<T, false, true>(w, wave, F0, C, lds, mask, se, vmax);
+            chain_stage_short_any<T, LB, false, true>(ch, w, wave, F0, C, lds, mask, se, vmax);
+            range |= chain_range<T>(vmax, s, true);
         } else {
-            if (s == 0 && !fcopy) chain_stage_short_any<T, true, false>(w, wave, F0, C, lds, mask, se, v);
-            else chain_stage_short_any<T, false, false>(w, wave, F0, C, lds, mask, se, v);
-            range |= chain_range<T>(v, s);
+            if (s == 0 && !fcopy) chain_stage_short_any<T, LB, true, false>(ch, w, wave, F0, C, lds, mask, se, v);
+            else chain_stage_short_any<T, LB, false, false>(ch, w, wave, F0, C, lds, mask, se, v);
+            range |= chain_range<T>(v, s, false);
             chain_barrier();
         }
     }
@@ -456,10 +475,10 @@ __device__ __forceinline__ void chain_run_big(chain_words ch, unsigned blk, unsi
                                               wmc_meta *meta, T *lds) {
     const unsigned tid = threadIdx.x, lane = tid & 63u;
     const unsigned L = ch[CH_STAGES], ob = ch[CH_TILE_BITS];
-    const ChainLanes cl = chain_lanes(ch, L, ob, blk << jb, meta);
+    const ChainLanes cl = chain_lanes<CS_WORDS_BIG>(ch, L, ob, blk << jb, meta);
     unsigned cur = cl.off;
-    const int shift = chain_shifts(cl, L, meta, ch[CH_TC], blk == 0u);
-    const unsigned tab = CH_WORDS + L * CS_WORDS + lane * ob;
+    const int shift = chain_shifts(cl, L, meta, ch[CH_TC], blk == 0u, chain_lift<T>());
+    const unsigned tab = CH_WORDS + L * CS_WORDS_BIG + lane * ob;
     unsigned mask[6];
 #pragma unroll
     for (int b = 0; b < 6; ++b) mask[b] = 0u - ((tid >> b) & 1u);
@@ -478,17 +497,18 @@ __device__ __forceinline__ void chain_run_big(chain_words ch, unsigned blk, unsi
         if (i + 1 < ntile && lane < L + 2) flip = ch[tab + __builtin_ctz(i + 1)];
 #pragma clang loop unroll(disable)
         for (unsigned s = 0; s < L; ++s) {
-            chain_words st = ch + CH_WORDS + s * CS_WORDS;
+            chain_words st = ch + CH_WORDS + s * CS_WORDS_BIG;
             const T *G = arena + chain_base(st[CS_G], st[CS_G_HI]) + (unsigned)__builtin_amdgcn_readlane(cur, 2 + s);
             const int se = __builtin_amdgcn_readlane(shift, s);
             double v = 0.0;
             if (s + 1 == L) {
                 chain_stage_any<T, false, true>(st, S, G, C, lds, mask, wave, se, nt, v);
                 vmax = fmax(vmax, v);
+                range |= chain_range<T>(v, s, true);
             } else {
                 if (s == 0) chain_stage_any<T, true, false>(st, S, G, C, lds, mask, wave, se, nt, v);
                 else chain_stage_any<T, false, false>(st, S, G, C, lds, mask, wave, se, nt, v);
-                range |= chain_range<T>(v, s);
+                range |= chain_range<T>(v, s, false);
             }
             chain_barrier();
         }
@@ -509,17 +529,16 @@ struct FusedStepArgs {
     int nnodes, pad;
 };
 
-#define WMC_CHAIN_THREADS (1 << WMC_CHAIN_LANE)
 #define WMC_CHAIN_THREADS_BIG (1 << WMC_CHAIN_LANE_BIG)
 
-template <typename T>
-__global__ void __launch_bounds__(WMC_CHAIN_THREADS) k_chain(const FusedStepArgs a, T *__restrict__ arena,
-                                                             wmc_meta *meta, const SliceGroup sg) {
+template <typename T, int LB>
+__global__ void __launch_bounds__(1 << LB) k_chain(const FusedStepArgs a, T *__restrict__ arena, wmc_meta *meta,
+                                                   const SliceGroup sg) {
     WMC_ENTER_SLICE(arena, meta, sg);
     extern __shared__ char smem_raw[];
     if (blockIdx.x < a.cblocks) {
         chain_words r = const_words((const unsigned *)(a.recs + blockIdx.x));
-        chain_run_short<T>(a.words + r[0], r[3], r[1], arena, meta, smem_raw);
+        chain_run_short<T, LB>(a.words + r[0], r[3], r[1], arena, meta, smem_raw);
     } else {
         nodes_body<T>(a.nodes, a.nnodes, a.node_work, arena, meta, a.wave_node, blockIdx.x - a.cblocks, a.nblocks);
     }
@@ -536,18 +555,20 @@ __global__ void __launch_bounds__(WMC_CHAIN_THREADS_BIG) k_chain_big(const Chain
     chain_run_big<T>(const_words(words) + r[0], r[1], r[2], arena, meta, (T *)smem_raw);
 }
 
+// Workgroups of 2^LB threads for a step's small nodes.
+template <int LB>
 static inline unsigned chain_node_blocks(long long work) {
-    const long long b = (work + WMC_CHAIN_THREADS - 1) / WMC_CHAIN_THREADS;
+    const long long b = (work + (1 << LB) - 1) >> LB;
     return (unsigned)(b > (1ll << 20) ? 1ll << 20 : b);
 }
 
-template <typename T>
+template <typename T, int LB>
 static inline void launch_fused_step(const FusedStepArgs &a, int lds, T *arena, wmc_meta *meta, hipStream_t st,
                                      const SliceGroup sg = SliceGroup{0, 0, 0}, unsigned nz = 1) {
     const unsigned g = a.cblocks + a.nblocks;
     if (g)
-        hipLaunchKernelGGL(k_chain<T>, dim3(g, 1, nz), dim3(WMC_CHAIN_THREADS), (size_t)lds * sizeof(T), st, a, arena,
-                           meta, sg);
+        hipLaunchKernelGGL((k_chain<T, LB>), dim3(g, 1, nz), dim3(1 << LB), (size_t)lds * sizeof(T), st, a, arena, meta,
+                           sg);
 }
 
 template <typename T>

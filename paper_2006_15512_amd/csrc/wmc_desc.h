@@ -93,43 +93,57 @@ struct GemmDesc {
 // other variables of F_L number the tiles.  In a short chain the parts of the
 // G_i and of F_0 that a tile reads are copied to LDS first.  Every
 // address is a bit deposit of the tile index and of the entry index within
-// the tile, so a chain is a list of 32-bit words: this header, L stages of
-// CS_WORDS words, then the offsets of each tile index bit (CH_TILE_BITS words
-// each) in F_0, C and every G_i.
+// the tile, so a chain is a list of 32-bit words: the header, the stages, the
+// offsets of each tile index bit (CH_TILE_BITS words each) in F_0, C and every
+// G_i, and the lists that copies refer to.
 #define WMC_CHAIN_MAX 15        // stages
 #define WMC_CHAIN_NK 3          // summed variables of a stage
 #define WMC_CHAIN_BITS 13       // entry bits of a tile
-#define WMC_CHAIN_LANE 9        // log2 of a workgroup's threads: short chains,
+#define WMC_CHAIN_LANE 9        // log2 of a workgroup's threads: short chains of one call,
+#define WMC_CHAIN_LANE_MANY 8   // of many calls together,
 #define WMC_CHAIN_LANE_BIG 8    // and chains of many tiles
-#define WMC_CHAIN_LDS (56 * 1024)
+// LDS bytes of a chain, its words included.  Short chains: four workgroups
+// of 8 waves fill a compute unit's 32 wave slots, so its 160 KB are shared by
+// four; many tiles: three workgroups of 4 waves at 110 registers.
+#define WMC_CHAIN_LDS_SHORT (38 * 1024)
+#define WMC_CHAIN_LDS (50 * 1024)
 #define WMC_CHAIN_TILE_BITS 11  // largest tile index of a short chain
 // A copied operand: log2 of its entries per tile, the lowest of them whose
-// offset is the entry index itself, its first LDS entry, and the offsets of
-// the other index bits.
-enum { CX_BITS = 0, CX_LOW, CX_LDS, CX_OFF, CX_WORDS = CX_OFF + WMC_CHAIN_BITS };
+// offset is the entry index itself, its first LDS entry, and the word where
+// the offsets of the other index bits are listed.
+enum { CX_BITS = 0, CX_LOW, CX_LDS, CX_LIST, CX_WORDS };
 enum {
     CH_STAGES = 0, CH_TILE_BITS, CH_F, CH_F_HI, CH_C, CH_C_HI, CH_TF, CH_TC,
     CH_MASK,                    // meta entry that collects the stages' range bits
     CH_NT,                      // C is stored non-temporally
     CH_FCOPY,                   // F_0 is copied to LDS
+    CH_TILES,                   // word where the tile index bits are listed
     CH_X,
-    CH_WORDS = CH_X + CX_WORDS + 1
+    CH_OUT = CH_X + CX_WORDS,   // short chains: last outputs' offsets of the entry bits
+    CH_SRC = CH_OUT + 16,       // and F_0's, where it is not copied
+    CH_WORDS = CH_SRC + 16
 };
-// A stage: the register bits (chains of many tiles only: up to two that only
-// the source has, with their source and output offsets, and up to two that
-// only G has, with their G and output offsets), the source, G and output
-// offsets of the other entry bits, and the copy of G.  Sources, copies and
-// outputs are LDS entries except F_0 where it is not copied and the last
-// output.
+// A stage: in a short chain, the offsets of the tile's entry bits in the
+// source (low half of a word) and in G's copy (high half), then the copy; the
+// entry index is the index of an output in LDS.  In a chain of many tiles the
+// offsets have a word each, some bits are taken inside the thread (up to two
+// that only the source has, with their source and output offsets, and up to
+// two that only G has, with their G and output offsets), and the output
+// offsets of the others are listed too.  Sources, copies and outputs are LDS
+// entries except F_0 where it is not copied and the last output.
 enum {
     CS_SHAPE = 0,               // nk | source-only register bits << 8 | G-only ones << 16
     CS_TBITS, CS_G, CS_G_HI, CS_TG, CS_SRC, CS_DST, CS_PAD,
-    CS_PS, CS_PO = CS_PS + 2, CS_QG = CS_PO + 2, CS_QO = CS_QG + 2,
-    CS_BIT_S = CS_QO + 2, CS_BIT_G = CS_BIT_S + 16, CS_BIT_O = CS_BIT_G + 16,
-    CS_X = CS_BIT_O + 16,
-    CS_WORDS = CS_X + CX_WORDS
+    CS_BIT_SG,                  // short
+    CS_X = CS_BIT_SG + 16,
+    CS_WORDS = CS_X + CX_WORDS,
+    CS_BIT_S = CS_BIT_SG,       // many tiles
+    CS_BIT_G = CS_BIT_S + 16, CS_BIT_O = CS_BIT_G + 16,
+    CS_PS = CS_BIT_O + 16, CS_PO = CS_PS + 2, CS_QG = CS_PO + 2, CS_QO = CS_QG + 2,
+    CS_WORDS_BIG = CS_QO + 2
 };
-static_assert(CH_WORDS % 4 == 0 && CS_WORDS % 4 == 0 && WMC_CHAIN_BITS <= 16, "words are read four at a time");
+static_assert(CH_WORDS % 4 == 0 && CS_WORDS % 4 == 0 && CS_WORDS_BIG % 4 == 0 && WMC_CHAIN_BITS <= 16,
+              "words are read four at a time");
 // One workgroup of a chain launch: tiles [blk << jbits, (blk + 1) << jbits)
 // of the chain at word `desc`, which has `words` words.
 struct ChainRec {

@@ -143,9 +143,9 @@ static void fused_launches(const wmc_plan_t &P, char *ws, T *arena, wmc_meta *me
             a.nnodes = Ln.node_count;
             a.node_work = Ln.node_work;
             a.wave_node = Ln.tab >= 0 ? TB + Ln.tab : nullptr;
-            a.nblocks = Ln.node_count ? chain_node_blocks(Ln.node_work) : 0;
+            a.nblocks = Ln.node_count ? chain_node_blocks<WMC_CHAIN_LANE>(Ln.node_work) : 0;
             if (Ln.type == FUSED_CHAIN) launch_chain_big<T>(a, Ln.lds, arena, meta, st, sg, nz);
-            else launch_fused_step<T>(a, Ln.lds, arena, meta, st, sg, nz);
+            else launch_fused_step<T, WMC_CHAIN_LANE>(a, Ln.lds, arena, meta, st, sg, nz);
         }
         if (tm) tm->mark();
     }

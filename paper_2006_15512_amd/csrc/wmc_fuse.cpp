@@ -140,8 +140,9 @@ struct Fuser {
         }
         total += odd + std::max(even, f);
         // the words of a short chain are read from LDS, too
-        const long long words = CH_WORDS + (long long)L * CS_WORDS + (long long)(L + 2) * WMC_CHAIN_TILE_BITS;
-        if (total * elem + words * 4 + 1024 > WMC_CHAIN_LDS) return false;
+        const long long words =
+            CH_WORDS + (long long)L * CS_WORDS + (long long)(L + 2) * WMC_CHAIN_TILE_BITS + (long long)(L + 1) * WMC_CHAIN_BITS;
+        if (total * elem + (copy_g ? words * 4 + 1024 : 0) > (copy_g ? WMC_CHAIN_LDS_SHORT : WMC_CHAIN_LDS)) return false;
         std::vector<std::pair<int, int>> r = {{odd, -1}, {std::max(even, f), -2}};
         for (size_t i = 0; i < L; ++i) r.push_back({g[i], (int)i});
         std::stable_sort(r.begin(), r.end(), [](auto &x, auto &y) { return x.first > y.first; });
@@ -285,19 +286,22 @@ struct Fuser {
         const std::vector<int> pf = place(h.f), pl = place(h.nodes.back());
         // an operand's copy: its variables summed at the stage or inside the
         // tile, in storage order; returns their bit positions in the copy
+        std::vector<std::pair<size_t, std::vector<unsigned>>> lists;
         auto copy = [&](size_t x, int32_t tensor, uint64_t vars, int lds) {
             std::vector<int> at(h.local.size(), -1);
             const std::vector<int32_t> &lay = T[(size_t)tensor].layout;
-            unsigned n = 0, low = 0;
+            std::vector<unsigned> off;
+            unsigned low = 0;
             for (size_t q = 0; q < lay.size(); ++q) {
                 if (!(vars & bit(lay[q]))) continue;
-                at[(size_t)id_of[(size_t)lay[q]]] = (int)n;
-                if (low == n && q == n) ++low;
-                w[x + CX_OFF + n++] = 1u << q;
+                at[(size_t)id_of[(size_t)lay[q]]] = (int)off.size();
+                if (low == off.size() && q == off.size()) ++low;
+                off.push_back(1u << q);
             }
-            w[x + CX_BITS] = n;
+            w[x + CX_BITS] = (unsigned)off.size();
             w[x + CX_LOW] = low;
             w[x + CX_LDS] = (unsigned)lds;
+            if (low < off.size()) lists.push_back({x, std::vector<unsigned>(off.begin() + low, off.end())});
             return at;
         };
         std::vector<int> src = pf;  // bit positions in the stage's source
@@ -340,7 +344,7 @@ struct Fuser {
                 if (std::find(pb.begin(), pb.end(), v) == pb.end() && std::find(qb.begin(), qb.end(), v) == qb.end())
                     tb.push_back(v);
             const size_t s = w.size();
-            w.resize(s + CS_WORDS, 0u);
+            w.resize(s + (size_t)(h.big ? CS_WORDS_BIG : CS_WORDS), 0u);
             w[s + CS_SHAPE] = (unsigned)bits(h.kap[i]) | ((unsigned)pb.size() << 8) | ((unsigned)qb.size() << 16);
             w[s + CS_TBITS] = (unsigned)tb.size();
             w[s + CS_TG] = (unsigned)h.gs[i];
@@ -351,6 +355,18 @@ struct Fuser {
             auto S = [&](int32_t v) { return (vp & bit(v)) ? offset(src[(size_t)id_of[(size_t)v]]) : 0u; };
             auto G = [&](int32_t v) { return offset(pg[(size_t)id_of[(size_t)v]]); };
             auto D = [&](int32_t v) { return offset(dst[(size_t)id_of[(size_t)v]]); };
+            for (size_t q = 0; q < tb.size(); ++q) {
+                if (h.big) {
+                    w[s + CS_BIT_S + q] = S(tb[q]);
+                    w[s + CS_BIT_G + q] = G(tb[q]);
+                    w[s + CS_BIT_O + q] = D(tb[q]);
+                    continue;
+                }
+                const bool memory = i == 0 && h.fcopy < 0;
+                w[s + CS_BIT_SG + q] = (memory ? 0u : S(tb[q])) | (G(tb[q]) << 16);
+                if (memory) w[CH_SRC + q] = S(tb[q]);
+                if (last) w[CH_OUT + q] = D(tb[q]);
+            }
             for (size_t q = 0; q < pb.size(); ++q) {
                 w[s + CS_PS + q] = S(pb[q]);
                 w[s + CS_PO + q] = D(pb[q]);
@@ -359,18 +375,18 @@ struct Fuser {
                 w[s + CS_QG + q] = G(qb[q]);
                 w[s + CS_QO + q] = D(qb[q]);
             }
-            for (size_t q = 0; q < tb.size(); ++q) {
-                w[s + CS_BIT_S + q] = S(tb[q]);
-                w[s + CS_BIT_G + q] = G(tb[q]);
-                w[s + CS_BIT_O + q] = D(tb[q]);
-            }
             src = dst;
         }
+        w[CH_TILES] = (unsigned)w.size();
         for (int32_t v : tv) w.push_back(offset(pf[(size_t)id_of[(size_t)v]]));
         for (int32_t v : tv) w.push_back(offset(pl[(size_t)id_of[(size_t)v]]));
         for (size_t i = 0; i < L; ++i) {
             const std::vector<int> pg = place(h.gs[i]);
             for (int32_t v : tv) w.push_back(offset(pg[(size_t)id_of[(size_t)v]]));
+        }
+        for (const auto &l : lists) {
+            w[l.first + CX_LIST] = (unsigned)w.size();
+            w.insert(w.end(), l.second.begin(), l.second.end());
         }
         F.words.insert(F.words.end(), w.begin(), w.end());
     }
@@ -378,7 +394,7 @@ struct Fuser {
 
 }  // namespace
 
-void wmc_fuse(wmc_plan_t &P) {
+void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
     FusedProgram &F = P.fused;
     F = FusedProgram();
     if (P.root < 0 || P.nodes.empty()) return;
@@ -519,7 +535,7 @@ void wmc_fuse(wmc_plan_t &P) {
     }
     std::vector<int64_t> offs;
     F.arena_bytes = wmc_place(birth, death, elems, &offs) * (uint64_t)P.elem;
-    if (F.arena_bytes > P.arena_bytes) return;  // never more memory than the general form
+    if (F.arena_bytes > max_arena) return;
     F.off.assign(NT, -1);
     for (size_t q = 0; q < stored.size(); ++q) F.off[(size_t)stored[q]] = offs[q];
 
@@ -551,7 +567,7 @@ void wmc_fuse(wmc_plan_t &P) {
                 };
                 put(CH_F, off(t.f));
                 put(CH_C, off(t.nodes.back()));
-                for (size_t s = 0; s < t.g.size(); ++s) put((unsigned)(CH_WORDS + s * CS_WORDS) + CS_G, off(t.g[s]));
+                for (size_t s = 0; s < t.g.size(); ++s) put((unsigned)(CH_WORDS + s * (t.big ? CS_WORDS_BIG : CS_WORDS)) + CS_G, off(t.g[s]));
                 if (t.nodes.size() > 1) F.masks.push_back(t.nodes.front());
                 L.lds = std::max(L.lds, t.lds + (t.big ? 0 : ((int)(F.words.size() - t.desc) * 4 + 1023) / 1024 * 1024 / P.elem));
                 if (t.big) L.type = FUSED_CHAIN;
@@ -632,6 +648,49 @@ void wmc_fuse(wmc_plan_t &P) {
     F.on = true;
 }
 
+FusedProgram wmc_program_of(const wmc_plan_t &P) {
+    if (P.fused.on) return P.fused;
+    FusedProgram F;
+    F.leaves = P.leaves;
+    F.nodes = P.nodes;
+    F.gemms = P.gemms;
+    for (const TNode &t : P.T) F.off.push_back(t.off);
+    for (size_t k = 1; k < P.launches.size(); ++k) {
+        const Launch &Ln = P.launches[k];
+        FusedLaunch L;
+        L.type = Ln.type == LAUNCH_GEMM ? FUSED_GEMM
+                 : Ln.count == 1 && P.nodes[(size_t)Ln.first].cls != WMC_CLASS_SMALL ? FUSED_NODE : FUSED_STEP;
+        L.node_first = Ln.first;
+        L.node_count = Ln.count;
+        L.node_work = Ln.work;
+        L.gemm = Ln.type == LAUNCH_GEMM ? Ln.pad : -1;
+        F.launches.push_back(L);
+    }
+    return F;
+}
+
+unsigned wmc_shift_chain(const FusedProgram &F, const ChainTask &t, unsigned words, long long abase, int mbase,
+                         std::vector<unsigned> &out) {
+    while (out.size() % 4) out.push_back(0);
+    const size_t at = out.size();
+    out.insert(out.end(), F.words.begin() + t.desc, F.words.begin() + t.desc + words);
+    unsigned *w = out.data() + at;
+    auto shift = [&](size_t q) {
+        const unsigned long long v = (((unsigned long long)w[q + 1] << 32) | w[q]) + (unsigned long long)abase;
+        w[q] = (unsigned)v;
+        w[q + 1] = (unsigned)(v >> 32);
+    };
+    shift(CH_F);
+    shift(CH_C);
+    for (int q : {(int)CH_TF, (int)CH_TC, (int)CH_MASK}) w[q] += (unsigned)mbase;
+    for (unsigned s = 0; s < w[CH_STAGES]; ++s) {
+        const size_t q = CH_WORDS + (size_t)s * (t.big ? CS_WORDS_BIG : CS_WORDS);
+        shift(q + CS_G);
+        w[q + CS_TG] += (unsigned)mbase;
+    }
+    return (unsigned)at;
+}
+
 // Bounds of the fused program: every tensor inside the arena, and for every
 // stage of every chain the largest address its index bits can form (the OR
 // of all of them) inside the tensor or LDS region it reads or writes.
@@ -643,7 +702,7 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
         return false;
     };
     auto rank = [&](int32_t t) { return (int)P.T[(size_t)t].layout.size(); };
-    const uint64_t arena = P.arena_bytes / (uint64_t)P.elem;
+    const uint64_t arena = std::max(P.arena_bytes, F.arena_bytes) / (uint64_t)P.elem;
     for (size_t t = 0; t < F.off.size(); ++t)
         if (F.off[t] >= 0 && (uint64_t)F.off[t] + (1ull << rank((int32_t)t)) > arena) return fail("tensor outside the arena");
     for (const ChainTask &t : F.chains) {
@@ -652,7 +711,9 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
         if (L < 1 || L > WMC_CHAIN_MAX || L != t.nodes.size() || (int)w[CH_TC] != t.nodes.back() || (int)w[CH_TF] != t.f)
             return fail("chain header");
         if (F.off[(size_t)t.f] < 0 || F.off[(size_t)t.nodes.back()] < 0) return fail("chain operand is not stored");
-        const unsigned *tiles = w + CH_WORDS + L * CS_WORDS;
+        const unsigned stride = t.big ? CS_WORDS_BIG : CS_WORDS;
+        const unsigned *tiles = w + w[CH_TILES];
+        if (w[CH_TILES] != CH_WORDS + L * stride) return fail("tile lists");
         unsigned long long of = 0, oc = 0;
         for (unsigned b = 0; b < ob; ++b) {
             of |= tiles[b];
@@ -668,9 +729,8 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
         auto copied = [&](const unsigned *x, unsigned long long tiles_or, int tensor, unsigned *end) {
             unsigned long long all = tiles_or;
             if (x[CX_BITS] > WMC_CHAIN_BITS || x[CX_LOW] > x[CX_BITS]) return false;
-            for (unsigned b = 0; b < x[CX_BITS]; ++b) all |= x[CX_OFF + b];
-            for (unsigned b = 0; b < x[CX_LOW]; ++b)
-                if (x[CX_OFF + b] != 1u << b) return false;
+            all |= (1ull << x[CX_LOW]) - 1ull;
+            for (unsigned b = x[CX_LOW]; b < x[CX_BITS]; ++b) all |= w[x[CX_LIST] + b - x[CX_LOW]];
             return (all >> rank(tensor)) == 0 && inside(x[CX_LDS], (1ull << x[CX_BITS]) - 1ull, end);
         };
         unsigned fe = 0, lo = 0, hi = 0;
@@ -679,7 +739,7 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
         if (t.lds * P.elem > WMC_CHAIN_LDS) return fail("LDS size");
         std::vector<std::pair<unsigned, unsigned>> gr;
         for (unsigned i = 0; i < L; ++i) {
-            const unsigned *s = w + CH_WORDS + i * CS_WORDS;
+            const unsigned *s = w + CH_WORDS + i * stride;
             unsigned long long og = 0;
             for (unsigned b = 0; b < ob; ++b) og |= tiles[(2 + i) * ob + b];
             unsigned e = 0;
@@ -697,21 +757,22 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
             gr.push_back({s[CS_X + CX_LDS], e});
         }
         for (unsigned i = 0; i < L; ++i) {
-            const unsigned *s = w + CH_WORDS + i * CS_WORDS;
+            const unsigned *s = w + CH_WORDS + i * stride;
             const unsigned nk = s[CS_SHAPE] & 255u, np = (s[CS_SHAPE] >> 8) & 255u, nq = s[CS_SHAPE] >> 16;
             const unsigned tb = s[CS_TBITS];
             if (nk > WMC_CHAIN_NK || np + nq > 2 || (!t.big && np + nq) || tb + np + nq > WMC_CHAIN_BITS)
                 return fail("stage shape");
             unsigned long long src = 0, g = 0, out = 0;
             for (unsigned q = 0; q < 2; ++q) {
+                if (!t.big) break;
                 src |= s[CS_PS + q];
                 out |= s[CS_PO + q] | s[CS_QO + q];
                 g |= s[CS_QG + q];
             }
             for (unsigned q = 0; q < WMC_CHAIN_BITS; ++q) {
-                src |= s[CS_BIT_S + q];
-                g |= s[CS_BIT_G + q];
-                out |= s[CS_BIT_O + q];
+                src |= t.big ? s[CS_BIT_S + q] : i == 0 && !fcopy ? w[CH_SRC + q] : s[CS_BIT_SG + q] & 0xFFFFu;
+                g |= t.big ? s[CS_BIT_G + q] : s[CS_BIT_SG + q] >> 16;
+                out |= t.big ? s[CS_BIT_O + q] : i + 1 == L ? w[CH_OUT + q] : q < tb ? 1u << q : 0u;
             }
             const unsigned long long row = (1ull << nk) - 1ull;
             if ((src & row) || (g & row)) return fail("summed entries of a row are not contiguous");
@@ -738,8 +799,8 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
     for (const ChainRec &r : F.recs) {
         const unsigned ob = F.words[r.desc + CH_TILE_BITS];
         const unsigned L = F.words[r.desc + CH_STAGES];
-        if (r.jbits > ob || r.blk >> (ob - r.jbits) || r.words != CH_WORDS + L * CS_WORDS + (L + 2) * ob ||
-            r.desc + r.words > F.words.size())
+        if (r.jbits > ob || r.blk >> (ob - r.jbits) || r.words < CH_WORDS + L * CS_WORDS + (L + 2) * ob ||
+            r.words > 3u << WMC_CHAIN_LANE || r.desc + r.words > F.words.size())
             return fail("workgroup record");
     }
     return true;
@@ -768,7 +829,7 @@ extern "C" wmc_status wmc_plan_program(const wmc_plan_t *plan, void *dst, uint64
     if (info) {
         const int64_t v[9] = {(int64_t)F.leaves.size(), (int64_t)F.nodes.size(),    (int64_t)F.gemms.size(),
                               (int64_t)F.words.size(),  (int64_t)F.recs.size(),     (int64_t)F.launches.size(),
-                              (int64_t)F.chains.size(), (int64_t)plan->T.size(), (int64_t)(plan->arena_bytes / (uint64_t)plan->elem)};
+                              (int64_t)F.chains.size(), (int64_t)plan->T.size(), (int64_t)(plan->arena_stride / (uint64_t)plan->elem)};
         std::memcpy(info, v, sizeof v);
     }
     if (!dst) return WMC_OK;

@@ -1394,16 +1394,19 @@ static wmc_status finalize_plan(const wmc_network &net, const wmc_plan_options &
     P.arena_stride = align_up(P.arena_bytes, 256);
     P.workspace_bytes = P.off_arena + (uint64_t)P.group * P.arena_stride;
     // the fused program's image shares the descriptor region and its tensors
-    // the arena; a plan that fits the static scratch keeps fitting it
-    wmc_fuse(P);
+    // the arena, which may grow by half unless the caller bounds it; a plan
+    // that fits the static scratch keeps fitting it
+    wmc_fuse(P, o.mem_cap_bytes ? P.arena_bytes : P.arena_bytes + P.arena_bytes / 2);
     if (P.fused.on) {
-        const uint64_t more = P.off_leaf + P.fused.image.size() > P.off_arena
-                                  ? P.off_leaf + P.fused.image.size() - P.off_arena : 0;
-        if (P.workspace_bytes <= WMC_NOALLOC_SCRATCH_BYTES && P.workspace_bytes + more > WMC_NOALLOC_SCRATCH_BYTES) {
+        const uint64_t arena = std::max(P.off_arena, P.off_leaf + P.fused.image.size());
+        const uint64_t stride = align_up(std::max(P.arena_bytes, P.fused.arena_bytes), 256);
+        const uint64_t bytes = arena + (uint64_t)P.group * stride;
+        if (P.workspace_bytes <= WMC_NOALLOC_SCRATCH_BYTES && bytes > WMC_NOALLOC_SCRATCH_BYTES) {
             P.fused = FusedProgram();
         } else {
-            P.off_arena += more;
-            P.workspace_bytes += more;
+            P.off_arena = arena;
+            P.arena_stride = stride;
+            P.workspace_bytes = bytes;
         }
     }
 

@@ -154,9 +154,16 @@ struct wmc_plan_t {
 // largest first; returns the arena's entries (wmc_host.cpp).
 uint64_t wmc_place(const std::vector<int32_t> &birth, const std::vector<int32_t> &death,
                    const std::vector<uint64_t> &elems, std::vector<int64_t> *offs);
-// Builds P.fused from the finished launch list (wmc_fuse.cpp).
-void wmc_fuse(wmc_plan_t &P);
+// Builds P.fused from the finished launch list, in an arena of at most
+// max_arena bytes (wmc_fuse.cpp).
+void wmc_fuse(wmc_plan_t &P, uint64_t max_arena);
 bool wmc_validate_fused(const wmc_plan_t &P, std::string *why);
+// P.fused, or the plan's launch list in the same form (no chains).
+FusedProgram wmc_program_of(const wmc_plan_t &P);
+// Appends the chain at word `desc` of P's program to `out`, its arena offsets
+// and meta entries shifted; returns its first word there.
+unsigned wmc_shift_chain(const FusedProgram &F, const ChainTask &t, unsigned words, long long abase, int mbase,
+                         std::vector<unsigned> &out);
 
 void wmc_set_error(const char *fmt, ...);
 // Bounds of every launch of a finished plan, proved on the host before

@@ -11,11 +11,13 @@ import paper_2006_15512_amd as W
 import wmc_workloads as wl
 from plan_emulator import GEMM, LEAF, NODE, _pext, _sexp
 
-CH_STAGES, CH_TILE_BITS, CH_F, CH_C, CH_TF, CH_TC, CH_FCOPY, CH_X, CH_WORDS = 0, 1, 2, 4, 6, 7, 10, 11, 28
+CH_STAGES, CH_TILE_BITS, CH_F, CH_C, CH_TF, CH_TC, CH_FCOPY, CH_TILES, CH_X, CH_OUT, CH_SRC, CH_WORDS = (
+    0, 1, 2, 4, 6, 7, 10, 11, 12, 16, 32, 48)
 BITS = 16  # words per list of entry bit offsets
-CS_SHAPE, CS_TBITS, CS_G, CS_TG, CS_SRC, CS_DST, CS_PS, CS_PO, CS_QG, CS_QO = 0, 1, 2, 4, 5, 6, 8, 10, 12, 14
-CS_BIT, CS_X, CS_WORDS = 16, 64, 80
-CX_BITS, CX_LOW, CX_LDS, CX_OFF = 0, 1, 2, 3
+CS_SHAPE, CS_TBITS, CS_G, CS_TG, CS_SRC, CS_DST, CS_BIT, CS_X, CS_BIT_O, CS_PS, CS_PO, CS_QG, CS_QO = (
+    0, 1, 2, 4, 5, 6, 8, 24, 40, 56, 58, 60, 62)
+CS_WORDS = {0: 28, 3: 64}  # by launch type: short chains, chains of many tiles
+CX_BITS, CX_LOW, CX_LDS, CX_LIST = 0, 1, 2, 3
 
 
 def parse(plan):
@@ -88,8 +90,9 @@ def replay(plan, w):
         for desc in prog["chains"][cf: cf + cc]:
             c = prog["words"][desc:].astype(np.int64)
             L, ob = int(c[CH_STAGES]), int(c[CH_TILE_BITS])
-            tiles = c[CH_WORDS + L * CS_WORDS:]
-            st = [c[CH_WORDS + i * CS_WORDS: CH_WORDS + (i + 1) * CS_WORDS] for i in range(L)]
+            n = CS_WORDS[int(typ)]
+            tiles = c[int(c[CH_TILES]):]
+            st = [c[CH_WORDS + i * n: CH_WORDS + (i + 1) * n] for i in range(L)]
             base = lambda x: int(x[0]) + (int(x[1]) << 32)
             shift = [_sexp(mx[int(s[CS_TG])]) for s in st]
             shift[0] += _sexp(mx[int(c[CH_TF])])
@@ -98,9 +101,15 @@ def replay(plan, w):
             maps = []
             for i, s in enumerate(st):
                 nk, np_, nq, tb = int(s[0]) & 255, (int(s[0]) >> 8) & 255, int(s[0]) >> 16, int(s[CS_TBITS])
-                bits = [tuple(int(s[CS_BIT + j * BITS + b]) for j in range(3)) for b in range(tb)]
-                bits += [(int(s[CS_PS + q]), 0, int(s[CS_PO + q])) for q in range(np_)]
-                bits += [(0, int(s[CS_QG + q]), int(s[CS_QO + q])) for q in range(nq)]
+                outs = s[CS_BIT_O:] if typ == 3 else c[CH_OUT:] if i + 1 == L else 1 << np.arange(16)
+                if typ == 0:  # source in the low half, G in the high half
+                    memory = i == 0 and not c[CH_FCOPY]
+                    bits = [(int(c[CH_SRC + b]) if memory else int(s[CS_BIT + b]) & 0xFFFF, int(s[CS_BIT + b]) >> 16,
+                             int(outs[b])) for b in range(tb)]
+                else:
+                    bits = [(int(s[CS_BIT + b]), int(s[CS_BIT + BITS + b]), int(outs[b])) for b in range(tb)]
+                    bits += [(int(s[CS_PS + q]), 0, int(s[CS_PO + q])) for q in range(np_)]
+                    bits += [(0, int(s[CS_QG + q]), int(s[CS_QO + q])) for q in range(nq)]
                 e = np.arange(1 << len(bits))
                 maps.append([_deposit(e, [x[j] for x in bits]) for j in range(3)])
                 assert len(np.unique(maps[-1][2])) == len(e)
@@ -112,8 +121,10 @@ def replay(plan, w):
 
                 def copy(x, start):
                     """The part of an operand each tile reads, into its LDS region."""
-                    q = np.arange(1 << int(x[CX_BITS]))
-                    lds[:, int(x[CX_LDS]) + q] = arena[start[:, None] + _deposit(q, x[CX_OFF: CX_OFF + int(x[CX_BITS])])]
+                    nb, low, at = int(x[CX_BITS]), int(x[CX_LOW]), int(x[CX_LIST])
+                    q = np.arange(1 << nb)
+                    offs = [1 << b for b in range(low)] + [int(y) for y in c[at: at + nb - low]]
+                    lds[:, int(x[CX_LDS]) + q] = arena[start[:, None] + _deposit(q, offs)]
 
                 if c[CH_FCOPY]:
                     copy(c[CH_X:], src_t)
