@@ -648,8 +648,8 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
     F.on = true;
 }
 
-FusedProgram wmc_program_of(const wmc_plan_t &P) {
-    if (P.fused.on) return P.fused;
+FusedProgram wmc_program_of(const wmc_plan_t &P, bool fused) {
+    if (fused && P.fused.on) return P.fused;
     FusedProgram F;
     F.leaves = P.leaves;
     F.nodes = P.nodes;

@@ -158,8 +158,9 @@ uint64_t wmc_place(const std::vector<int32_t> &birth, const std::vector<int32_t>
 // max_arena bytes (wmc_fuse.cpp).
 void wmc_fuse(wmc_plan_t &P, uint64_t max_arena);
 bool wmc_validate_fused(const wmc_plan_t &P, std::string *why);
-// P.fused, or the plan's launch list in the same form (no chains).
-FusedProgram wmc_program_of(const wmc_plan_t &P);
+// P.fused if `fused` and there is one, else the plan's launch list in the
+// same form (no chains).
+FusedProgram wmc_program_of(const wmc_plan_t &P, bool fused = true);
 // Appends the chain at word `desc` of P's program to `out`, its arena offsets
 // and meta entries shifted; returns its first word there.
 unsigned wmc_shift_chain(const FusedProgram &F, const ChainTask &t, unsigned words, long long abase, int mbase,

@@ -28,7 +28,7 @@
 #include <deque>
 #include <map>
 
-#include "wmc_kernels.h"
+#include "wmc_chain.h"
 
 namespace {
 
@@ -53,24 +53,44 @@ struct SLaunch {
         int32_t nk, blk;
     };
     std::vector<Blk> blocks;
+    // per chain workgroup: descriptor words, and the launch it joins
+    struct Chain {
+        uint64_t off;
+        unsigned blk, jbits, words;
+        int32_t kind, lds;
+    };
+    std::vector<Chain> chains;
+};
+
+// Chains of a step by launch: short ones that leave room for eight
+// workgroups on a compute unit, short ones that need more LDS, and ones of
+// many tiles.
+enum { SCHAIN_SHORT = 0, SCHAIN_WIDE, SCHAIN_BIG, SCHAIN_KINDS };
+const int kServeLds = 19 * 1024;
+
+// One program of a structure, its descriptors resident.
+struct SProg {
+    std::vector<GemmDesc> gemms;  // host copies (launch shapes); the device reads the resident ones
+    std::vector<SLaunch> L;       // per launch of the program; L[0] is the leaf fill
+    uint64_t img_off = 0, img_bytes = 0;   // resident image (offset into the region pool)
+    uint64_t leaves_off = 0, gemms_off = 0, masks_off = 0;
+    int32_t nmasks = 0;
+    std::vector<std::pair<uint64_t, int32_t>> leaf_waves;  // per wave of the leaf fill
+    long long root_off = 0;
 };
 
 struct SStruct {
     int32_t n = 0;                // variables, auxiliary ones included
     int32_t n_user = 0;           // a request brings 2 * n_user weights
     std::vector<double> w_aux;    // (1, 1) per auxiliary variable
-    std::vector<GemmDesc> gemms;  // host copies (launch shapes); the device reads the resident ones
     GemmShape gemm_shape;         // from the plan's tuning table
-    std::vector<SLaunch> L;       // per launch of the plan; L[0] is the leaf fill
-    uint64_t img_off = 0, img_bytes = 0;   // resident image (offset into the region pool)
-    uint64_t leaves_off = 0, gemms_off = 0;
-    std::vector<std::pair<uint64_t, int32_t>> leaf_waves;  // per wave of the leaf fill
-    int32_t nleaves = 0;
+    // the fused program, and the plan's launch list, which a request runs on
+    // if a chain of the first left its range (and which is all there is if
+    // the plan has no fused program or no room for it)
+    std::vector<SProg> prog;
     int32_t root = -1;
-    long long root_off = 0;
     int64_t nt = 0;
     uint64_t meta_bytes = 0, arena_bytes = 0, footprint = 0;
-    int64_t leaf_work = 0;
     uint64_t max_step_bytes = 0;  // largest staging contribution of one request in one step
     int64_t nslices = 1;          // slices of the plan: parts per request
 };
@@ -81,6 +101,7 @@ struct SReq {
     int32_t slot = -1;
     uint64_t region = 0;
     size_t k = 0;
+    size_t prog = 0;              // program it runs on
     std::vector<double> w;
     double t_arrive = 0, t_admit = 0;
     double deadline = 0;          // server clock, 0 = none
@@ -105,6 +126,10 @@ struct FinishEntry {
     int root_meta;
     int slot;
     long long root_off;
+    const int *masks;  // chains' range entries, counted from mbase
+    long long mbase;
+    int nmasks;
+    int pad;
 };
 
 struct ClearRange {
@@ -146,6 +171,29 @@ struct ServeWave {
     int entry;
     int item;
 };
+
+// One workgroup of a step's chains.
+struct ServeChain {
+    const unsigned *words;
+    long long abase, mbase;
+    unsigned blk, jbits, nwords, pad;
+};
+
+template <typename T>
+__global__ void __launch_bounds__(1 << WMC_CHAIN_LANE_MANY) k_chain_serve(const ServeChain *__restrict__ recs,
+                                                                          T *__restrict__ arena, wmc_meta *meta) {
+    extern __shared__ char smem_raw[];
+    const ServeChain &r = recs[blockIdx.x];
+    chain_run_short<T, WMC_CHAIN_LANE_MANY>(r.words, r.nwords, r.blk, arena + r.abase, meta + r.mbase, smem_raw);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(WMC_CHAIN_THREADS_BIG) k_chain_big_serve(const ServeChain *__restrict__ recs,
+                                                                           T *__restrict__ arena, wmc_meta *meta) {
+    extern __shared__ char smem_raw[];
+    const ServeChain &r = recs[blockIdx.x];
+    chain_run_big<T>(const_words(r.words), r.blk, r.jbits, arena + r.abase, meta + r.mbase, (T *)smem_raw);
+}
 
 static uint64_t sal(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
@@ -211,12 +259,19 @@ struct ServeRes {
     long long e;
 };
 
+// One wave per finished request: its root's value, and whether one of its
+// chains left its range.
+#define WMC_SERVE_RERUN (-0x7fffffffffffffffll)
 template <typename T>
 __global__ void k_finish_serve(const FinishEntry *__restrict__ f, int n, const T *__restrict__ arena,
                                const wmc_meta *meta, ServeRes *res) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) / WMC_WAVE), lane = (int)(threadIdx.x % WMC_WAVE);
     if (i >= n) return;
     const FinishEntry e = f[i];
+    bool bad = false;
+    for (int q = lane; q < e.nmasks; q += WMC_WAVE) bad |= chain_out_of_range(meta[e.mbase + e.masks[q]].maxbits);
+    bad = __any(bad);
+    if (lane != 0) return;
     if (e.root_meta < 0) {  // no variables and no clauses: the empty product
         res[e.slot].m = 0.5;
         res[e.slot].e = 1;
@@ -232,7 +287,7 @@ __global__ void k_finish_serve(const FinishEntry *__restrict__ f, int n, const T
         ex = 0;
     }
     res[e.slot].m = v;
-    res[e.slot].e = ex;
+    res[e.slot].e = bad ? WMC_SERVE_RERUN : ex;
 }
 
 struct wmc_server {
@@ -363,6 +418,83 @@ static void region_free(wmc_server *v, uint64_t off, uint64_t size) {
     }
 }
 
+// A program's resident image (offsets relative to its start): leaves,
+// matrix-node descriptors, and per launch its small nodes, its streaming
+// tasks (grouped by summed-index size), with their workgroup table, and its
+// chains' words.
+static SProg serve_program(const wmc_plan_t &plan, const FusedProgram &F, std::vector<uint8_t> &img) {
+    SProg s;
+    img.clear();
+    s.gemms = F.gemms;
+    s.root_off = plan.root >= 0 ? F.off[(size_t)plan.root] : 0;
+    auto put = [&](const void *src, size_t bytes) {
+        const uint64_t at = sal(img.size(), 256);
+        img.resize(at + bytes);
+        if (bytes) std::memcpy(img.data() + at, src, bytes);
+        return at;
+    };
+    s.leaves_off = put(F.leaves.data(), sizeof(LeafDesc) * F.leaves.size());
+    for (size_t q = 0; q < F.leaves.size(); ++q)
+        for (uint64_t e = 0; e < (1ull << F.leaves[q].rank); e += WMC_WAVE)
+            s.leaf_waves.push_back({s.leaves_off + sizeof(LeafDesc) * q, (int32_t)e});
+    s.gemms_off = put(F.gemms.data(), sizeof(GemmDesc) * F.gemms.size());
+    s.masks_off = put(F.masks.data(), sizeof(int32_t) * F.masks.size());
+    s.nmasks = (int32_t)F.masks.size();
+    const uint64_t words_off = put(F.words.data(), sizeof(unsigned) * F.words.size());
+    std::vector<int> tab;
+    s.L.resize(plan.root >= 0 ? F.launches.size() + 1 : std::max<size_t>(F.launches.size() + 1, plan.launches.size()));
+    for (size_t k = 0; k < F.launches.size(); ++k) {
+        const FusedLaunch &Ln = F.launches[k];
+        SLaunch &sl = s.L[k + 1];
+        if (Ln.type == FUSED_GEMM) {
+            sl.type = LAUNCH_GEMM;
+            sl.gemm = Ln.gemm;
+            continue;
+        }
+        int32_t r = Ln.rec_first;
+        for (int32_t q = 0; q < Ln.chain_count; ++q) {
+            const ChainTask &t = F.chains[(size_t)(Ln.chain_first + q)];
+            for (; r < Ln.rec_first + Ln.rec_count && F.recs[(size_t)r].desc == t.desc; ++r) {
+                const ChainRec &x = F.recs[(size_t)r];
+                const int lds = t.lds * plan.elem + (t.big ? 0 : (int)((x.words * 4 + 1023) / 1024 * 1024));
+                sl.chains.push_back({words_off + sizeof(unsigned) * (uint64_t)x.desc, x.blk, x.jbits, x.words,
+                                     t.big ? SCHAIN_BIG : lds > kServeLds ? SCHAIN_WIDE : SCHAIN_SHORT, lds});
+            }
+        }
+        std::vector<NodeDesc> generic(F.nodes.begin() + Ln.node_first, F.nodes.begin() + Ln.node_first + Ln.node_count);
+        std::vector<StreamTask> tasks;
+        std::vector<int> nkf;
+        int64_t work = 0;
+        split_stream(generic, tasks, nkf, work, plan.tune.multi_min_rank);
+        sl.nnodes = (int32_t)generic.size();
+        sl.node_work = work;
+        sl.nodes_off = put(generic.data(), sizeof(NodeDesc) * generic.size());
+        for (size_t q = 0; q < generic.size(); ++q)
+            for (uint64_t e = 0; e < (1ull << generic[q].rc); e += WMC_WAVE)
+                sl.waves.push_back({sl.nodes_off + sizeof(NodeDesc) * q, (int32_t)e});
+        sl.tasks_off = put(tasks.data(), sizeof(StreamTask) * tasks.size());
+        block_task_table(tasks, nkf, tab);
+        sl.btask_off = put(tab.data(), sizeof(int) * tab.size());
+        unsigned long long blocks = 0;
+        for (int q = 0; q < 4; ++q) {
+            sl.gblock[q] = (long long)blocks;
+            sl.gtask[q] = nkf[(size_t)q];
+            blocks += stream_multi_blocks(tasks.data(), nkf[(size_t)q], nkf[(size_t)q + 1]);
+        }
+        sl.gblock[4] = (long long)blocks;
+        sl.gtask[4] = nkf[4];
+        sl.sblocks = (unsigned)blocks;
+        for (int q = 0; q < 4; ++q)
+            for (int t = nkf[(size_t)q]; t < nkf[(size_t)q + 1]; ++t) {
+                const long long b0 = tasks[(size_t)t].block_begin;
+                const long long nb = (long long)stream_task_blocks(tasks[(size_t)t].a);
+                for (long long b = 0; b < nb; ++b)
+                    sl.blocks.push_back({sl.tasks_off + sizeof(StreamTask) * (uint64_t)t, q, (int32_t)(b0 + b)});
+            }
+    }
+    return s;
+}
+
 // Registration builds the structure's resident image -- leaves and their
 // wave table, matrix-node descriptors, and per node launch its generic nodes
 // with their wave table and its streaming tasks (grouped by summed-index
@@ -386,98 +518,67 @@ extern "C" wmc_status wmc_serve_register(wmc_server *v, const wmc_plan_t *plan, 
         s.n = plan->n;
         s.n_user = plan->n_user;
         s.w_aux.assign(plan->w.begin() + 2 * (size_t)plan->n_user, plan->w.end());
-        s.gemms = plan->gemms;
         s.gemm_shape = GemmShape{plan->tune.gemm_tpw_max_nt, plan->tune.gemm_orient};
         s.root = plan->root;
-        s.root_off = plan->root >= 0 ? plan->T[(size_t)plan->root].off : 0;
         s.nt = (int64_t)std::max<size_t>(plan->T.size(), 1);
         s.meta_bytes = sal(sizeof(wmc_meta) * (uint64_t)s.nt, 256);
         s.arena_bytes = sal(std::max<uint64_t>(plan->arena_bytes, 256), 256);
         s.footprint = s.meta_bytes + s.arena_bytes;
-        s.leaf_work = plan->leaf_work;
-        s.nleaves = (int32_t)plan->leaves.size();
         s.nslices = (int64_t)1 << plan->sliced.size();
-        // image, offsets relative to its start
-        std::vector<uint8_t> img;
-        auto put = [&](const void *src, size_t bytes) {
-            const uint64_t at = sal(img.size(), 256);
-            img.resize(at + bytes);
-            if (bytes) std::memcpy(img.data() + at, src, bytes);
-            return at;
-        };
-        s.leaves_off = put(plan->leaves.data(), sizeof(LeafDesc) * plan->leaves.size());
-        for (size_t q = 0; q < plan->leaves.size(); ++q)
-            for (uint64_t e = 0; e < (1ull << plan->leaves[q].rank); e += WMC_WAVE)
-                s.leaf_waves.push_back({s.leaves_off + sizeof(LeafDesc) * q, (int32_t)e});
-        std::vector<int> tab;
-        s.gemms_off = put(plan->gemms.data(), sizeof(GemmDesc) * plan->gemms.size());
-        s.L.resize(plan->launches.size());
-        for (size_t k = 1; k < plan->launches.size(); ++k) {
-            const Launch &Ln = plan->launches[k];
-            SLaunch &sl = s.L[k];
-            sl.type = Ln.type;
-            if (Ln.type == LAUNCH_GEMM) {
-                sl.gemm = Ln.pad;
-                continue;
-            }
-            std::vector<NodeDesc> generic(plan->nodes.begin() + Ln.first, plan->nodes.begin() + Ln.first + Ln.count);
-            std::vector<StreamTask> tasks;
-            std::vector<int> nkf;
-            int64_t work = 0;
-            split_stream(generic, tasks, nkf, work, plan->tune.multi_min_rank);
-            sl.nnodes = (int32_t)generic.size();
-            sl.node_work = work;
-            sl.nodes_off = put(generic.data(), sizeof(NodeDesc) * generic.size());
-            for (size_t q = 0; q < generic.size(); ++q)
-                for (uint64_t e = 0; e < (1ull << generic[q].rc); e += WMC_WAVE)
-                    sl.waves.push_back({sl.nodes_off + sizeof(NodeDesc) * q, (int32_t)e});
-            sl.tasks_off = put(tasks.data(), sizeof(StreamTask) * tasks.size());
-            block_task_table(tasks, nkf, tab);
-            sl.btask_off = put(tab.data(), sizeof(int) * tab.size());
-            unsigned long long blocks = 0;
-            for (int q = 0; q < 4; ++q) {
-                sl.gblock[q] = (long long)blocks;
-                sl.gtask[q] = nkf[(size_t)q];
-                blocks += stream_multi_blocks(tasks.data(), nkf[(size_t)q], nkf[(size_t)q + 1]);
-            }
-            sl.gblock[4] = (long long)blocks;
-            sl.gtask[4] = nkf[4];
-            sl.sblocks = (unsigned)blocks;
-            for (int q = 0; q < 4; ++q)
-                for (int t = nkf[(size_t)q]; t < nkf[(size_t)q + 1]; ++t) {
-                    const long long b0 = tasks[(size_t)t].block_begin;
-                    const long long nb = (long long)stream_task_blocks(tasks[(size_t)t].a);
-                    for (long long b = 0; b < nb; ++b)
-                        sl.blocks.push_back({sl.tasks_off + sizeof(StreamTask) * (uint64_t)t, q, (int32_t)(b0 + b)});
-                }
-        }
-        s.img_bytes = sal(std::max<uint64_t>(img.size(), 256), 256);
         // staging per request and step: its weights (first step), a work
-        // entry, a clear range or a finish entry
-        uint64_t units = sizeof(ServeWave) * s.leaf_waves.size();
-        for (const SLaunch &sl : s.L)
-            units = std::max<uint64_t>(units, sizeof(ServeBlock) * sl.sblocks + sizeof(ServeWave) * sl.waves.size());
-        s.max_step_bytes = sal(sizeof(double) * 2 * (uint64_t)s.n, 256) + sizeof(ServeWork) + sizeof(ClearRange) +
-                           sizeof(FinishEntry) + units + 6 * 256;
+        // entry, a clear range or a finish entry, and its records
+        auto staging = [&](const SProg &g) {
+            uint64_t units = sizeof(ServeWave) * g.leaf_waves.size();
+            for (const SLaunch &sl : g.L)
+                units = std::max<uint64_t>(units, sizeof(ServeBlock) * sl.sblocks + sizeof(ServeWave) * sl.waves.size() +
+                                                      sizeof(ServeChain) * sl.chains.size());
+            return sal(sizeof(double) * 2 * (uint64_t)s.n, 256) + sizeof(ServeWork) + sizeof(ClearRange) +
+                   sizeof(FinishEntry) + units + (6 + SCHAIN_KINDS) * 256;
+        };
+        std::vector<uint8_t> img;
+        const FusedProgram &fused = plan->fused;
+        const FusedProgram list = wmc_program_of(*plan, false);
+        SProg general = serve_program(*plan, list, img);
+        s.max_step_bytes = staging(general);
         if (s.footprint > v->regions_bytes || s.max_step_bytes > v->step_cap) {
             wmc_set_error("wmc_serve_register: structure needs %llu bytes of region and %llu of staging",
                           (unsigned long long)s.footprint, (unsigned long long)s.max_step_bytes);
             return WMC_ERR_CAP_UNREACHABLE;
         }
-        const uint64_t peak = v->peak_used;
-        if (!region_alloc(v, s.img_bytes, &s.img_off)) {
-            wmc_set_error("wmc_serve_register: no room for the structure's %llu bytes of descriptors",
-                          (unsigned long long)s.img_bytes);
-            return WMC_ERR_OUT_OF_MEMORY;
-        }
-        // descriptors are resident: they leave the budget for requests
-        v->used_bytes -= s.img_bytes;
-        v->peak_used = peak;
-        v->structure_bytes += s.img_bytes;
         if (v->inflight) HIP_TRY(hipEventSynchronize(v->ev[v->parity]));
-        HIP_TRY(hipMemcpyAsync(v->dev + v->off_regions + s.img_off, img.data(), img.size(), hipMemcpyHostToDevice,
-                               v->st));
-        HIP_TRY(hipStreamSynchronize(v->st));
+        // descriptors are resident: they leave the budget for requests
+        auto upload = [&](SProg &g) -> wmc_status {
+            g.img_bytes = sal(std::max<uint64_t>(img.size(), 256), 256);
+            const uint64_t peak = v->peak_used;
+            if (!region_alloc(v, g.img_bytes, &g.img_off)) {
+                wmc_set_error("wmc_serve_register: no room for the structure's %llu bytes of descriptors",
+                              (unsigned long long)g.img_bytes);
+                return WMC_ERR_OUT_OF_MEMORY;
+            }
+            v->used_bytes -= g.img_bytes;
+            v->peak_used = peak;
+            v->structure_bytes += g.img_bytes;
+            HIP_TRY(hipMemcpyAsync(v->dev + v->off_regions + g.img_off, img.data(), img.size(), hipMemcpyHostToDevice,
+                                   v->st));
+            HIP_TRY(hipStreamSynchronize(v->st));
+            return WMC_OK;
+        };
+        wmc_status us = upload(general);
+        if (us != WMC_OK) return us;
+        if (fused.on) {
+            // only where the second image and the larger region leave the
+            // budget to the requests
+            SProg g = serve_program(*plan, fused, img);
+            const uint64_t foot = s.meta_bytes + sal(std::max(plan->arena_bytes, fused.arena_bytes), 256);
+            const uint64_t step = std::max(s.max_step_bytes, staging(g));
+            if (step <= v->step_cap / 4 && foot <= v->regions_bytes / 16 &&
+                v->structure_bytes + img.size() + 256 <= v->regions_bytes / 8 && upload(g) == WMC_OK) {
+                s.footprint = foot;
+                s.max_step_bytes = step;
+                s.prog.push_back(std::move(g));
+            }
+        }
+        s.prog.push_back(std::move(general));
         v->S.push_back(std::move(s));
         if (structure_id) *structure_id = (int32_t)v->S.size() - 1;
     } catch (std::bad_alloc &) {
@@ -653,6 +754,14 @@ static wmc_status serve_collect(wmc_server *v) {
             continue;
         }
         (void)t;
+        if (s.root >= 0 && res[r.slot].e == WMC_SERVE_RERUN) {
+            // a chain left its range: once more, on the launch list, in the
+            // same slot and region
+            r.k = 0;
+            r.prog = s.prog.size() - 1;
+            v->active.push_back(std::move(r));
+            continue;
+        }
         if (s.root < 0) complete(v, r, true, 0.5, 1);  // the empty product: 1
         else complete(v, r, true, res[r.slot].m, res[r.slot].e);
         region_free(v, r.region, s.footprint);
@@ -731,6 +840,8 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
     std::vector<FinishEntry> fin;
     std::vector<ServeBlock> sblk;      // streaming workgroups
     std::vector<ServeWave> node_waves, leaf_waves;
+    std::vector<ServeChain> chains[SCHAIN_KINDS];
+    int chain_lds[SCHAIN_KINDS] = {0, 0, 0};
     unsigned sblocks = 0;
     std::vector<SReq> keep;
     keep.reserve(v->active.size());
@@ -743,7 +854,8 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
         }
         const long long mbase = (long long)(r.region / sizeof(wmc_meta));
         const long long abase = (long long)((r.region + s.meta_bytes) / elem);
-        const char *base = img + s.img_off;
+        const SProg &g = s.prog[r.prog];
+        const char *base = img + g.img_off;
         const int entry = (int)works.size();
         ServeWork w;
         std::memset(&w, 0, sizeof w);
@@ -756,12 +868,12 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
             clears.push_back({mbase, s.nt});
             woff = (long long)wts.size();
             wts.insert(wts.end(), r.w.begin(), r.w.end());
-            for (const auto &x : s.leaf_waves) leaf_waves.push_back({base + x.first, entry, x.second});
-            used = !s.leaf_waves.empty();
+            for (const auto &x : g.leaf_waves) leaf_waves.push_back({base + x.first, entry, x.second});
+            used = !g.leaf_waves.empty();
         } else {
-            const SLaunch &L = s.L[r.k];
+            const SLaunch &L = g.L[r.k];
             if (L.type == LAUNCH_GEMM) {
-                gemms.push_back({&s.gemms[(size_t)L.gemm], (const GemmDesc *)(base + s.gemms_off) + L.gemm, abase, mbase,
+                gemms.push_back({&g.gemms[(size_t)L.gemm], (const GemmDesc *)(base + g.gemms_off) + L.gemm, abase, mbase,
                                  s.gemm_shape});
             } else {
                 if (L.sblocks) {
@@ -778,6 +890,10 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
                         sblk.push_back({(const StreamTask *)(base + x.off), entry, x.nk, x.blk, 0});
                 }
                 for (const auto &x : L.waves) node_waves.push_back({base + x.first, entry, x.second});
+                for (const SLaunch::Chain &x : L.chains) {
+                    chains[x.kind].push_back({(const unsigned *)(base + x.off), abase, mbase, x.blk, x.jbits, x.words, 0u});
+                    chain_lds[x.kind] = std::max(chain_lds[x.kind], x.lds);
+                }
                 used = L.sblocks > 0 || !L.waves.empty();
             }
         }
@@ -785,8 +901,9 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
             works.push_back(w);
             work_woff.push_back(woff);
         }
-        if (r.k + 1 >= s.L.size()) {
-            fin.push_back({s.root < 0 ? -1 : s.root + (int)mbase, r.slot, s.root_off + abase});
+        if (r.k + 1 >= g.L.size()) {
+            fin.push_back({s.root < 0 ? -1 : s.root + (int)mbase, r.slot, g.root_off + abase,
+                           (const int *)(base + g.masks_off), mbase, g.nmasks, 0});
             finishing.push_back(std::move(r));
         } else {
             r.k += 1;
@@ -808,6 +925,8 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
     const uint64_t o_b = place(sizeof(ServeBlock) * sblk.size());
     const uint64_t o_v = place(sizeof(ServeWave) * node_waves.size());
     const uint64_t o_f = place(sizeof(FinishEntry) * fin.size());
+    uint64_t o_h[SCHAIN_KINDS];
+    for (int q = 0; q < SCHAIN_KINDS; ++q) o_h[q] = place(sizeof(ServeChain) * chains[q].size());
     if (o > v->step_cap) {
         wmc_set_error("wmc_serve: step staging overflow (%llu > %llu)", (unsigned long long)o,
                       (unsigned long long)v->step_cap);
@@ -825,6 +944,7 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
     cp(o_b, sblk.data(), sizeof(ServeBlock) * sblk.size());
     cp(o_v, node_waves.data(), sizeof(ServeWave) * node_waves.size());
     cp(o_f, fin.data(), sizeof(FinishEntry) * fin.size());
+    for (int q = 0; q < SCHAIN_KINDS; ++q) cp(o_h[q], chains[q].data(), sizeof(ServeChain) * chains[q].size());
     hipStream_t st = v->st;
     if (o) HIP_TRY(hipMemcpyAsync(stp, stage, o, hipMemcpyHostToDevice, st));
     wmc_meta *meta = (wmc_meta *)(v->dev + v->off_regions);
@@ -837,11 +957,22 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
         hipLaunchKernelGGL(k_step_serve<T>, dim3(sblocks + wblocks), dim3(256), 0, st, (const ServeWork *)(stp + o_k),
                            (const ServeBlock *)(stp + o_b), (const ServeWave *)(stp + o_v), sblocks, nwaves, lwaves, arena,
                            meta);
+    for (int q = 0; q < SCHAIN_KINDS; ++q) {
+        const dim3 grid((unsigned)chains[q].size());
+        const ServeChain *recs = (const ServeChain *)(stp + o_h[q]);
+        if (chains[q].empty()) continue;
+        if (q == SCHAIN_BIG)
+            hipLaunchKernelGGL(k_chain_big_serve<T>, grid, dim3(WMC_CHAIN_THREADS_BIG), (size_t)chain_lds[q], st, recs,
+                               arena, meta);
+        else
+            hipLaunchKernelGGL(k_chain_serve<T>, grid, dim3(1 << WMC_CHAIN_LANE_MANY), (size_t)chain_lds[q], st, recs, arena,
+                               meta);
+    }
     for (const GemmCall &g : gemms)
         launch_gemm<T>(*g.host, g.dev, arena + g.abase, meta + g.mbase, st, SliceGroup{0, 0, 0}, 1, g.shape);
     ServeRes *res = (ServeRes *)(v->dev + v->off_res);
     if (!fin.empty()) {
-        hipLaunchKernelGGL(k_finish_serve<T>, dim3((unsigned)((fin.size() + 255) / 256)), dim3(256), 0, st,
+        hipLaunchKernelGGL(k_finish_serve<T>, dim3((unsigned)((fin.size() + 3) / 4)), dim3(4 * WMC_WAVE), 0, st,
                            (const FinishEntry *)(stp + o_f), (int)fin.size(), arena, meta, res);
         HIP_TRY(hipMemcpyAsync(v->res_host[h], res, sizeof(ServeRes) * (size_t)v->opt.max_slots,
                                hipMemcpyDeviceToHost, st));

@@ -230,3 +230,33 @@ def test_chain_out_of_range_runs_the_launch_list(precision, small):
         fits = same(general, om, oe, tolerance(p))
         assert fits or small < (1e-4 if precision == "fp32" else 1e-15), seed
         assert same(v, om, oe, tolerance(p)) or not fits, (seed, v, om, oe)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision,small", [("fp64", 1e-15), ("fp32", 1e-4)])
+def test_out_of_range_chains_in_batches_and_servers(precision, small):
+    """The same weights in a batch (eager and replayed, beside an ordinary
+    instance) and served (several in flight): where the launch list gives the
+    oracle's count, both do, and the ordinary instance keeps its value."""
+    fs, refs = [wl.banded_3cnf(60, 210, 15, seed=9)], []
+    for seed in range(3):
+        f = wl.banded_3cnf(60, 210, 15, seed=seed)
+        rng = np.random.default_rng(seed)
+        fs.append(f.with_weights(np.where(rng.random((f.n, 1)) < 0.5, small, 1.0) * rng.uniform(0.1, 0.9, (f.n, 2)) *
+                                 [1.0, small]))
+    plans = [W.Plan(W.Network.from_formula(f), seed=0, precision=precision) for f in fs]
+    refs = [oracle.bucket(f) for f in fs]
+    b = W.Batch(plans)
+    ws = b.workspace()
+    for flags in (0, W.BATCH_GRAPH, W.BATCH_GRAPH | W.BATCH_RESIDENT):
+        for v, p, (om, oe) in zip(b.contract(ws=ws, flags=flags), plans, refs):
+            assert same(v, om, oe, tolerance(p)), flags
+    srv = W.Server(precision=precision, max_slots=8, hbm_budget_bytes=1 << 28, buffer_bytes=1 << 29)
+    ids = [srv.register(p) for p in plans]
+    for q in range(12):
+        srv.submit(ids[q % 4], np.asarray(fs[q % 4].weights).reshape(-1), q)
+    done = srv.drain()
+    assert sorted(r.request_id for r in done) == list(range(12))
+    for r in done:
+        om, oe = refs[r.request_id % 4]
+        assert same(r.value, om, oe, tolerance(plans[r.request_id % 4])), r.request_id
