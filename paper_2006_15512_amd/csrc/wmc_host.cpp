@@ -885,25 +885,30 @@ uint64_t wmc_place(const std::vector<int32_t> &birth, const std::vector<int32_t>
         if (elems[(size_t)a] != elems[(size_t)b]) return elems[(size_t)a] > elems[(size_t)b];
         return birth[(size_t)a] < birth[(size_t)b];
     });
+    // the placed intervals in ascending order of offset: the first gap among
+    // those that live at the same time is found in one pass
+    struct Placed {
+        uint64_t begin, end;
+        int32_t birth, death;
+    };
     std::vector<int64_t> off(NT, 0);
-    std::vector<int32_t> placed;
+    std::vector<Placed> placed;
+    placed.reserve(NT);
     uint64_t arena_elems = 0;
-    std::vector<std::pair<uint64_t, uint64_t>> busy;
     for (int32_t t : by_size) {
-        busy.clear();
-        for (int32_t p : placed) {
-            if (death[(size_t)p] < birth[(size_t)t] || death[(size_t)t] < birth[(size_t)p]) continue;
-            busy.push_back({(uint64_t)off[(size_t)p], (uint64_t)off[(size_t)p] + elems[(size_t)p]});
-        }
-        std::sort(busy.begin(), busy.end());
+        const int32_t tb = birth[(size_t)t], td = death[(size_t)t];
+        const uint64_t n = elems[(size_t)t];
         uint64_t o = 0;
-        for (auto &iv : busy) {
-            if (iv.first >= o + elems[(size_t)t]) break;
-            o = std::max(o, iv.second);
+        for (const Placed &p : placed) {
+            if (p.death < tb || td < p.birth) continue;
+            if (p.begin >= o + n) break;
+            o = std::max(o, p.end);
         }
         off[(size_t)t] = (int64_t)o;
-        arena_elems = std::max(arena_elems, o + elems[(size_t)t]);
-        placed.push_back(t);
+        arena_elems = std::max(arena_elems, o + n);
+        const auto at = std::upper_bound(placed.begin(), placed.end(), o,
+                                         [](uint64_t x, const Placed &p) { return x < p.begin; });
+        placed.insert(at, {o, o + n, tb, td});
     }
     if (offs) offs->swap(off);
     return arena_elems;
