@@ -52,6 +52,7 @@ struct Fuser {
     const std::vector<TNode> &T;
     const int elem;
     double slices = 1, level = kLaunch;
+    double total = 0;  // seconds of the plan's bytes at the streaming rate
     std::vector<int32_t> nk;       // summed variables per internal tensor
     std::vector<int32_t> id_of;    // variable -> local id while a chain is built
     std::vector<int32_t> stamp;
@@ -65,7 +66,8 @@ struct Fuser {
             bytes += (double)elem * (std::ldexp(1.0, rank(d.ta)) + std::ldexp(1.0, rank(d.tb)) + std::ldexp(1.0, d.rc));
         }
         slices = (double)P.group;
-        if (slices * bytes / kBytes > 1e-3) level = 1e-6;
+        total = slices * bytes / kBytes;
+        if (total > 1e-3) level = 1e-6;
         id_of.assign((size_t)P.n + 1, -1);
         stamp.assign((size_t)P.n + 1, 0);
     }
@@ -405,6 +407,7 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
     // the least cost.
     std::vector<Chain> chains;
     std::vector<int32_t> chain_of(NT, -1);
+    double saved = 0;
     for (int32_t c0 : P.node_order) {
         const int32_t below = fu.big(c0);
         if (!fu.fits(c0) || (P.T[(size_t)below].kind == 2 && fu.fits(below))) continue;
@@ -436,6 +439,8 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
                 }
             }
         }
+        for (int32_t q : path) saved += fu.price_node(q);
+        saved -= cost[m];
         for (size_t j = m; j > 0; j = (size_t)from[j]) {
             const size_t i = (size_t)from[j];
             if (j - i < 2) continue;
@@ -447,7 +452,11 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
             chains.push_back(std::move(h));
         }
     }
-    if (chains.empty()) return;
+    // A plan whose time goes to nodes that no chain takes (K >= 16) keeps its
+    // launch list: fusing only its small ends made the row-major 24x24 lattice
+    // 0.6% and the banded 300-variable formula 0.3% slower (FP64; the larger
+    // image), while plans that gain save over a tenth (min-fill lattice 50%).
+    if (chains.empty() || (fu.total > 1e-3 && saved < 0.05 * fu.total)) return;
 
     // items: a chain or a single node, in launch order of their last node;
     // all ready small ones share a launch, big ones run alone
@@ -736,7 +745,7 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
         unsigned fe = 0, lo = 0, hi = 0;
         const bool fcopy = w[CH_FCOPY] != 0;
         if (fcopy && !copied(w + CH_X, of, t.f, &fe)) return fail("copy of the first operand");
-        if (t.lds * P.elem > WMC_CHAIN_LDS) return fail("LDS size");
+        if (t.lds * P.elem > (t.big ? WMC_CHAIN_LDS : WMC_CHAIN_LDS_SHORT)) return fail("LDS size");
         std::vector<std::pair<unsigned, unsigned>> gr;
         for (unsigned i = 0; i < L; ++i) {
             const unsigned *s = w + CH_WORDS + i * stride;

@@ -260,3 +260,14 @@ def test_out_of_range_chains_in_batches_and_servers(precision, small):
     for r in done:
         om, oe = refs[r.request_id % 4]
         assert same(r.value, om, oe, tolerance(plans[r.request_id % 4])), r.request_id
+
+
+@pytest.mark.parametrize("name,fused", [("grid24", False), ("grid24_minfill", True)])
+def test_plan_that_chains_hardly_help_keeps_its_launch_list(name, fused):
+    """A plan whose bytes go to nodes with K >= 16 has no fused program; the
+    same formula on a tree of K <= 8 nodes has one."""
+    import bench
+    f, pkw, _, _ = bench.workload(name)
+    pkw = dict(pkw)
+    plan, _ = bench.make_plan(W, f, "fp64", pkw.pop("block"), pkw)
+    assert (plan.program()[1]["n_launches"] > 0) == fused
