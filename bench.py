@@ -272,7 +272,8 @@ def solo(W, torch, name, precision, steps, warmup, block=0, probes=None, slice_g
     ms_step = dt / steps * 1e3
 
     # per-launch timing with HIP events on the launch stream (outside the
-    # timed region), as many solves as timed ones
+    # timed region), as many solves as timed ones: the plan's launch list,
+    # node by node (the timed solves run it with chains of nodes fused)
     bytes_l, flops_l, cls_l = W.plan_launches(plan)
     kern_l = W.plan_kernels(plan)
     reps = max(3, steps)
@@ -321,6 +322,7 @@ def solo(W, torch, name, precision, steps, warmup, block=0, probes=None, slice_g
         roof = {"bound": "mfma", "achieved": round(ach_tf, 2), "peak": peak_tf, "unit": "TFLOP/s",
                 "frac": round(ach_tf / peak_tf, 4), "traffic": traffic}
     roof["kernel"] = dom
+    roof["launch_list"] = "node by node"
     roof["launches_per_solve"] = d["launches"]
     roof["bytes_per_launch"] = d["bytes"] / d["launches"]
     roof["us_per_launch"] = round(d["ms"] * 1e3 / d["launches"], 2)

@@ -190,7 +190,7 @@ typedef struct {
     uint64_t arena_bytes;       /* static arena after placement (MemCost, what mem_cap bounds) */
     uint64_t workspace_bytes;   /* device workspace wmc_contract needs */
     int64_t class_hist[WMC_N_CLASSES];
-    int64_t n_launches;         /* kernel launches per slice */
+    int64_t n_launches;         /* kernel launches per slice, node by node */
     double max_node_bytes;      /* largest single-node traffic */
     int32_t n_aux_vars;         /* auxiliary variables of factored long clauses */
     int32_t slice_group;        /* slices per launch (workspace holds this many arenas) */
@@ -312,13 +312,14 @@ wmc_status wmc_contract_slices(const wmc_plan_t *plan, const double *weights, vo
                                uint64_t workspace_bytes, void *stream, int64_t slice_begin,
                                int64_t slice_end, wmc_value *out, wmc_value *per_slice);
 
-/* Per-launch accounting for measurement.  Launch k of one slice, in the
- * order wmc_contract issues them: 0 = meta reset, 1 = leaf fill, then the
- * node launches, last = slice accumulation.  wmc_plan_launches gives each
+/* Per-launch accounting for measurement, of the plan's launch list (node by
+ * node; wmc_contract runs the program of wmc_plan_program, in which chains
+ * of those nodes are fused).  Launch k of one slice: 0 = meta reset, 1 = leaf
+ * fill, then the node launches, last = slice accumulation.  wmc_plan_launches gives each
  * launch's algorithmic bytes (elem_size * (|A|+|B|+|C|) summed over its
  * nodes), flops (2*b*m*n*k) and node class (-1 for non-node launches); with
- * all arrays NULL it only reports *n_out.  wmc_contract_profile is
- * wmc_contract with a HIP event recorded on `stream` around every launch;
+ * all arrays NULL it only reports *n_out.  wmc_contract_profile runs that
+ * list with a HIP event recorded on `stream` around every launch;
  * ms (cap >= n_out entries) receives in ms[k] the duration of launch k in
  * that same order, summed over the slices. */
 wmc_status wmc_plan_launches(const wmc_plan_t *plan, double *bytes, double *flops, int32_t *cls,
@@ -342,7 +343,7 @@ enum {
     WMC_KERNEL_STREAM2_SPLIT = 7, /* k_stream2_split: summed index split over lane groups */
     WMC_KERNEL_FINISH = 8,        /* k_finish: slice accumulation */
     WMC_KERNEL_STREAM2_VEC = 9,   /* k_stream2_vec: K = 1 streaming node, output pairs per thread */
-    WMC_KERNEL_CHAIN = 10         /* k_chain: consecutive nodes with their intermediates in LDS, and small nodes */
+    WMC_KERNEL_CHAIN = 10         /* k_chain, k_chain_big: fused nodes (wmc_plan_program; not in launch lists) */
 };
 wmc_status wmc_plan_kernels(const wmc_plan_t *plan, int32_t *kernel, int64_t cap, int64_t *n_out);
 

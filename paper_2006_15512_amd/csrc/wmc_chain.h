@@ -224,7 +224,12 @@ __device__ __forceinline__ ChainMaps chain_maps(chain_words st, const unsigned *
 }
 
 // Chains of many tiles: the thread's 2^(NP + NQ) outputs of every entry
-// index.  SG: the source rows are in memory (stage 1), else in LDS; DG: the
+// index.  Bound by instruction issue (about 100 vector and 100 scalar
+// instructions per wave and stage beside the products) and the L2 latency of
+// G: 4 waves per workgroup and 2 x 2 outputs per thread took the min-fill
+// lattice from 57 (8 waves) to 42 ms; copying each tile's part of G to LDS
+// leaves room for smaller tiles only (59 ms), and fetching the next stage's G
+// ahead costs registers (50 ms).  SG: the source rows are in memory (stage 1), else in LDS; DG: the
 // outputs go to memory (last stage), else to LDS.
 template <typename T, int NK, int NP, int NQ, bool SG, bool DG>
 __device__ __forceinline__ void chain_stage(chain_words st, const T *__restrict__ S, const T *__restrict__ G,
@@ -402,9 +407,12 @@ __device__ __forceinline__ long long chain_base(unsigned lo, unsigned hi) {
     return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
-// One tile of a short chain, by a workgroup of 2^LB threads: 2^9 where a call
+// One tile of a short chain.  What bounds it is waiting: read where they are
+// first needed, a stage's words, its G and its sources are a cold miss each
+// (2 to 3 us a stage); fetched together before the first stage, a stage takes
+// 0.4 to 0.7 us and the start 3 us.  A workgroup of 2^LB threads: 2^9 where a call
 // waits for it, 2^8 where many chains share the device and each wave's fixed
-// instructions count.  smem: the chain's words, then (from the next
+// instructions count (512-instance batch FP64 4.18 -> 3.72 ms).  smem: the chain's words, then (from the next
 // 1024-byte boundary) its LDS entries.
 template <typename T, int LB>
 __device__ __forceinline__ void chain_run_short(const unsigned *__restrict__ words, unsigned nwords, unsigned tile,

@@ -104,7 +104,10 @@ struct GemmDesc {
 #define WMC_CHAIN_LANE_BIG 8    // and chains of many tiles
 // LDS bytes of a chain, its words included.  Short chains: four workgroups
 // of 8 waves fill a compute unit's 32 wave slots, so its 160 KB are shared by
-// four; many tiles: three workgroups of 4 waves at 110 registers.
+// four (512-instance batch FP64: 6.2 ms at 56 KB, 4.2 at 38, and 4.1 at 19
+// with its shorter chains against 3.7 once 38 KB chains had a launch of their
+// own); many tiles: three workgroups of 4 waves at 110 registers (min-fill
+// lattice FP64: 54.6 ms at 30 KB, 48.7 at 38, 42.8 at 50, 42.9 at 72).
 #define WMC_CHAIN_LDS_SHORT (38 * 1024)
 #define WMC_CHAIN_LDS (50 * 1024)
 #define WMC_CHAIN_TILE_BITS 11  // largest tile index of a short chain
