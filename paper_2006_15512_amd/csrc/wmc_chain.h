@@ -10,11 +10,21 @@
 //
 // Numerics: a stage forms every sum in double, in the order of the summed
 // index, and rounds once to the storage type, as the other node kernels do;
-// only the power of two an intermediate is stored with differs (it cannot
-// be brought to [0.5, 1) before all its tiles exist).  Each stage therefore
-// reports whether it had an entry of ordinary size: if an intermediate was
-// nonzero but everywhere below chain_tiny, the caller runs the general launch
-// list instead.
+// only the power of two a tensor is stored with differs.  The launch list
+// brings every operand's largest entry to [0.5, 1) as it reads it; the tiles
+// of an intermediate exist one after another, so here stage i reads F_{i-1}
+// as it was stored.  Instead the whole chain, F_L included, is stored
+// 2^lift larger (chain word CS_LIFT; the published exponent takes it back).
+//
+// Range: let S_i be F_i as stored here and R_i as the launch list stores it,
+// S_i = 2^c_i R_i.  The list reads R_i scaled by the power of two that S_i is
+// 2^e_i away from, e_i the exponent of S_i's largest entry, so c_1 = lift
+// and c_{i+1} = e_i.  As long as every intermediate has an entry of at least
+// chain_tiny = 2^-1 (e_i >= 0), no c_i is negative: nothing the launch list
+// can represent is lost here, neither in an intermediate nor in F_L.  Each
+// stage but the last reports whether its unrounded sums reached chain_tiny
+// and whether one was nonzero; a chain with an intermediate that was nonzero
+// but below chain_tiny everywhere is run again on the general launch list.
 #pragma once
 #include "wmc_kernels.h"
 
@@ -25,17 +35,8 @@ __device__ __forceinline__ chain_words const_words(const unsigned *p) {
     return (chain_words)(unsigned long long)p;
 }
 
-// FP32 intermediates are kept 2^64 larger (at most 2^(64 + 45) after 15
-// stages of 8 terms each), so that an intermediate may lose 96 bits of
-// magnitude against F_0 before its largest entry falls below chain_tiny, and
-// 94 more bits of entries below that one are still normal numbers.  The last
-// stage takes the 2^64 back.
-template <typename T>
-__device__ __forceinline__ constexpr int chain_lift() { return sizeof(T) == 4 ? 64 : 0; }
-template <typename T>
-__device__ __forceinline__ constexpr double chain_tiny(bool last) {
-    return sizeof(T) == 4 ? (last ? 0x1p-64 : 0x1p-32) : (last ? 0x1p-512 : 0x1p-128);
-}
+// Smallest largest entry of an intermediate (see Range above).
+constexpr double chain_tiny = 0.5;
 
 // LDS entry e sits at slot chain_slot(e): 16-byte units XOR-ed with the
 // three address bits above a 128-byte bank row, so that lanes reading rows
@@ -372,7 +373,7 @@ __device__ __forceinline__ ChainLanes chain_lanes(WP ch, unsigned L, unsigned ob
 }
 
 // In lane i, the power of two stage i's products are scaled by; the first
-// workgroup also publishes the chain's exponent.
+// workgroup also publishes the chain's exponent.  lift: CS_LIFT.
 __device__ __forceinline__ int chain_shifts(const ChainLanes &c, unsigned L, wmc_meta *meta, unsigned tc, bool first,
                                             int lift) {
     const unsigned lane = threadIdx.x & 63u;
@@ -380,17 +381,16 @@ __device__ __forceinline__ int chain_shifts(const ChainLanes &c, unsigned L, wmc
     if (first && threadIdx.x < 64) {
         long long e = lane <= L ? c.exp + own : 0;
         for (int o = 8; o > 0; o >>= 1) e += __shfl_xor(e, o, WMC_WAVE);
-        if (lane == 0) meta[tc].exp = e;
+        if (lane == 0) meta[tc].exp = e - lift;
     }
     const int f = __builtin_amdgcn_readlane(own, L);
-    return (lane == 0 ? lift - own - f : -own) - (lane + 1 == L ? lift : 0);
+    return lane == 0 ? lift - own - f : -own;
 }
 
-// Range bits of stage s's intermediate, whose largest magnitude in this
-// thread is v: an ordinary entry, a nonzero entry.
-template <typename T>
-__device__ __forceinline__ unsigned chain_range(double v, unsigned s, bool last) {
-    return ((v >= chain_tiny<T>(last) ? 1u : 0u) | (v > 0.0 ? 2u : 0u)) << (2 * s);
+// Range bits of stage s's intermediate, whose largest unrounded magnitude in
+// this thread is v: an ordinary entry, a nonzero entry.
+__device__ __forceinline__ unsigned chain_range(double v, unsigned s) {
+    return ((v >= chain_tiny ? 1u : 0u) | (v > 0.0 ? 2u : 0u)) << (2 * s);
 }
 
 __device__ __forceinline__ void chain_end(wmc_meta *meta, unsigned tmask, unsigned tc, unsigned range, double vmax) {
@@ -452,7 +452,7 @@ __device__ __forceinline__ void chain_run_short(const unsigned *__restrict__ wor
 #pragma unroll
     for (int b = 0; b < LB; ++b) mask[b] = 0u - ((tid >> b) & 1u);
     const unsigned tc = uni(ch[CH_TC]);
-    const int shift = chain_shifts(cl, L, meta, tc, tile == 0u, chain_lift<T>());
+    const int shift = chain_shifts(cl, L, meta, tc, tile == 0u, (int)uni(ch[CH_WORDS + CS_LIFT]));
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     unsigned range = 0;
@@ -464,11 +464,10 @@ __device__ __forceinline__ void chain_run_short(const unsigned *__restrict__ wor
         double v = 0.0;
         if (s + 1 == L) {
             chain_stage_short_any<T, LB, false, true>(ch, w, wave, F0, C, lds, mask, se, vmax);
-            range |= chain_range<T>(vmax, s, true);
         } else {
             if (s == 0 && !fcopy) chain_stage_short_any<T, LB, true, false>(ch, w, wave, F0, C, lds, mask, se, v);
             else chain_stage_short_any<T, LB, false, false>(ch, w, wave, F0, C, lds, mask, se, v);
-            range |= chain_range<T>(v, s, false);
+            range |= chain_range(v, s);
             chain_barrier();
         }
     }
@@ -485,7 +484,7 @@ __device__ __forceinline__ void chain_run_big(chain_words ch, unsigned blk, unsi
     const unsigned L = ch[CH_STAGES], ob = ch[CH_TILE_BITS];
     const ChainLanes cl = chain_lanes<CS_WORDS_BIG>(ch, L, ob, blk << jb, meta);
     unsigned cur = cl.off;
-    const int shift = chain_shifts(cl, L, meta, ch[CH_TC], blk == 0u, chain_lift<T>());
+    const int shift = chain_shifts(cl, L, meta, ch[CH_TC], blk == 0u, (int)ch[CH_WORDS + CS_LIFT]);
     const unsigned tab = CH_WORDS + L * CS_WORDS_BIG + lane * ob;
     unsigned mask[6];
 #pragma unroll
@@ -512,11 +511,10 @@ __device__ __forceinline__ void chain_run_big(chain_words ch, unsigned blk, unsi
             if (s + 1 == L) {
                 chain_stage_any<T, false, true>(st, S, G, C, lds, mask, wave, se, nt, v);
                 vmax = fmax(vmax, v);
-                range |= chain_range<T>(v, s, true);
             } else {
                 if (s == 0) chain_stage_any<T, true, false>(st, S, G, C, lds, mask, wave, se, nt, v);
                 else chain_stage_any<T, false, false>(st, S, G, C, lds, mask, wave, se, nt, v);
-                range |= chain_range<T>(v, s, false);
+                range |= chain_range(v, s);
             }
             chain_barrier();
         }

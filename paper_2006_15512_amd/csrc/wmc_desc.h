@@ -111,6 +111,15 @@ struct GemmDesc {
 #define WMC_CHAIN_LDS_SHORT (38 * 1024)
 #define WMC_CHAIN_LDS (50 * 1024)
 #define WMC_CHAIN_TILE_BITS 11  // largest tile index of a short chain
+// log2 of the bound of a chain's stored magnitudes.  Every operand entry is
+// below 1 as it is read, so F_i stays below 2^(lift + summed variables up to
+// stage i): the lift is this bound less all of the chain's summed variables.
+// FP32: below the largest finite number.  FP64, and FP32 where a matrix node
+// (K >= 16) reads the output: those multiply the operands as stored, in that
+// type, so the product of two such tensors, summed, stays finite, too.
+#define WMC_CHAIN_TOP_FP32 126
+#define WMC_CHAIN_TOP_FP32_MATRIX 56
+#define WMC_CHAIN_TOP_FP64 480
 // A copied operand: log2 of its entries per tile, the lowest of them whose
 // offset is the entry index itself, its first LDS entry, and the word where
 // the offsets of the other index bits are listed.
@@ -136,7 +145,8 @@ enum {
 // entries except F_0 where it is not copied and the last output.
 enum {
     CS_SHAPE = 0,               // nk | source-only register bits << 8 | G-only ones << 16
-    CS_TBITS, CS_G, CS_G_HI, CS_TG, CS_SRC, CS_DST, CS_PAD,
+    CS_TBITS, CS_G, CS_G_HI, CS_TG, CS_SRC, CS_DST,
+    CS_LIFT,                    // first stage: log2 of the factor F_1 .. F_L are stored larger by
     CS_BIT_SG,                  // short
     CS_X = CS_BIT_SG + 16,
     CS_WORDS = CS_X + CX_WORDS,

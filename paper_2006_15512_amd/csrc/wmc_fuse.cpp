@@ -244,6 +244,18 @@ struct Fuser {
         return (C.cls == WMC_CLASS_SMALL ? level : kLaunch) + slices * (double)elem * b / kBytes;
     }
 
+    int lift(const Chain &h) const {
+        int summed = 0;
+        for (uint64_t k : h.kap) summed += bits(k);
+        return top(h.nodes.back()) - summed;
+    }
+    // Bound of the stored magnitudes of a chain that ends at `out`.
+    int top(int32_t out) const {
+        const int32_t up = T[(size_t)out].parent;
+        if (elem == 8) return WMC_CHAIN_TOP_FP64;
+        return up >= 0 && nk[(size_t)up] >= 4 ? WMC_CHAIN_TOP_FP32_MATRIX : WMC_CHAIN_TOP_FP32;
+    }
+
     // The chain's words.  Positions: the entry index of stage i's output
     // tile numbers its inner variables in F_i's storage order (F_i stores
     // [kappa_{i+1} | F_{i+1}'s order], so the summed entries of the next
@@ -352,6 +364,7 @@ struct Fuser {
             w[s + CS_TG] = (unsigned)h.gs[i];
             w[s + CS_SRC] = (unsigned)(i ? (i % 2 ? h.odd : h.even) : std::max(h.fcopy, 0));
             w[s + CS_DST] = (unsigned)(last ? 0 : i % 2 ? h.even : h.odd);
+            if (i == 0) w[s + CS_LIFT] = (unsigned)lift(h);
             const std::vector<int> pg =
                 h.big ? place(h.gs[i]) : copy(s + CS_X, h.gs[i], h.vg[i] & (h.inner | h.kap[i]), h.gcopy[i]);
             auto S = [&](int32_t v) { return (vp & bit(v)) ? offset(src[(size_t)id_of[(size_t)v]]) : 0u; };
@@ -747,6 +760,10 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
         if (fcopy && !copied(w + CH_X, of, t.f, &fe)) return fail("copy of the first operand");
         if (t.lds * P.elem > (t.big ? WMC_CHAIN_LDS : WMC_CHAIN_LDS_SHORT)) return fail("LDS size");
         std::vector<std::pair<unsigned, unsigned>> gr;
+        unsigned summed = 0;
+        for (unsigned i = 0; i < L; ++i) summed += w[CH_WORDS + i * stride + CS_SHAPE] & 255u;
+        if (w[CH_WORDS + CS_LIFT] + summed > (unsigned)(P.elem == 8 ? WMC_CHAIN_TOP_FP64 : WMC_CHAIN_TOP_FP32))
+            return fail("lift");
         for (unsigned i = 0; i < L; ++i) {
             const unsigned *s = w + CH_WORDS + i * stride;
             unsigned long long og = 0;
