@@ -556,8 +556,9 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
         elems.push_back((((uint64_t)1 << fu.rank((int32_t)t)) + align - 1) / align * align);
     }
     std::vector<int64_t> offs;
-    F.arena_bytes = wmc_place(birth, death, elems, &offs) * (uint64_t)P.elem;
-    if (F.arena_bytes > max_arena) return;
+    const uint64_t arena_bytes = wmc_place(birth, death, elems, &offs) * (uint64_t)P.elem;
+    if (arena_bytes > max_arena) return;
+    F.arena_bytes = arena_bytes;
     F.off.assign(NT, -1);
     for (size_t q = 0; q < stored.size(); ++q) F.off[(size_t)stored[q]] = offs[q];
 
