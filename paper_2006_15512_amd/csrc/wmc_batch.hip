@@ -16,6 +16,7 @@
 // roots with one kernel.  The whole sequence can be captured once as a HIP
 // graph and replayed.
 #include <array>
+#include <memory>
 #include <mutex>
 
 #include "wmc_chain.h"
@@ -75,7 +76,7 @@ struct BatchStep {
 };
 
 // The instances' fused programs merged by launch index, with an image of
-// their own that takes the place of the launch lists' one.
+// their own beside the launch lists' one.
 struct BatchFused {
     bool on = false;
     std::vector<LeafDesc> leaves;
@@ -87,7 +88,7 @@ struct BatchFused {
     std::vector<int> tables, mask_first, masks;
     std::vector<long long> root_off;
     std::vector<BatchStep> steps;
-    // offsets from the descriptor region's start
+    // offsets from the image's start
     uint64_t o_leaf = 0, o_node = 0, o_gemm = 0, o_tasks = 0, o_words = 0, o_recs = 0, o_tables = 0, o_mask_first = 0,
              o_masks = 0, o_roots = 0, o_rootoff = 0, o_leaf_eta = 0;
     std::vector<uint8_t> image;
@@ -133,9 +134,16 @@ struct wmc_batch {
     std::vector<uint8_t> image;  // [off_leaf, off_arena) of the workspace
     std::mutex mu;
     void *graph_ws = nullptr;
-    void *image_ws = nullptr;  // workspace a descriptor image was last uploaded to
-    bool image_fused = false;  // which one: the fused programs' or the launch lists'
+    // workspace each descriptor image was last uploaded to: [0] the launch
+    // lists', [1] the fused programs'
+    void *image_ws[2] = {nullptr, nullptr};
     BatchFused fused;
+    // with fused programs: their image, and one byte per tensor that names
+    // the instances whose launch lists run
+    uint64_t off_fused = 0, off_live = 0;
+    std::vector<int64_t> meta_first;   // first tensor of instance j (n_inst + 1 entries)
+    std::vector<int32_t> inst_launches, launch_at;  // launches of instance j's plan; the one that launch k merges
+    std::vector<uint8_t> live;
     // persistent form: the merged steps' arguments (absolute pointers into a
     // workspace, so kept after the arena and rebuilt for a new workspace)
     uint64_t off_steps = 0;
@@ -156,9 +164,6 @@ static uint64_t bal(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::vector<int64_t> &iplan,
                        const std::vector<int64_t> &abase, const std::vector<int64_t> &mbase) {
     BatchFused &F = B.fused;
-    bool any = false;
-    for (int64_t i = 0; i < B.n; ++i) any = any || plans[i]->fused.on;
-    if (!any) return;
     std::vector<FusedProgram> prog;
     size_t kmax = 0;
     for (int64_t i = 0; i < B.n; ++i) {
@@ -273,6 +278,212 @@ static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::
     F.on = true;
 }
 
+// What the fused programs may add to a batch's workspace (their image, and
+// arenas that grew): a quarter, and in large batches not more than 1 GiB, so
+// that a batch that fills the device goes on fitting it.  (512 instances of
+// 15 to 24 variables: 0.99 -> 1.06 GB in FP64, 0.54 -> 0.61 in FP32.)
+static bool batch_growth_ok(uint64_t list_bytes, uint64_t bytes) {
+    const uint64_t most = std::max<uint64_t>(64ull << 20, std::min<uint64_t>(list_bytes / 4, 1ull << 30));
+    return bytes <= list_bytes + most;
+}
+
+// A batch of checked plans; null if `fuse` and the fused programs would take
+// too much memory.
+static std::unique_ptr<wmc_batch> make_batch(const wmc_plan_t *const *plans, int64_t n, bool fuse) {
+    std::unique_ptr<wmc_batch> B(new wmc_batch());
+    B->precision = plans[0]->precision;
+    B->gemm_shape = GemmShape{plans[0]->tune.gemm_tpw_max_nt, plans[0]->tune.gemm_orient};
+    B->elem = plans[0]->elem;
+    B->n = n;
+    // instances: slice eta of plan i is instance inst_first[i] + eta
+    B->inst_first.assign((size_t)n + 1, 0);
+    for (int64_t i = 0; i < n; ++i)
+        B->inst_first[(size_t)i + 1] = B->inst_first[(size_t)i] + ((int64_t)1 << plans[i]->sliced.size());
+    const int64_t ni = B->inst_first[(size_t)n];
+    B->n_inst = ni;
+    std::vector<int64_t> iplan((size_t)ni), ieta((size_t)ni);
+    for (int64_t i = 0; i < n; ++i)
+        for (int64_t j = B->inst_first[(size_t)i]; j < B->inst_first[(size_t)i + 1]; ++j) {
+            iplan[(size_t)j] = i;
+            ieta[(size_t)j] = j - B->inst_first[(size_t)i];
+        }
+    std::vector<int64_t> abase((size_t)ni), mbase((size_t)ni);
+    int64_t arena_elems = 0, list_elems = 0, meta = 0, vars = 0;
+    size_t kmax = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        const wmc_plan_t &P = *plans[i];
+        B->var_off.push_back(vars);
+        B->nvars.push_back(P.n);
+        B->nuser.push_back(P.n_user);
+        B->n_user_total += P.n_user;
+        B->w.insert(B->w.end(), P.w.begin(), P.w.end());
+        vars += P.n;
+        kmax = std::max(kmax, P.launches.size());
+    }
+    for (int64_t j = 0; j < ni; ++j) {
+        const wmc_plan_t &P = *plans[iplan[(size_t)j]];
+        abase[(size_t)j] = arena_elems;
+        mbase[(size_t)j] = meta;
+        const uint64_t own = fuse && P.fused.on ? std::max(P.arena_bytes, P.fused.arena_bytes) : P.arena_bytes;
+        arena_elems += (int64_t)bal(own / (uint64_t)P.elem, 64);
+        list_elems += (int64_t)bal(P.arena_bytes / (uint64_t)P.elem, 64);
+        meta += (int64_t)P.T.size();
+    }
+    B->meta_first = mbase;
+    B->launch_at.push_back(0);
+    for (int64_t j = 0; j < ni; ++j) B->inst_launches.push_back((int32_t)plans[iplan[(size_t)j]]->launches.size());
+    B->meta_first.push_back(meta);
+    B->n_vars_total = vars;
+    B->meta_total = std::max<int64_t>(meta, 1);
+    // leaves
+    B->launches.push_back({LAUNCH_LEAF, 0, 0, 0, 0});
+    for (int64_t j = 0; j < ni; ++j) {
+        const int64_t i = iplan[(size_t)j];
+        const wmc_plan_t &P = *plans[i];
+        for (LeafDesc d : P.leaves) {
+            d.out += abase[(size_t)j];
+            d.tensor += (int)mbase[(size_t)j];
+            if (d.kind != WMC_LEAF_CLAUSE) d.var += (int)B->var_off[(size_t)i];
+            d.work_begin = B->leaf_work;
+            B->leaf_work += (int64_t)bal((uint64_t)1 << d.rank, WMC_WAVE);
+            B->leaves.push_back(d);
+            B->leaf_eta.push_back((unsigned long long)ieta[(size_t)j]);
+        }
+    }
+    B->launches[0].work = B->leaf_work;
+    std::vector<int> ltab;
+    wave_leaf_table(B->leaves, B->leaf_work, ltab);
+    B->leaf_tab_off = (int64_t)B->tables.size();
+    B->tables.insert(B->tables.end(), ltab.begin(), ltab.end());
+    // node launches, merged by index; big streaming nodes become tasks
+    B->task_first.push_back(0);
+    B->task_nk.push_back({0, 0, 0, 0, 0});
+    B->wave_off.push_back(0);
+    B->btask_off.push_back(0);
+    std::vector<int> tab;
+    for (size_t k = 1; k < kmax; ++k) {
+        Launch merged{LAUNCH_NODES, (int32_t)B->nodes.size(), 0, 0, 0};
+        std::vector<Launch> gemm_launches;
+        std::vector<NodeDesc> step_nodes;
+        for (int64_t j = 0; j < ni; ++j) {
+            const wmc_plan_t &P = *plans[iplan[(size_t)j]];
+            const size_t i = (size_t)j;  // instance: arena and meta base
+            if (k >= P.launches.size()) continue;
+            const Launch &L = P.launches[k];
+            if (L.type == LAUNCH_GEMM) {
+                GemmDesc g = P.gemms[(size_t)L.pad];
+                g.a += abase[(size_t)i];
+                g.b += abase[(size_t)i];
+                g.c += abase[(size_t)i];
+                g.ta += (int)mbase[(size_t)i];
+                g.tb += (int)mbase[(size_t)i];
+                g.tc += (int)mbase[(size_t)i];
+                gemm_launches.push_back({LAUNCH_GEMM, 0, 1, (int32_t)B->gemms.size(), 0});
+                B->gemms.push_back(g);
+                continue;
+            }
+            for (int32_t q = 0; q < L.count; ++q) {
+                NodeDesc d = P.nodes[(size_t)(L.first + q)];
+                d.a += abase[(size_t)i];
+                d.b += abase[(size_t)i];
+                d.c += abase[(size_t)i];
+                d.ta += (int)mbase[(size_t)i];
+                d.tb += (int)mbase[(size_t)i];
+                d.tc += (int)mbase[(size_t)i];
+                step_nodes.push_back(d);
+            }
+        }
+        std::vector<StreamTask> tasks;
+        std::vector<int> nkf;
+        int64_t work = 0;
+        split_stream(step_nodes, tasks, nkf, work, plans[0]->tune.multi_min_rank);
+        merged.count = (int32_t)step_nodes.size();
+        merged.work = work;
+        B->nodes.insert(B->nodes.end(), step_nodes.begin(), step_nodes.end());
+        if (merged.count || !tasks.empty()) {
+            B->launches.push_back(merged);
+            B->launch_at.push_back((int32_t)k);
+            B->task_first.push_back((int)B->tasks.size());
+            B->task_nk.push_back({nkf[0], nkf[1], nkf[2], nkf[3], nkf[4]});
+            B->tasks.insert(B->tasks.end(), tasks.begin(), tasks.end());
+            B->wave_off.push_back((int64_t)B->tables.size());
+            wave_node_table(step_nodes, work, tab);
+            B->tables.insert(B->tables.end(), tab.begin(), tab.end());
+            B->btask_off.push_back((int64_t)B->tables.size());
+            block_task_table(tasks, nkf, tab);
+            B->tables.insert(B->tables.end(), tab.begin(), tab.end());
+        }
+        for (const Launch &g : gemm_launches) {
+            B->launches.push_back(g);
+            B->launch_at.push_back((int32_t)k);
+            B->task_first.push_back((int)B->tasks.size());
+            B->task_nk.push_back({0, 0, 0, 0, 0});
+            B->wave_off.push_back(0);
+            B->btask_off.push_back(0);
+        }
+    }
+    for (int64_t j = 0; j < ni; ++j) {
+        const wmc_plan_t &P = *plans[iplan[(size_t)j]];
+        B->roots.push_back(P.root < 0 ? -1 : P.root + (int)mbase[(size_t)j]);
+        B->root_off.push_back(P.root < 0 ? 0 : (long long)(P.T[(size_t)P.root].off + abase[(size_t)j]));
+    }
+    // workspace layout
+    uint64_t off = 0;
+    B->off_res = off;
+    off += bal(sizeof(BatchRes) * (uint64_t)ni, 256);
+    B->off_w = off;
+    off += bal(sizeof(double) * 2 * (uint64_t)std::max<int64_t>(vars, 1), 256);
+    B->off_meta = off;
+    off += bal(sizeof(wmc_meta) * (uint64_t)B->meta_total, 256);
+    B->off_leaf = off;
+    off += bal(sizeof(LeafDesc) * std::max<size_t>(B->leaves.size(), 1), 256);
+    B->off_node = off;
+    off += bal(sizeof(NodeDesc) * std::max<size_t>(B->nodes.size(), 1), 256);
+    B->off_gemm = off;
+    off += bal(sizeof(GemmDesc) * std::max<size_t>(B->gemms.size(), 1), 256);
+    B->off_tasks = off;
+    off += bal(sizeof(StreamTask) * std::max<size_t>(B->tasks.size(), 1), 256);
+    B->off_roots = off;
+    off += bal(sizeof(int) * (uint64_t)ni, 256);
+    B->off_rootoff = off;
+    off += bal(sizeof(long long) * (uint64_t)ni, 256);
+    B->off_leaf_eta = off;
+    off += bal(sizeof(unsigned long long) * std::max<size_t>(B->leaf_eta.size(), 1), 256);
+    B->off_tables = off;
+    off += bal(sizeof(int) * std::max<size_t>(B->tables.size(), 1), 256);
+    B->desc_bytes = off - B->off_leaf;
+    const uint64_t list_off = off;
+    if (fuse) fuse_batch(*B, plans, iplan, abase, mbase);
+    if (B->fused.on) {
+        B->off_fused = off;
+        off += bal(B->fused.image.size(), 256);
+        B->off_live = off;
+        off += bal((uint64_t)B->meta_total, 256);
+        if (!batch_growth_ok(list_off + (uint64_t)list_elems * (uint64_t)B->elem,
+                             off + (uint64_t)arena_elems * (uint64_t)B->elem))
+            return nullptr;
+    }
+    B->off_arena = off;
+    B->arena_bytes = (uint64_t)arena_elems * (uint64_t)B->elem;
+    B->off_steps = off + bal(B->arena_bytes, 256);
+    // [barrier counter, flag][step arguments]
+    B->workspace_bytes = B->off_steps + 256 + bal(sizeof(StepArgs) * B->launches.size(), 256);
+    B->image.assign(B->desc_bytes, 0);
+    uint8_t *img = B->image.data();
+    auto put = [&](uint64_t o, const void *src, size_t bytes) {
+        if (bytes) std::memcpy(img + (o - B->off_leaf), src, bytes);
+    };
+    put(B->off_leaf, B->leaves.data(), sizeof(LeafDesc) * B->leaves.size());
+    put(B->off_node, B->nodes.data(), sizeof(NodeDesc) * B->nodes.size());
+    put(B->off_gemm, B->gemms.data(), sizeof(GemmDesc) * B->gemms.size());
+    put(B->off_tasks, B->tasks.data(), sizeof(StreamTask) * B->tasks.size());
+    put(B->off_roots, B->roots.data(), sizeof(int) * B->roots.size());
+    put(B->off_rootoff, B->root_off.data(), sizeof(long long) * B->root_off.size());
+    put(B->off_tables, B->tables.data(), sizeof(int) * B->tables.size());
+    put(B->off_leaf_eta, B->leaf_eta.data(), sizeof(unsigned long long) * B->leaf_eta.size());
+    return B;
+}
+
 extern "C" wmc_status wmc_batch_create(const wmc_plan_t *const *plans, int64_t n, wmc_batch **out) {
     if (!out) {
         wmc_set_error("wmc_batch_create: out is NULL");
@@ -299,181 +510,11 @@ extern "C" wmc_status wmc_batch_create(const wmc_plan_t *const *plans, int64_t n
         }
     }
     try {
-        wmc_batch *B = new wmc_batch();
-        B->precision = plans[0]->precision;
-        B->gemm_shape = GemmShape{plans[0]->tune.gemm_tpw_max_nt, plans[0]->tune.gemm_orient};
-        B->elem = plans[0]->elem;
-        B->n = n;
-        // instances: slice eta of plan i is instance inst_first[i] + eta
-        B->inst_first.assign((size_t)n + 1, 0);
-        for (int64_t i = 0; i < n; ++i)
-            B->inst_first[(size_t)i + 1] = B->inst_first[(size_t)i] + ((int64_t)1 << plans[i]->sliced.size());
-        const int64_t ni = B->inst_first[(size_t)n];
-        B->n_inst = ni;
-        std::vector<int64_t> iplan((size_t)ni), ieta((size_t)ni);
-        for (int64_t i = 0; i < n; ++i)
-            for (int64_t j = B->inst_first[(size_t)i]; j < B->inst_first[(size_t)i + 1]; ++j) {
-                iplan[(size_t)j] = i;
-                ieta[(size_t)j] = j - B->inst_first[(size_t)i];
-            }
-        std::vector<int64_t> abase((size_t)ni), mbase((size_t)ni);
-        int64_t arena_elems = 0, meta = 0, vars = 0;
-        size_t kmax = 0;
-        for (int64_t i = 0; i < n; ++i) {
-            const wmc_plan_t &P = *plans[i];
-            B->var_off.push_back(vars);
-            B->nvars.push_back(P.n);
-            B->nuser.push_back(P.n_user);
-            B->n_user_total += P.n_user;
-            B->w.insert(B->w.end(), P.w.begin(), P.w.end());
-            vars += P.n;
-            kmax = std::max(kmax, P.launches.size());
-        }
-        for (int64_t j = 0; j < ni; ++j) {
-            const wmc_plan_t &P = *plans[iplan[(size_t)j]];
-            abase[(size_t)j] = arena_elems;
-            mbase[(size_t)j] = meta;
-            arena_elems += (int64_t)bal(std::max(P.arena_bytes, P.fused.arena_bytes) / (uint64_t)P.elem, 64);
-            meta += (int64_t)P.T.size();
-        }
-        B->n_vars_total = vars;
-        B->meta_total = std::max<int64_t>(meta, 1);
-        // leaves
-        B->launches.push_back({LAUNCH_LEAF, 0, 0, 0, 0});
-        for (int64_t j = 0; j < ni; ++j) {
-            const int64_t i = iplan[(size_t)j];
-            const wmc_plan_t &P = *plans[i];
-            for (LeafDesc d : P.leaves) {
-                d.out += abase[(size_t)j];
-                d.tensor += (int)mbase[(size_t)j];
-                if (d.kind != WMC_LEAF_CLAUSE) d.var += (int)B->var_off[(size_t)i];
-                d.work_begin = B->leaf_work;
-                B->leaf_work += (int64_t)bal((uint64_t)1 << d.rank, WMC_WAVE);
-                B->leaves.push_back(d);
-                B->leaf_eta.push_back((unsigned long long)ieta[(size_t)j]);
-            }
-        }
-        B->launches[0].work = B->leaf_work;
-        std::vector<int> ltab;
-        wave_leaf_table(B->leaves, B->leaf_work, ltab);
-        B->leaf_tab_off = (int64_t)B->tables.size();
-        B->tables.insert(B->tables.end(), ltab.begin(), ltab.end());
-        // node launches, merged by index; big streaming nodes become tasks
-        B->task_first.push_back(0);
-        B->task_nk.push_back({0, 0, 0, 0, 0});
-        B->wave_off.push_back(0);
-        B->btask_off.push_back(0);
-        std::vector<int> tab;
-        for (size_t k = 1; k < kmax; ++k) {
-            Launch merged{LAUNCH_NODES, (int32_t)B->nodes.size(), 0, 0, 0};
-            std::vector<Launch> gemm_launches;
-            std::vector<NodeDesc> step_nodes;
-            for (int64_t j = 0; j < ni; ++j) {
-                const wmc_plan_t &P = *plans[iplan[(size_t)j]];
-                const size_t i = (size_t)j;  // instance: arena and meta base
-                if (k >= P.launches.size()) continue;
-                const Launch &L = P.launches[k];
-                if (L.type == LAUNCH_GEMM) {
-                    GemmDesc g = P.gemms[(size_t)L.pad];
-                    g.a += abase[(size_t)i];
-                    g.b += abase[(size_t)i];
-                    g.c += abase[(size_t)i];
-                    g.ta += (int)mbase[(size_t)i];
-                    g.tb += (int)mbase[(size_t)i];
-                    g.tc += (int)mbase[(size_t)i];
-                    gemm_launches.push_back({LAUNCH_GEMM, 0, 1, (int32_t)B->gemms.size(), 0});
-                    B->gemms.push_back(g);
-                    continue;
-                }
-                for (int32_t q = 0; q < L.count; ++q) {
-                    NodeDesc d = P.nodes[(size_t)(L.first + q)];
-                    d.a += abase[(size_t)i];
-                    d.b += abase[(size_t)i];
-                    d.c += abase[(size_t)i];
-                    d.ta += (int)mbase[(size_t)i];
-                    d.tb += (int)mbase[(size_t)i];
-                    d.tc += (int)mbase[(size_t)i];
-                    step_nodes.push_back(d);
-                }
-            }
-            std::vector<StreamTask> tasks;
-            std::vector<int> nkf;
-            int64_t work = 0;
-            split_stream(step_nodes, tasks, nkf, work, plans[0]->tune.multi_min_rank);
-            merged.count = (int32_t)step_nodes.size();
-            merged.work = work;
-            B->nodes.insert(B->nodes.end(), step_nodes.begin(), step_nodes.end());
-            if (merged.count || !tasks.empty()) {
-                B->launches.push_back(merged);
-                B->task_first.push_back((int)B->tasks.size());
-                B->task_nk.push_back({nkf[0], nkf[1], nkf[2], nkf[3], nkf[4]});
-                B->tasks.insert(B->tasks.end(), tasks.begin(), tasks.end());
-                B->wave_off.push_back((int64_t)B->tables.size());
-                wave_node_table(step_nodes, work, tab);
-                B->tables.insert(B->tables.end(), tab.begin(), tab.end());
-                B->btask_off.push_back((int64_t)B->tables.size());
-                block_task_table(tasks, nkf, tab);
-                B->tables.insert(B->tables.end(), tab.begin(), tab.end());
-            }
-            for (const Launch &g : gemm_launches) {
-                B->launches.push_back(g);
-                B->task_first.push_back((int)B->tasks.size());
-                B->task_nk.push_back({0, 0, 0, 0, 0});
-                B->wave_off.push_back(0);
-                B->btask_off.push_back(0);
-            }
-        }
-        for (int64_t j = 0; j < ni; ++j) {
-            const wmc_plan_t &P = *plans[iplan[(size_t)j]];
-            B->roots.push_back(P.root < 0 ? -1 : P.root + (int)mbase[(size_t)j]);
-            B->root_off.push_back(P.root < 0 ? 0 : (long long)(P.T[(size_t)P.root].off + abase[(size_t)j]));
-        }
-        // workspace layout
-        uint64_t off = 0;
-        B->off_res = off;
-        off += bal(sizeof(BatchRes) * (uint64_t)ni, 256);
-        B->off_w = off;
-        off += bal(sizeof(double) * 2 * (uint64_t)std::max<int64_t>(vars, 1), 256);
-        B->off_meta = off;
-        off += bal(sizeof(wmc_meta) * (uint64_t)B->meta_total, 256);
-        B->off_leaf = off;
-        off += bal(sizeof(LeafDesc) * std::max<size_t>(B->leaves.size(), 1), 256);
-        B->off_node = off;
-        off += bal(sizeof(NodeDesc) * std::max<size_t>(B->nodes.size(), 1), 256);
-        B->off_gemm = off;
-        off += bal(sizeof(GemmDesc) * std::max<size_t>(B->gemms.size(), 1), 256);
-        B->off_tasks = off;
-        off += bal(sizeof(StreamTask) * std::max<size_t>(B->tasks.size(), 1), 256);
-        B->off_roots = off;
-        off += bal(sizeof(int) * (uint64_t)ni, 256);
-        B->off_rootoff = off;
-        off += bal(sizeof(long long) * (uint64_t)ni, 256);
-        B->off_leaf_eta = off;
-        off += bal(sizeof(unsigned long long) * std::max<size_t>(B->leaf_eta.size(), 1), 256);
-        B->off_tables = off;
-        off += bal(sizeof(int) * std::max<size_t>(B->tables.size(), 1), 256);
-        B->desc_bytes = off - B->off_leaf;
-        fuse_batch(*B, plans, iplan, abase, mbase);
-        off = std::max(off, B->off_leaf + bal(B->fused.image.size(), 256));
-        B->off_arena = off;
-        B->arena_bytes = (uint64_t)arena_elems * (uint64_t)B->elem;
-        B->off_steps = off + bal(B->arena_bytes, 256);
-        // [barrier counter, flag][step arguments]
-        B->workspace_bytes = B->off_steps + 256 + bal(sizeof(StepArgs) * B->launches.size(), 256);
-        B->image.assign(B->desc_bytes, 0);
-        uint8_t *img = B->image.data();
-        auto put = [&](uint64_t o, const void *src, size_t bytes) {
-            if (bytes) std::memcpy(img + (o - B->off_leaf), src, bytes);
-        };
-        put(B->off_leaf, B->leaves.data(), sizeof(LeafDesc) * B->leaves.size());
-        put(B->off_node, B->nodes.data(), sizeof(NodeDesc) * B->nodes.size());
-        put(B->off_gemm, B->gemms.data(), sizeof(GemmDesc) * B->gemms.size());
-        put(B->off_tasks, B->tasks.data(), sizeof(StreamTask) * B->tasks.size());
-        put(B->off_roots, B->roots.data(), sizeof(int) * B->roots.size());
-        put(B->off_rootoff, B->root_off.data(), sizeof(long long) * B->root_off.size());
-        put(B->off_tables, B->tables.data(), sizeof(int) * B->tables.size());
-        put(B->off_leaf_eta, B->leaf_eta.data(), sizeof(unsigned long long) * B->leaf_eta.size());
-        *out = B;
+        bool any = false;
+        for (int64_t i = 0; i < n; ++i) any = any || plans[i]->fused.on;
+        std::unique_ptr<wmc_batch> B = make_batch(plans, n, any);
+        if (!B) B = make_batch(plans, n, false);
+        *out = B.release();
     } catch (std::bad_alloc &) {
         wmc_set_error("wmc_batch_create: host allocation failed");
         return WMC_ERR_OUT_OF_MEMORY;
@@ -514,8 +555,12 @@ static StepArgs step_args(const wmc_batch &B, char *ws, size_t k) {
     return a;
 }
 
+// The merged launch lists; with `live`, of the instances whose bytes of
+// B.live (host copy) and live (on the device) are set, the longest of which
+// has `most` launches.
 template <typename T>
-static void batch_launches(const wmc_batch &B, char *ws, hipStream_t st) {
+static void batch_launches(const wmc_batch &B, char *ws, hipStream_t st, const unsigned char *live = nullptr,
+                           int32_t most = INT32_MAX) {
     wmc_meta *meta = (wmc_meta *)(ws + B.off_meta);
     const double *w = (const double *)(ws + B.off_w);
     const LeafDesc *L = (const LeafDesc *)(ws + B.off_leaf);
@@ -524,19 +569,30 @@ static void batch_launches(const wmc_batch &B, char *ws, hipStream_t st) {
     const int nt = (int)B.meta_total;
     hipLaunchKernelGGL(k_begin, dim3((nt + WMC_BLOCK - 1) / WMC_BLOCK), dim3(WMC_BLOCK), 0, st, meta, nt,
                        (wmc_acc *)nullptr, 0);
-    if (!B.leaves.empty())
-        hipLaunchKernelGGL(k_leaves<T>, dim3(grid_for(B.leaf_work)), dim3(WMC_BLOCK), 0, st, L, (int)B.leaves.size(),
-                           (long long)B.leaf_work, w, arena, meta, SliceGroup{0, 0, 0}, 0ull,
-                           (const int *)(ws + B.off_tables) + B.leaf_tab_off,
-                           (const unsigned long long *)(ws + B.off_leaf_eta));
+    StepArgs a{};
+    if (!B.leaves.empty()) {
+        a.leaves = L;
+        a.wave_leaf = (const int *)(ws + B.off_tables) + B.leaf_tab_off;
+        a.leaf_eta = (const unsigned long long *)(ws + B.off_leaf_eta);
+        a.w = w;
+        a.leaf_work = (long long)B.leaf_work;
+        a.nleaves = (int)B.leaves.size();
+        a.lblocks = grid_for(B.leaf_work);
+        if (live) launch_step<T>(a, arena, meta, st, live);
+        else
+            hipLaunchKernelGGL(k_leaves<T>, dim3(a.lblocks), dim3(WMC_BLOCK), 0, st, L, a.nleaves, a.leaf_work, w, arena,
+                               meta, SliceGroup{0, 0, 0}, 0ull, a.wave_leaf, a.leaf_eta);
+    }
     for (size_t k = 1; k < B.launches.size(); ++k) {
         const Launch &Ln = B.launches[k];
+        if (B.launch_at[k] >= most) break;
         if (Ln.type == LAUNCH_GEMM) {
+            if (live && !B.live[(size_t)B.gemms[(size_t)Ln.pad].tc]) continue;
             launch_gemm<T>(B.gemms[(size_t)Ln.pad], G + Ln.pad, arena, meta, st, SliceGroup{0, 0, 0}, 1, B.gemm_shape);
             continue;
         }
         // the merged step's small nodes and streaming tasks in one launch
-        launch_step<T>(step_args(B, ws, k), arena, meta, st);
+        launch_step<T>(step_args(B, ws, k), arena, meta, st, live);
     }
     hipLaunchKernelGGL(k_finish_batch<T>, dim3((unsigned)((B.n_inst + 3) / 4)), dim3(4 * WMC_WAVE), 0, st, arena,
                        (const long long *)(ws + B.off_rootoff), (const int *)(ws + B.off_roots), meta, (int)B.n_inst,
@@ -547,7 +603,7 @@ template <typename T>
 static void batch_fused_launches(const wmc_batch &B, char *ws, hipStream_t st) {
     const BatchFused &F = B.fused;
     wmc_meta *meta = (wmc_meta *)(ws + B.off_meta);
-    char *img = ws + B.off_leaf;
+    char *img = ws + B.off_fused;
     T *arena = (T *)(ws + B.off_arena);
     const int *tabs = (const int *)(img + F.o_tables);
     const int nt = (int)B.meta_total;
@@ -695,60 +751,85 @@ extern "C" wmc_status wmc_batch_contract(wmc_batch *b, const double *weights, vo
     if (B.n_vars_total > 0)
         HIP_TRY(hipMemcpyAsync(ws + B.off_w, w, sizeof(double) * 2 * (size_t)B.n_vars_total, hipMemcpyHostToDevice, st));
     const bool persistent = (flags & WMC_BATCH_PERSISTENT) && B.gemms.empty() && B.launches.size() > 1;
+    const bool fused = B.fused.on && !persistent;  // the persistent form runs the launch lists
     std::vector<BatchRes> h((size_t)B.n_inst);
     unsigned gave_up = 0;
-    // the fused programs, and once more the launch lists if a chain left its
-    // range (the persistent form runs the launch lists)
-    for (bool fused = B.fused.on && !persistent;; fused = false) {
-        // the image goes up unless the caller says it is there already and
-        // this batch did put it into this workspace (a first call on a
-        // workspace always uploads, whatever the flags say)
-        if (!(flags & WMC_BATCH_RESIDENT) || B.image_ws != workspace || B.image_fused != fused) {
-            const std::vector<uint8_t> &img = fused ? B.fused.image : B.image;
-            HIP_TRY(hipMemcpyAsync(ws + B.off_leaf, img.data(), img.size(), hipMemcpyHostToDevice, st));
-            B.image_ws = workspace;
-            B.image_fused = fused;
+    // an image goes up unless the caller says it is there already and this
+    // batch did put it into this workspace (a first call on a workspace
+    // always uploads, whatever the flags say)
+    auto upload = [&](bool of_fused) -> wmc_status {
+        if ((flags & WMC_BATCH_RESIDENT) && B.image_ws[of_fused] == workspace) return WMC_OK;
+        const std::vector<uint8_t> &img = of_fused ? B.fused.image : B.image;
+        HIP_TRY(hipMemcpyAsync(ws + (of_fused ? B.off_fused : B.off_leaf), img.data(), img.size(), hipMemcpyHostToDevice,
+                               st));
+        B.image_ws[of_fused] = workspace;
+        return WMC_OK;
+    };
+    wmc_status us = upload(fused);
+    if (us != WMC_OK) return us;
+    auto launch = [&](hipStream_t to) {
+        if (B.precision == WMC_FP64) fused ? batch_fused_launches<double>(B, ws, to) : batch_launches<double>(B, ws, to);
+        else fused ? batch_fused_launches<float>(B, ws, to) : batch_launches<float>(B, ws, to);
+    };
+    if (persistent) {
+        const bool resident = (flags & WMC_BATCH_RESIDENT) != 0;
+        const wmc_status ps = B.precision == WMC_FP64 ? batch_persistent<double>(B, ws, st, resident)
+                                                      : batch_persistent<float>(B, ws, st, resident);
+        if (ps != WMC_OK) return ps;
+    } else if (flags & WMC_BATCH_GRAPH) {
+        if (B.exec && B.graph_ws != workspace) {
+            HIP_TRY(hipGraphExecDestroy(B.exec));
+            B.exec = nullptr;
         }
-        auto launch = [&](hipStream_t to) {
-            if (B.precision == WMC_FP64) fused ? batch_fused_launches<double>(B, ws, to) : batch_launches<double>(B, ws, to);
-            else fused ? batch_fused_launches<float>(B, ws, to) : batch_launches<float>(B, ws, to);
-        };
-        if (persistent) {
-            const bool resident = (flags & WMC_BATCH_RESIDENT) != 0;
-            const wmc_status ps = B.precision == WMC_FP64 ? batch_persistent<double>(B, ws, st, resident)
-                                                          : batch_persistent<float>(B, ws, st, resident);
-            if (ps != WMC_OK) return ps;
-        } else if ((flags & WMC_BATCH_GRAPH) && fused == B.fused.on) {
-            if (B.exec && B.graph_ws != workspace) {
-                HIP_TRY(hipGraphExecDestroy(B.exec));
+        if (!B.exec) {
+            if (!B.cap_stream) HIP_TRY(hipStreamCreateWithFlags(&B.cap_stream, hipStreamNonBlocking));
+            hipGraph_t graph = nullptr;
+            HIP_TRY(hipStreamBeginCapture(B.cap_stream, hipStreamCaptureModeThreadLocal));
+            launch(B.cap_stream);
+            HIP_TRY(hipStreamEndCapture(B.cap_stream, &graph));
+            hipError_t e = hipGraphInstantiate(&B.exec, graph, nullptr, nullptr, 0);
+            (void)hipGraphDestroy(graph);
+            if (e != hipSuccess) {
                 B.exec = nullptr;
+                wmc_set_error("hipGraphInstantiate failed: %s", hipGetErrorString(e));
+                return WMC_ERR_DEVICE;
             }
-            if (!B.exec) {
-                if (!B.cap_stream) HIP_TRY(hipStreamCreateWithFlags(&B.cap_stream, hipStreamNonBlocking));
-                hipGraph_t graph = nullptr;
-                HIP_TRY(hipStreamBeginCapture(B.cap_stream, hipStreamCaptureModeThreadLocal));
-                launch(B.cap_stream);
-                HIP_TRY(hipStreamEndCapture(B.cap_stream, &graph));
-                hipError_t e = hipGraphInstantiate(&B.exec, graph, nullptr, nullptr, 0);
-                (void)hipGraphDestroy(graph);
-                if (e != hipSuccess) {
-                    B.exec = nullptr;
-                    wmc_set_error("hipGraphInstantiate failed: %s", hipGetErrorString(e));
-                    return WMC_ERR_DEVICE;
-                }
-                B.graph_ws = workspace;
-            }
-            HIP_TRY(hipGraphLaunch(B.exec, st));
-        } else {
-            launch(st);
+            B.graph_ws = workspace;
         }
+        HIP_TRY(hipGraphLaunch(B.exec, st));
+    } else {
+        launch(st);
+    }
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(h.data(), ws + B.off_res, sizeof(BatchRes) * (size_t)B.n_inst, hipMemcpyDeviceToHost, st));
+    if (persistent) HIP_TRY(hipMemcpyAsync(&gave_up, ws + B.off_steps + 4, 4, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    // instances with a chain that left its range run their launch lists, the
+    // others keep their results
+    bool again = false;
+    int32_t most = 0;
+    if (fused) {
+        for (int64_t j = 0; j < B.n_inst; ++j) {
+            if (h[(size_t)j].e != WMC_BATCH_RERUN) continue;
+            if (!again) B.live.assign((size_t)B.meta_total, 0);
+            again = true;
+            most = std::max(most, B.inst_launches[(size_t)j]);
+            std::fill(B.live.begin() + B.meta_first[(size_t)j], B.live.begin() + B.meta_first[(size_t)j + 1], (uint8_t)1);
+        }
+    }
+    if (again) {
+        us = upload(false);
+        if (us != WMC_OK) return us;
+        HIP_TRY(hipMemcpyAsync(ws + B.off_live, B.live.data(), B.live.size(), hipMemcpyHostToDevice, st));
+        const unsigned char *live = (const unsigned char *)(ws + B.off_live);
+        if (B.precision == WMC_FP64) batch_launches<double>(B, ws, st, live, most);
+        else batch_launches<float>(B, ws, st, live, most);
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(h.data(), ws + B.off_res, sizeof(BatchRes) * (size_t)B.n_inst, hipMemcpyDeviceToHost, st));
-        if (persistent) HIP_TRY(hipMemcpyAsync(&gave_up, ws + B.off_steps + 4, 4, hipMemcpyDeviceToHost, st));
+        std::vector<BatchRes> g((size_t)B.n_inst);
+        HIP_TRY(hipMemcpyAsync(g.data(), ws + B.off_res, sizeof(BatchRes) * (size_t)B.n_inst, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
-        bool again = false;
-        for (const BatchRes &r : h) again = again || r.e == WMC_BATCH_RERUN;
-        if (!fused || !again) break;
+        for (int64_t j = 0; j < B.n_inst; ++j)
+            if (h[(size_t)j].e == WMC_BATCH_RERUN) h[(size_t)j] = g[(size_t)j];
     }
     if (gave_up) {
         wmc_set_error("wmc_batch_contract: a grid barrier of the persistent launch timed out");

@@ -196,12 +196,13 @@ __device__ __forceinline__ void leaf_item(DP d, long long e, const double *__res
 
 // The body takes its workgroup index and count, so that the fused step
 // kernel can run it on a share of its workgroups.
-template <typename T>
+template <typename T, bool SOME = false>
 __device__ __forceinline__ void leaves_body(const LeafDesc *__restrict__ L, int nl, long long work,
                                             const double *__restrict__ w, T *__restrict__ arena, wmc_meta *meta,
                                             unsigned long long eta, const int *__restrict__ wave_leaf,
                                             const unsigned long long *__restrict__ leaf_eta, unsigned blk,
-                                            unsigned nblk, unsigned width = 0, unsigned tid = 0) {
+                                            unsigned nblk, unsigned width = 0, unsigned tid = 0,
+                                            const unsigned char *__restrict__ live = nullptr) {
     // units of `width` threads (a workgroup by default, or one wave)
     const unsigned W = width ? width : blockDim.x, t = width ? tid : threadIdx.x;
     const long long stride = (long long)nblk * W;
@@ -217,6 +218,8 @@ __device__ __forceinline__ void leaves_body(const LeafDesc *__restrict__ L, int 
                 if (L[mid].work_begin <= g) lo = mid; else hi = mid - 1;
             }
         }
+        if constexpr (SOME)
+            if (!live[L[lo].tensor]) continue;
         // a batch of sliced plans gives every leaf the slice of its instance
         leaf_item<T>(L + lo, g - L[lo].work_begin, w, arena, meta, leaf_eta ? leaf_eta[lo] : eta);
     }
@@ -262,10 +265,11 @@ __device__ __forceinline__ void node_item(DP d, unsigned long long r, T *__restr
     if (r == 0) meta[d->tc].exp = meta[d->ta].exp + meta[d->tb].exp + sA + sB;
 }
 
-template <typename T>
+template <typename T, bool SOME = false>
 __device__ __forceinline__ void nodes_body(const NodeDesc *__restrict__ D, int nd, long long work,
                                            T *__restrict__ arena, wmc_meta *meta, const int *__restrict__ wave_node,
-                                           unsigned blk, unsigned nblk, unsigned width = 0, unsigned tid = 0) {
+                                           unsigned blk, unsigned nblk, unsigned width = 0, unsigned tid = 0,
+                                           const unsigned char *__restrict__ live = nullptr) {
     // units of `width` threads (a workgroup by default, or one wave)
     const unsigned W = width ? width : blockDim.x, t = width ? tid : threadIdx.x;
     const long long stride = (long long)nblk * W;
@@ -285,6 +289,8 @@ __device__ __forceinline__ void nodes_body(const NodeDesc *__restrict__ D, int n
             }
         }
         lo = __builtin_amdgcn_readfirstlane(lo);
+        if constexpr (SOME)
+            if (!live[D[lo].tc]) continue;
         node_item<T>(D + lo, (unsigned long long)(g - D[lo].work_begin), arena, meta);
     }
 }
@@ -1723,10 +1729,11 @@ static inline unsigned long long stream_task_blocks(const Stream2Args &a) {
     return (threads + STREAM2_MULTI_THREADS - 1) / STREAM2_MULTI_THREADS;
 }
 
-template <typename T, int NK, typename TP = const StreamTask *>
+template <typename T, int NK, bool SOME = false, typename TP = const StreamTask *>
 __device__ __forceinline__ void stream_multi_body(TP tasks, int ntasks,
                                                   T *__restrict__ arena, wmc_meta *meta,
-                                                  const int *__restrict__ block_task, unsigned blk) {
+                                                  const int *__restrict__ block_task, unsigned blk,
+                                                  const unsigned char *__restrict__ live = nullptr) {
     constexpr int K = 1 << NK;
     constexpr int KC = K < 4 ? K : 4;
     int lo = 0;
@@ -1741,6 +1748,8 @@ __device__ __forceinline__ void stream_multi_body(TP tasks, int ntasks,
     }
     lo = __builtin_amdgcn_readfirstlane(lo);
     const auto &args = tasks[lo].a;
+    if constexpr (SOME)
+        if (!live[args.tc]) return;  // the whole workgroup: it is one task's
     const unsigned long long lb = (unsigned long long)((long long)blk - tasks[lo].block_begin);
     const int sS = scale_exp(meta[args.ts].maxbits);
     const int sO = scale_exp(meta[args.to].maxbits);
@@ -1820,11 +1829,12 @@ struct StepArgs {
     unsigned lblocks;
 };
 
-// Workgroup bx of merged step a (every thread of the workgroup runs it).  A
-// macro rather than a function, so that both kernels keep the descriptor
-// reads on the scalar path: the compiler proves them unclobbered only in a
-// kernel's own body.
-#define WMC_STEP_BLOCK(T, a, bx, arena, meta)                                                                 \
+// Workgroup bx of merged step a (every thread of the workgroup runs it); with
+// SOME, only the work of tensors whose byte in live is set.  A macro rather
+// than a function, so that the kernels keep the descriptor reads on the
+// scalar path: the compiler proves them unclobbered only in a kernel's own
+// body.
+#define WMC_STEP_BLOCK(T, SOME, a, bx, arena, meta, live)                                                     \
     do {                                                                                                      \
         if ((bx) < (a).sblocks) {                                                                             \
             int k_ = 0;                                                                                       \
@@ -1834,23 +1844,32 @@ struct StepArgs {
             const int *bt_ = (a).block_task ? (a).block_task + (a).gblock[k_] : nullptr;                      \
             const unsigned blk_ = (bx) - (unsigned)(a).gblock[k_];                                            \
             switch (k_) {                                                                                     \
-            case 0: stream_multi_body<T, 0>(t_, nt_, arena, meta, bt_, blk_); break;                          \
-            case 1: stream_multi_body<T, 1>(t_, nt_, arena, meta, bt_, blk_); break;                          \
-            case 2: stream_multi_body<T, 2>(t_, nt_, arena, meta, bt_, blk_); break;                          \
-            default: stream_multi_body<T, 3>(t_, nt_, arena, meta, bt_, blk_); break;                         \
+            case 0: stream_multi_body<T, 0, SOME>(t_, nt_, arena, meta, bt_, blk_, live); break;              \
+            case 1: stream_multi_body<T, 1, SOME>(t_, nt_, arena, meta, bt_, blk_, live); break;              \
+            case 2: stream_multi_body<T, 2, SOME>(t_, nt_, arena, meta, bt_, blk_, live); break;              \
+            default: stream_multi_body<T, 3, SOME>(t_, nt_, arena, meta, bt_, blk_, live); break;             \
             }                                                                                                 \
         } else if ((bx) < (a).sblocks + (a).nblocks) {                                                        \
-            nodes_body<T>((a).nodes, (a).nnodes, (a).node_work, arena, meta, (a).wave_node, (bx) - (a).sblocks, \
-                          (a).nblocks);                                                                       \
+            nodes_body<T, SOME>((a).nodes, (a).nnodes, (a).node_work, arena, meta, (a).wave_node,             \
+                                (bx) - (a).sblocks, (a).nblocks, 0, 0, live);                                 \
         } else {                                                                                              \
-            leaves_body<T>((a).leaves, (a).nleaves, (a).leaf_work, (a).w, arena, meta, 0ull, (a).wave_leaf,   \
-                           (a).leaf_eta, (bx) - (a).sblocks - (a).nblocks, (a).lblocks);                      \
+            leaves_body<T, SOME>((a).leaves, (a).nleaves, (a).leaf_work, (a).w, arena, meta, 0ull,            \
+                                 (a).wave_leaf, (a).leaf_eta, (bx) - (a).sblocks - (a).nblocks, (a).lblocks, 0, 0, \
+                                 live);                                                                       \
         }                                                                                                     \
     } while (0)
 
 template <typename T>
 __global__ void __launch_bounds__(256) k_step(const StepArgs a, T *__restrict__ arena, wmc_meta *meta) {
-    WMC_STEP_BLOCK(T, a, blockIdx.x, arena, meta);
+    WMC_STEP_BLOCK(T, false, a, blockIdx.x, arena, meta, nullptr);
+}
+
+// The same for the instances of a batch that are run again: one byte per
+// tensor says whether its instance is.  The others' workgroups end at once.
+template <typename T>
+__global__ void __launch_bounds__(256) k_step_some(const StepArgs a, T *__restrict__ arena, wmc_meta *meta,
+                                                   const unsigned char *__restrict__ live) {
+    WMC_STEP_BLOCK(T, true, a, blockIdx.x, arena, meta, live);
 }
 
 // Grid-wide barrier number n (1, 2, ...) of a launch whose counter bar[0]
@@ -1896,7 +1915,7 @@ __global__ void __launch_bounds__(256) k_steps_persistent(const StepArgs *__rest
         const StepArgs &a = steps[k];
         const unsigned total = a.sblocks + a.nblocks + a.lblocks;
         for (unsigned bx = blockIdx.x; bx < total; bx += gridDim.x) {
-            WMC_STEP_BLOCK(T, a, bx, arena, meta);
+            WMC_STEP_BLOCK(T, false, a, bx, arena, meta, nullptr);
             __syncthreads();  // the block's max reduction reuses its LDS slots
         }
         grid_barrier(bar, (unsigned)k + 1, wait_ticks);
@@ -1976,9 +1995,12 @@ static inline void step_stream_part(StepArgs &a, const StreamTask *dev_tasks, co
 }
 
 template <typename T>
-static void launch_step(const StepArgs &a, T *arena, wmc_meta *meta, hipStream_t st) {
+static void launch_step(const StepArgs &a, T *arena, wmc_meta *meta, hipStream_t st,
+                        const unsigned char *live = nullptr) {
     const unsigned g = a.sblocks + a.nblocks + a.lblocks;
-    if (g) hipLaunchKernelGGL(k_step<T>, dim3(g), dim3(256), 0, st, a, arena, meta);
+    if (!g) return;
+    if (live) hipLaunchKernelGGL(k_step_some<T>, dim3(g), dim3(256), 0, st, a, arena, meta, live);
+    else hipLaunchKernelGGL(k_step<T>, dim3(g), dim3(256), 0, st, a, arena, meta);
 }
 
 // Split a merged node list into (generic nodes, streaming tasks grouped by

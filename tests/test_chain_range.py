@@ -320,3 +320,24 @@ def test_out_of_range_batches_and_servers(precision):
     assert sorted(r.request_id for r in done) == list(range(15))
     for r in done:
         assert same(r.value, *refs[r.request_id % 5], tolerance(plans[r.request_id % 5])), r.request_id
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_out_of_range_batch_with_matrix_nodes(precision):
+    """Instances with matrix nodes, some of which run again: each has what
+    its plan's launch list gives alone, the others what they give alone."""
+    f = wl.banded_3cnf(80, 280, 18, seed=2)
+    small = 1e-60 if precision == "fp64" else 1e-9
+    rng = np.random.default_rng(4)
+    fs = [f, f.with_weights(rng.uniform(0.1, 0.9, (f.n, 2)) * [1.0, small]), out_of_range(precision),
+          f.with_weights(rng.uniform(0.1, 0.9, (f.n, 2)))]
+    plans = [W.Plan(W.Network.from_formula(g), seed=0, precision=precision, block=1 if q == 2 else 4)
+             for q, g in enumerate(fs)]
+    assert plans[0].image()[1]["n_gemms"] > 0 and plans[0].program()[1]["n_chains"] > 0
+    lists = [W.wmc_contract_profile(p)[0] for p in plans]
+    b = W.Batch(plans)
+    ws = b.workspace()
+    for flags in (0, W.BATCH_GRAPH | W.BATCH_RESIDENT, W.BATCH_GRAPH | W.BATCH_RESIDENT):
+        for q, (v, p, g) in enumerate(zip(b.contract(ws=ws, flags=flags), plans, lists)):
+            assert same(v, g.mantissa, g.exp2, tolerance(p)), (q, flags)
