@@ -118,7 +118,7 @@ static void general_launches(const wmc_plan_t &P, char *ws, T *arena, wmc_meta *
 // Launches of the fused program on one slice group.
 template <typename T>
 static void fused_launches(const wmc_plan_t &P, char *ws, T *arena, wmc_meta *meta, hipStream_t st,
-                           const SliceGroup sg, unsigned nz, LaunchTimer *tm) {
+                           const SliceGroup sg, unsigned nz) {
     const FusedProgram &F = P.fused;
     char *img = ws + P.off_leaf;
     const NodeDesc *D = (const NodeDesc *)(img + F.o_node);
@@ -147,48 +147,53 @@ static void fused_launches(const wmc_plan_t &P, char *ws, T *arena, wmc_meta *me
             if (Ln.type == FUSED_CHAIN) launch_chain_big<T>(a, Ln.lds, arena, meta, st, sg, nz);
             else launch_fused_step<T, WMC_CHAIN_LANE>(a, Ln.lds, arena, meta, st, sg, nz);
         }
-        if (tm) tm->mark();
     }
 }
 
+// Launches of one slice group up to its roots' values: slices eta ... eta +
+// nz - 1 side by side (grid dimension z).
 template <typename T>
-static wmc_status run_slices(const wmc_plan_t &P, char *ws, hipStream_t st, long long b, long long e,
-                             wmc_value *per_slice, bool fused, LaunchTimer *tm = nullptr, bool keep_sum = false) {
+static void group_launches(const wmc_plan_t &P, char *ws, hipStream_t st, long long eta, unsigned nz, bool fused,
+                           bool reset, LaunchTimer *tm = nullptr) {
     const FusedProgram &F = P.fused;
     wmc_meta *meta = (wmc_meta *)(ws + P.off_meta);
-    wmc_acc *acc = (wmc_acc *)(ws + P.off_acc);
-    const double *w = (const double *)(ws + P.off_w);
     char *img = ws + P.off_leaf;
     const LeafDesc *L = (const LeafDesc *)(fused ? img + F.o_leaf : img);
     const int *TB = (const int *)(fused ? img + F.o_tab : ws + P.off_tab);
     const int64_t leaf_tab = fused ? F.leaf_tab : P.leaf_tab;
     T *arena = (T *)(ws + P.off_arena);
-    const int nt = (int)P.T.size();
-    const int nmasks = fused ? (int)F.masks.size() : 0;
-    const long long root_off = fused ? (long long)F.off[(size_t)P.root] : (long long)P.T[(size_t)P.root].off;
-    // slices run in groups of up to P.group, side by side in every launch
-    // (grid dimension z); per-slice results need one slice at a time
-    const long long G = per_slice ? 1 : (long long)P.group;
     const SliceGroup sg{(long long)(P.arena_stride / sizeof(T)), (int)P.meta_stride, 0};
+    const long long nmeta = (long long)(nz - 1) * P.meta_stride + (long long)P.T.size();
+    hipLaunchKernelGGL(k_begin, dim3((unsigned)((nmeta + WMC_BLOCK - 1) / WMC_BLOCK)), dim3(WMC_BLOCK), 0, st, meta,
+                       (int)nmeta, (wmc_acc *)(ws + P.off_acc), reset ? 1 : 0);
+    if (tm) tm->mark();
+    if (!P.leaves.empty())
+        hipLaunchKernelGGL(k_leaves<T>, dim3(grid_for(P.leaf_work), 1, nz), dim3(WMC_BLOCK), 0, st, L,
+                           (int)P.leaves.size(), (long long)P.leaf_work, (const double *)(ws + P.off_w), arena, meta, sg,
+                           (unsigned long long)eta, leaf_tab >= 0 ? TB + leaf_tab : nullptr);
+    if (tm) tm->mark();
+    if (fused) fused_launches<T>(P, ws, arena, meta, st, sg, nz);
+    else general_launches<T>(P, ws, arena, meta, st, sg, nz, tm);
+}
+
+// Slices [b, e) on the general launch list.
+template <typename T>
+static wmc_status run_slices(const wmc_plan_t &P, char *ws, hipStream_t st, long long b, long long e,
+                             wmc_value *per_slice, LaunchTimer *tm, bool keep_sum) {
+    wmc_acc *acc = (wmc_acc *)(ws + P.off_acc);
+    // slices run in groups of up to P.group, side by side in every launch;
+    // per-slice results need one slice at a time
+    const long long G = per_slice ? 1 : (long long)P.group;
     for (long long eta = b; eta < e; eta += G) {
         const unsigned nz = (unsigned)std::min<long long>(G, e - eta);
         if (tm) {
             tm->k = 0;
             tm->mark();
         }
-        const long long nmeta = (long long)(nz - 1) * P.meta_stride + nt;
-        hipLaunchKernelGGL(k_begin, dim3((unsigned)((nmeta + WMC_BLOCK - 1) / WMC_BLOCK)), dim3(WMC_BLOCK), 0, st, meta,
-                           (int)nmeta, acc, eta == b && !keep_sum ? 1 : 0);
-        if (tm) tm->mark();
-        if (!P.leaves.empty())
-            hipLaunchKernelGGL(k_leaves<T>, dim3(grid_for(P.leaf_work), 1, nz), dim3(WMC_BLOCK), 0, st, L,
-                               (int)P.leaves.size(), (long long)P.leaf_work, w, arena, meta, sg,
-                               (unsigned long long)eta, leaf_tab >= 0 ? TB + leaf_tab : nullptr);
-        if (tm) tm->mark();
-        if (fused) fused_launches<T>(P, ws, arena, meta, st, sg, nz, tm);
-        else general_launches<T>(P, ws, arena, meta, st, sg, nz, tm);
-        hipLaunchKernelGGL(k_finish<T>, dim3(1), dim3(nmasks ? WMC_BLOCK : 1), 0, st, arena, root_off, meta, P.root, acc,
-                           (int)nz, sg.astride, sg.mstride, (const int *)(img + F.o_masks), nmasks);
+        group_launches<T>(P, ws, st, eta, nz, false, eta == b && !keep_sum, tm);
+        hipLaunchKernelGGL(k_finish<T>, dim3(1), dim3(1), 0, st, (const T *)(ws + P.off_arena),
+                           (long long)P.T[(size_t)P.root].off, (const wmc_meta *)(ws + P.off_meta), P.root, acc, (int)nz,
+                           (long long)(P.arena_stride / sizeof(T)), (int)P.meta_stride);
         if (tm) tm->mark();
         HIP_TRY(hipGetLastError());
         if (tm) {
@@ -209,26 +214,87 @@ static wmc_status run_slices(const wmc_plan_t &P, char *ws, hipStream_t st, long
     return WMC_OK;
 }
 
+// Slices [b, e), at most P.log_slices, on the fused program, and once more on
+// the launch list the groups with a slice whose chains left their range: *h is
+// the sum after them.  *resident: whether the program's image is in ws.
+template <typename T>
+static wmc_status run_window(const wmc_plan_t &P, char *ws, hipStream_t st, long long b, long long e,
+                             wmc_value *per_slice, bool keep_sum, bool *resident, wmc_acc *h) {
+    const FusedProgram &F = P.fused;
+    const T *arena = (const T *)(ws + P.off_arena);
+    const wmc_meta *meta = (const wmc_meta *)(ws + P.off_meta);
+    wmc_acc *acc = (wmc_acc *)(ws + P.off_acc);
+    SliceVal *log = (SliceVal *)(ws + P.off_log);
+    const long long astride = (long long)(P.arena_stride / sizeof(T)), n = e - b;
+    const int mstride = (int)P.meta_stride;
+    if (!*resident)
+        HIP_TRY(hipMemcpyAsync(ws + P.off_leaf, F.image.data(), F.image.size(), hipMemcpyHostToDevice, st));
+    *resident = true;
+    for (long long eta = b; eta < e; eta += P.group) {
+        const unsigned nz = (unsigned)std::min<long long>(P.group, e - eta);
+        group_launches<T>(P, ws, st, eta, nz, true, eta == b && !keep_sum);
+        hipLaunchKernelGGL(k_finish_fused<T>, dim3(1), dim3(nz > 1 ? WMC_BLOCK : WMC_WAVE), 0, st, arena, (long long)F.off[(size_t)P.root],
+                           meta, P.root, acc, (int)nz, astride, mstride, (const int *)(ws + P.off_leaf + F.o_masks),
+                           (int)F.masks.size(), log + (eta - b));
+        HIP_TRY(hipGetLastError());
+    }
+    HIP_TRY(hipMemcpyAsync(h, acc, sizeof *h, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (!h->pad[0] && !per_slice) return WMC_OK;
+    std::vector<SliceVal> v((size_t)n);
+    HIP_TRY(hipMemcpyAsync(v.data(), log, sizeof(SliceVal) * (size_t)n, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (h->pad[0]) {
+        long long first = n;
+        HIP_TRY(hipMemcpyAsync(ws + P.off_leaf, P.desc_image.data(), P.desc_bytes, hipMemcpyHostToDevice, st));
+        *resident = false;
+        for (long long q = 0; q < n; q += P.group) {
+            const unsigned nz = (unsigned)std::min<long long>(P.group, n - q);
+            long long z = q;
+            while (z < q + nz && v[(size_t)z].e != WMC_SLICE_OUT) ++z;
+            if (z == q + nz) continue;
+            first = std::min(first, z);
+            group_launches<T>(P, ws, st, b + q, nz, false, false);
+            hipLaunchKernelGGL(k_relog<T>, dim3((nz + 63) / 64), dim3(64), 0, st, arena,
+                               (long long)P.T[(size_t)P.root].off, meta, P.root, (int)nz, astride, mstride, log + q);
+        }
+        hipLaunchKernelGGL(k_fold, dim3(1), dim3(1), 0, st, acc, log + first, (int)(n - first));
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(hipMemcpyAsync(h, acc, sizeof *h, hipMemcpyDeviceToHost, st));
+        if (per_slice)
+            HIP_TRY(hipMemcpyAsync(v.data(), log, sizeof(SliceVal) * (size_t)n, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+    }
+    for (long long q = 0; per_slice && q < n; ++q) per_slice[q] = make_value(v[(size_t)q].m, v[(size_t)q].e);
+    return WMC_OK;
+}
+
 // Slices [b, e) with the weights and the running sum *init (null: zero),
-// into *h: on the fused program, and once more on the general launch list if
-// one of its chains left its range.
+// into *h.
 static wmc_status contract_range(const wmc_plan_t &P, const double *weights, char *ws, hipStream_t st, long long b,
                                  long long e, wmc_value *per_slice, const wmc_acc *init, wmc_acc *h,
                                  LaunchTimer *tm = nullptr) {
-    // a profile times the launch list it reports, node by node
-    for (bool fused = P.fused.on && !tm;; fused = false) {
-        HIP_TRY(upload_weights(P, weights, ws, st));
-        const std::vector<uint8_t> &img = fused ? P.fused.image : P.desc_image;
-        HIP_TRY(hipMemcpyAsync(ws + P.off_leaf, img.data(), img.size(), hipMemcpyHostToDevice, st));
-        if (init) HIP_TRY(hipMemcpyAsync(ws + P.off_acc, init, sizeof *init, hipMemcpyHostToDevice, st));
-        const wmc_status s = P.precision == WMC_FP64
-                                 ? run_slices<double>(P, ws, st, b, e, per_slice, fused, tm, init != nullptr)
-                                 : run_slices<float>(P, ws, st, b, e, per_slice, fused, tm, init != nullptr);
-        if (s != WMC_OK) return s;
-        HIP_TRY(hipMemcpyAsync(h, ws + P.off_acc, sizeof *h, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        if (!fused || !h->pad[0]) return WMC_OK;
+    HIP_TRY(upload_weights(P, weights, ws, st));
+    if (init) HIP_TRY(hipMemcpyAsync(ws + P.off_acc, init, sizeof *init, hipMemcpyHostToDevice, st));
+    if (P.fused.on && !tm) {  // a profile times the launch list it reports, node by node
+        bool resident = false;
+        for (long long q = b; q < e; q += P.log_slices) {
+            const long long end = std::min<long long>(e, q + P.log_slices);
+            const bool keep = init || q > b;
+            wmc_value *out = per_slice ? per_slice + (q - b) : nullptr;
+            const wmc_status s = P.precision == WMC_FP64 ? run_window<double>(P, ws, st, q, end, out, keep, &resident, h)
+                                                         : run_window<float>(P, ws, st, q, end, out, keep, &resident, h);
+            if (s != WMC_OK) return s;
+        }
+        return WMC_OK;
     }
+    HIP_TRY(hipMemcpyAsync(ws + P.off_leaf, P.desc_image.data(), P.desc_bytes, hipMemcpyHostToDevice, st));
+    const wmc_status s = P.precision == WMC_FP64 ? run_slices<double>(P, ws, st, b, e, per_slice, tm, init != nullptr)
+                                                 : run_slices<float>(P, ws, st, b, e, per_slice, tm, init != nullptr);
+    if (s != WMC_OK) return s;
+    HIP_TRY(hipMemcpyAsync(h, ws + P.off_acc, sizeof *h, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    return WMC_OK;
 }
 
 extern "C" wmc_status wmc_contract_slices(const wmc_plan_t *plan, const double *weights, void *workspace,

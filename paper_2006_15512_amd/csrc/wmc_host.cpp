@@ -1403,7 +1403,12 @@ static wmc_status finalize_plan(const wmc_network &net, const wmc_plan_options &
     // that fits the static scratch keeps fitting it
     wmc_fuse(P, o.mem_cap_bytes ? P.arena_bytes : P.arena_bytes + P.arena_bytes / 2);
     if (P.fused.on) {
-        const uint64_t arena = std::max(P.off_arena, P.off_leaf + P.fused.image.size());
+        // a call looks for slices out of range once per log of them; 1024
+        // slices take long enough that the look is nothing (5 ms and more)
+        P.log_slices = std::min<int64_t>((int64_t)1 << P.sliced.size(),
+                                         std::max<int64_t>(P.group, 1024 / P.group * (int64_t)P.group));
+        P.off_log = std::max(P.off_arena, align_up(P.off_leaf + P.fused.image.size(), 256));
+        const uint64_t arena = P.off_log + align_up(16 * (uint64_t)P.log_slices, 256);
         const uint64_t stride = align_up(std::max(P.arena_bytes, P.fused.arena_bytes), 256);
         const uint64_t bytes = arena + (uint64_t)P.group * stride;
         if (P.workspace_bytes <= WMC_NOALLOC_SCRATCH_BYTES && bytes > WMC_NOALLOC_SCRATCH_BYTES) {

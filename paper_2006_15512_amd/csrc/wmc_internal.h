@@ -148,6 +148,10 @@ struct wmc_plan_t {
     int64_t meta_stride = 0;     // wmc_meta entries
     wmc_plan_info info{};
     FusedProgram fused;
+    // with a fused program: values of up to log_slices slices (SliceVal),
+    // whole groups of them
+    uint64_t off_log = 0;
+    int64_t log_slices = 0;
 };
 
 // Static placement of intervals [birth, death] of `elems` entries each,

@@ -2037,13 +2037,6 @@ static inline void split_stream(std::vector<NodeDesc> &generic, std::vector<Stre
     nk_first[4] = (int)tasks.size();
 }
 
-// Roots of nz consecutive slices (slice z's arena and meta table astride
-// elements and mstride entries after slice z-1's): fold each value, in
-// slice order, into the running sum (s + c) * 2^e.
-template <typename T>
-__device__ void finish_one(const T *__restrict__ arena, long long root_off, const wmc_meta *meta, int root,
-                           wmc_acc *acc);
-
 // True if a chain's range bits (two per stage: an ordinary entry, a nonzero
 // entry) name a stage whose intermediate was nonzero but nowhere ordinary.
 __device__ __forceinline__ bool chain_out_of_range(unsigned long long mask) {
@@ -2051,33 +2044,103 @@ __device__ __forceinline__ bool chain_out_of_range(unsigned long long mask) {
     return (((m >> 1) & ~m) & 0x55555555u) != 0u;
 }
 
-template <typename T>
-__global__ void k_finish(const T *__restrict__ arena, long long root_off, const wmc_meta *meta, int root,
-                         wmc_acc *acc, int nz, long long astride, int mstride, const int *__restrict__ masks = nullptr,
-                         int nmasks = 0) {
-    if (blockIdx.x != 0) return;
-    // chains of the fused program: one out of range marks the whole sum
-    bool bad = false;
-    for (int i = (int)threadIdx.x; i < nmasks * nz; i += (int)blockDim.x)
-        bad |= chain_out_of_range(meta[(long long)(i / nmasks) * mstride + masks[i % nmasks]].maxbits);
-    if (bad) acc->pad[0] = 1;
-    if (threadIdx.x != 0) return;
-    for (int z = 0; z < nz; ++z)
-        finish_one<T>(arena + (long long)z * astride, root_off, meta + (long long)z * mstride, root, acc);
+// A slice's value m * 2^e (m = 0: e = 0; e = WMC_SLICE_OUT: one of its chains
+// left its range).
+struct SliceVal {
+    double m;
+    long long e;
+};
+static_assert(sizeof(SliceVal) == 16, "the planner lays out 16 bytes per logged slice");
+#define WMC_SLICE_OUT (-0x7fffffffffffffffll)
+
+__device__ __forceinline__ SliceVal slice_value(double m, long long e) {
+    SliceVal x{m, e};
+    if (x.m != 0.0) {
+        int k;
+        x.m = frexp(x.m, &k);
+        x.e += k;
+    } else {
+        x.e = 0;
+    }
+    return x;
 }
 
 template <typename T>
-__device__ void finish_one(const T *__restrict__ arena, long long root_off, const wmc_meta *meta, int root,
-                           wmc_acc *acc) {
-    double v = (double)arena[root_off];
-    long long e = meta[root].exp;
-    if (v != 0.0) {
-        int k;
-        v = frexp(v, &k);
-        e += k;
-    } else {
-        e = 0;
+__device__ __forceinline__ SliceVal root_value(const T *__restrict__ arena, long long root_off, const wmc_meta *meta,
+                                               int root) {
+    return slice_value((double)arena[root_off], meta[root].exp);
+}
+
+__device__ inline void fold_value(wmc_acc *acc, const SliceVal x);
+
+// Roots of nz consecutive slices (slice z's arena and meta table astride
+// elements and mstride entries after slice z-1's): fold each value, in
+// slice order, into the running sum (s + c) * 2^e.
+template <typename T>
+__global__ void k_finish(const T *__restrict__ arena, long long root_off, const wmc_meta *meta, int root,
+                         wmc_acc *acc, int nz, long long astride, int mstride) {
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    for (int z = 0; z < nz; ++z)
+        fold_value(acc, root_value(arena + (long long)z * astride, root_off, meta + (long long)z * mstride, root));
+}
+
+// The same after a fused program: one workgroup, a wave per slice looks at
+// the slice's chains (meta entries masks[0 .. nmasks)) and writes its value to
+// log[z].  From the first slice out of range on, nothing is added to the sum
+// (acc->pad[0] says so; k_fold goes on from there).  Bound by the latency of
+// its dependent loads, so those that depend on nothing go first.
+template <typename T>
+__global__ void __launch_bounds__(WMC_BLOCK) k_finish_fused(const T *__restrict__ arena, long long root_off,
+                                                            const wmc_meta *meta, int root, wmc_acc *acc, int nz,
+                                                            long long astride, int mstride,
+                                                            const int *__restrict__ masks, int nmasks, SliceVal *log) {
+    const int lane = (int)(threadIdx.x % WMC_WAVE);
+    wmc_acc sum = *acc;
+    SliceVal own{0.0, 0};  // thread 0: the first slice's
+    for (int z = (int)(threadIdx.x / WMC_WAVE); z < nz; z += (int)(blockDim.x / WMC_WAVE)) {
+        const wmc_meta *m = meta + (long long)z * mstride;
+        const double rm = (double)arena[(long long)z * astride + root_off];
+        const long long re = m[root].exp;
+        bool bad = false;
+        for (int q = lane; q < nmasks; q += WMC_WAVE) bad |= chain_out_of_range(m[masks[q]].maxbits);
+        bad = __any(bad);
+        if (lane == 0) {
+            SliceVal x = slice_value(rm, re);
+            if (bad) x.e = WMC_SLICE_OUT;
+            log[z] = x;
+            if (z == 0) own = x;
+        }
     }
+    if (nz > 1) __syncthreads();
+    if (threadIdx.x != 0 || sum.pad[0]) return;
+    for (int z = 0; z < nz && !sum.pad[0]; ++z) {
+        const SliceVal x = z ? log[z] : own;
+        if (x.e == WMC_SLICE_OUT) sum.pad[0] = 1;
+        else fold_value(&sum, x);
+    }
+    *acc = sum;
+}
+
+// Slices that ran again on the launch list: their values take the place of
+// those out of range.
+template <typename T>
+__global__ void k_relog(const T *__restrict__ arena, long long root_off, const wmc_meta *meta, int root, int nz,
+                        long long astride, int mstride, SliceVal *log) {
+    const int z = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (z < nz && log[z].e == WMC_SLICE_OUT)
+        log[z] = root_value(arena + (long long)z * astride, root_off, meta + (long long)z * mstride, root);
+}
+
+// Adds the logged values that k_finish_fused left out.
+static __global__ __attribute__((unused)) void k_fold(wmc_acc *acc, const SliceVal *log, int n) {
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    for (int z = 0; z < n; ++z) fold_value(acc, log[z]);
+    acc->pad[0] = 0;
+}
+
+__device__ inline void fold_value(wmc_acc *acc, const SliceVal x) {
+    const double v = x.m;
+    const long long e = x.e;
     acc->last_m = v;
     acc->last_e = e;
     if (v == 0.0) return;

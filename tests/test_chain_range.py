@@ -341,3 +341,28 @@ def test_out_of_range_batch_with_matrix_nodes(precision):
     for flags in (0, W.BATCH_GRAPH | W.BATCH_RESIDENT, W.BATCH_GRAPH | W.BATCH_RESIDENT):
         for q, (v, p, g) in enumerate(zip(b.contract(ws=ws, flags=flags), plans, lists)):
             assert same(v, g.mantissa, g.exp2, tolerance(p)), (q, flags)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_many_slices_out_of_range(precision):
+    """8192 slices, about half of them out of range, looked at 1024 and (in
+    groups of 3) 1023 at a time: the values and sums do not depend on how the
+    slices are grouped or on where a range begins."""
+    first = None
+    f, _ = sliced_out_of_range(precision)
+    for group in (8, 3):
+        p = W.Plan(W.Network.from_formula(f), seed=0, precision=precision, rank_cap=7, slice_group=group)
+        assert p.n_slices == 8192 and p.program()[1]["n_launches"] > 0
+        ws = W.workspace(p)
+        total, per = W.wmc_contract_slices(p, 0, 8192, ws=ws, per_slice=True)
+        assert same(total, *oracle.bucket(f), tolerance(p))
+        assert total == W.wmc_contract(p, ws=ws) and total == W.wmc_contract(p, ws=ws)
+        part, some = W.wmc_contract_slices(p, 1000, 2100, ws=ws, per_slice=True)
+        assert some == per[1000:2100] and part == W.wmc_contract_slices(p, 1000, 2100, ws=ws)
+        state = W.wmc_slice_state()
+        for count in (1, 1500, 1000, 6000):
+            v = W.wmc_contract_resume(p, state, count, ws=ws)
+        assert v == total
+        first = first or (total, per)
+        assert (total, per) == first
