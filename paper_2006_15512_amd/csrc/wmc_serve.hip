@@ -300,6 +300,7 @@ struct wmc_server {
     std::vector<SStruct> S;
     std::deque<SReq> queue;
     std::vector<SReq> active;
+    std::deque<SReq> again;                      // to run again, in their slots and regions, once staging allows
     std::vector<int32_t> free_slots;
     std::map<uint64_t, uint64_t> free_regions;  // offset -> size
     uint64_t used_bytes = 0, peak_used = 0, structure_bytes = 0;
@@ -727,11 +728,14 @@ extern "C" wmc_status wmc_serve_cancel(wmc_server *v, uint64_t request_id) {
         }
         ++it;
     }
-    for (SReq &r : v->active)
+    auto mark = [&](SReq &r) {
         if (r.id == request_id && !r.cancelled) {
             r.cancelled = true;  // released once no step in flight can touch its region
             found = true;
         }
+    };
+    for (SReq &r : v->active) mark(r);
+    for (SReq &r : v->again) mark(r);
     if (found) return WMC_OK;
     wmc_set_error("wmc_serve_cancel: request %llu is not queued or running", (unsigned long long)request_id);
     return WMC_ERR_INVALID_ARGUMENT;
@@ -759,7 +763,7 @@ static wmc_status serve_collect(wmc_server *v) {
             // same slot and region
             r.k = 0;
             r.prog = s.prog.size() - 1;
-            v->active.push_back(std::move(r));
+            v->again.push_back(std::move(r));
             continue;
         }
         if (s.root < 0) complete(v, r, true, 0.5, 1);  // the empty product: 1
@@ -799,11 +803,22 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
             ++it;
         }
     }
-    for (SReq &r : v->active)
+    auto expire = [&](SReq &r) {
         if (r.deadline > 0.0 && tnow > r.deadline) r.cancelled = true;
+    };
+    for (SReq &r : v->active) expire(r);
+    for (SReq &r : v->again) expire(r);
     uint64_t stage_need = 0;
     for (const SReq &r : v->active) stage_need += v->S[(size_t)r.s].max_step_bytes;
-    while (!v->queue.empty() && !v->free_slots.empty()) {
+    // requests to run again hold a slot and a region already
+    while (!v->again.empty()) {
+        const uint64_t need = v->S[(size_t)v->again.front().s].max_step_bytes;
+        if (stage_need + need > v->step_cap) break;
+        stage_need += need;
+        v->active.push_back(std::move(v->again.front()));
+        v->again.pop_front();
+    }
+    while (v->again.empty() && !v->queue.empty() && !v->free_slots.empty()) {
         SReq &r = v->queue.front();
         const SStruct &s = v->S[(size_t)r.s];
         if (stage_need + s.max_step_bytes > v->step_cap) break;
@@ -1010,7 +1025,7 @@ extern "C" wmc_status wmc_serve_step(wmc_server *v, int32_t *n_active, int32_t *
     }
     wmc_status s = v->elem == 8 ? serve_step_t<double>(v) : serve_step_t<float>(v);
     // requests whose last launch is still in flight count as active
-    if (n_active) *n_active = (int32_t)(v->active.size() + v->finishing.size());
+    if (n_active) *n_active = (int32_t)(v->active.size() + v->again.size() + v->finishing.size());
     if (n_queued) *n_queued = (int32_t)v->queue.size();
     return s;
 }
@@ -1034,7 +1049,8 @@ extern "C" wmc_status wmc_serve_wait(wmc_server *v, wmc_response *out, int32_t m
         return WMC_ERR_INVALID_ARGUMENT;
     }
     const double t_end = v->now() + (double)std::max<int64_t>(timeout_us, 0) * 1e-6;
-    while (v->done.empty() && (!v->active.empty() || !v->queue.empty() || v->inflight) && v->now() < t_end) {
+    while (v->done.empty() && (!v->active.empty() || !v->again.empty() || !v->queue.empty() || v->inflight) &&
+           v->now() < t_end) {
         const wmc_status st = wmc_serve_step(v, nullptr, nullptr);
         if (st != WMC_OK) return st;
     }
@@ -1052,7 +1068,7 @@ extern "C" wmc_status wmc_serve_stats(const wmc_server *v, wmc_serve_info *out) 
     out->peak_used_bytes = v->peak_used;
     out->peak_active = v->peak_active;
     out->steps = v->steps;
-    out->n_active = (int64_t)(v->active.size() + v->finishing.size());
+    out->n_active = (int64_t)(v->active.size() + v->again.size() + v->finishing.size());
     out->n_queued = (int64_t)v->queue.size();
     out->n_structures = (int64_t)v->S.size();
     return WMC_OK;
@@ -1083,7 +1099,7 @@ extern "C" wmc_status wmc_serve(wmc_server *v, const wmc_request *trace, int64_t
             if (s != WMC_OK) return s;
             ++next;
         }
-        if (v->active.empty() && v->queue.empty() && !v->inflight) {
+        if (v->active.empty() && v->again.empty() && v->queue.empty() && !v->inflight) {
             if (next < n) {
                 // idle until the next arrival
                 while (v->now() < trace[next].t_arrive) {

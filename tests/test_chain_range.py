@@ -366,3 +366,36 @@ def test_many_slices_out_of_range(precision):
         assert v == total
         first = first or (total, per)
         assert (total, per) == first
+
+
+def crowded():
+    """A lattice whose chains report an intermediate out of range."""
+    f = wl.grid_cnf(8, 14, 0.2, seed=2)
+    return f.with_weights(np.random.default_rng(0).uniform(0.1, 0.9, (f.n, 2)) * [1.0, 1e-12])
+
+
+def test_crowded_lattice_runs_again():
+    f = crowded()
+    p, w = W.Plan(W.Network.from_formula(f), seed=0, precision="fp32"), f.weights.reshape(-1)
+    assert ranged(p, w)[2] and listed_off_by(p, w, *oracle.bucket(f)) <= tolerance(p)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("step_kib", [80, 96, 160, 320])
+def test_requests_that_run_again_fit_the_staging(step_kib):
+    """Many requests at once that run again, where the staging of a step
+    bounds how many run side by side."""
+    fs = [crowded(), wl.grid_cnf(8, 14, 0.2, seed=3)]
+    plans = [W.Plan(W.Network.from_formula(f), seed=0, precision="fp32") for f in fs]
+    refs = [oracle.bucket(f) for f in fs]
+    srv = W.Server(precision="fp32", max_slots=64, hbm_budget_bytes=1 << 28, buffer_bytes=1 << 29,
+                   step_bytes=step_kib << 10)
+    ids = [srv.register(p) for p in plans]
+    kind = [int(q % 8 == 7) for q in range(96)]
+    for q, k in enumerate(kind):
+        srv.submit(ids[k], fs[k].weights.reshape(-1), q)
+    done = srv.drain()
+    assert sorted(r.request_id for r in done) == list(range(96))
+    for r in done:
+        k = kind[r.request_id]
+        assert same(r.value, *refs[k], tolerance(plans[k])), r.request_id
