@@ -84,14 +84,18 @@ struct SStruct {
     int32_t n_user = 0;           // a request brings 2 * n_user weights
     std::vector<double> w_aux;    // (1, 1) per auxiliary variable
     GemmShape gemm_shape;         // from the plan's tuning table
-    // the fused program, and the plan's launch list, which a request runs on
-    // if a chain of the first left its range (and which is all there is if
-    // the plan has no fused program or no room for it)
-    std::vector<SProg> prog;
+    // the plan's launch list, and the fused program if the plan has one and
+    // there is room; a request of the latter whose chain left its range runs
+    // again on the former
+    SProg list, fused;
+    bool has_fused = false;
     int32_t root = -1;
     int64_t nt = 0;
-    uint64_t meta_bytes = 0, arena_bytes = 0, footprint = 0;
-    uint64_t max_step_bytes = 0;  // largest staging contribution of one request in one step
+    uint64_t meta_bytes = 0, arena_bytes = 0;
+    // region of a request, and its largest staging contribution in one step:
+    // on the launch list, and on either program
+    uint64_t list_footprint = 0, footprint = 0;
+    uint64_t list_step_bytes = 0, max_step_bytes = 0;
     int64_t nslices = 1;          // slices of the plan: parts per request
 };
 
@@ -99,9 +103,9 @@ struct SReq {
     uint64_t id = 0;
     int32_t s = 0;
     int32_t slot = -1;
-    uint64_t region = 0;
+    uint64_t region = 0, region_bytes = 0;
     size_t k = 0;
-    size_t prog = 0;              // program it runs on
+    bool fused = false;           // program it runs on
     std::vector<double> w;
     double t_arrive = 0, t_admit = 0;
     double deadline = 0;          // server clock, 0 = none
@@ -388,18 +392,19 @@ extern "C" wmc_status wmc_serve_create(const wmc_serve_options *opts, void *devi
 
 extern "C" void wmc_serve_destroy(wmc_server *v) { delete v; }
 
-static bool region_alloc(wmc_server *v, uint64_t size, uint64_t *off) {
-    for (auto it = v->free_regions.begin(); it != v->free_regions.end(); ++it) {
-        if (it->second < size) continue;
-        *off = it->first;
-        uint64_t rest = it->second - size, roff = it->first + size;
-        v->free_regions.erase(it);
-        if (rest) v->free_regions[roff] = rest;
-        v->used_bytes += size;
-        v->peak_used = std::max(v->peak_used, v->used_bytes);
-        return true;
-    }
-    return false;
+// First fit from the start of the pool, or (top) from its end.
+static bool region_alloc(wmc_server *v, uint64_t size, uint64_t *off, bool top = false) {
+    auto it = v->free_regions.begin(), found = v->free_regions.end();
+    for (; it != v->free_regions.end() && (top || found == v->free_regions.end()); ++it)
+        if (it->second >= size) found = it;
+    if (found == v->free_regions.end()) return false;
+    const uint64_t begin = found->first, rest = found->second - size;
+    v->free_regions.erase(found);
+    *off = top ? begin + rest : begin;
+    if (rest) v->free_regions[top ? begin : begin + size] = rest;
+    v->used_bytes += size;
+    v->peak_used = std::max(v->peak_used, v->used_bytes);
+    return true;
 }
 
 static void region_free(wmc_server *v, uint64_t off, uint64_t size) {
@@ -496,6 +501,29 @@ static SProg serve_program(const wmc_plan_t &plan, const FusedProgram &F, std::v
     return s;
 }
 
+// Gives back the resident images of the fused programs that no request runs
+// on: they are kept only where nothing else needs the room.
+static bool drop_fused(wmc_server *v) {
+    bool any = false;
+    for (size_t q = 0; q < v->S.size(); ++q) {
+        SStruct &s = v->S[q];
+        if (!s.has_fused) continue;
+        auto uses = [&](const SReq &r) { return r.fused && (size_t)r.s == q; };
+        if (std::any_of(v->active.begin(), v->active.end(), uses) ||
+            std::any_of(v->finishing.begin(), v->finishing.end(), uses))
+            continue;
+        v->used_bytes += s.fused.img_bytes;
+        region_free(v, s.fused.img_off, s.fused.img_bytes);
+        v->structure_bytes -= s.fused.img_bytes;
+        s.fused = SProg();
+        s.has_fused = false;
+        s.footprint = s.list_footprint;
+        s.max_step_bytes = s.list_step_bytes;
+        any = true;
+    }
+    return any;
+}
+
 // Registration builds the structure's resident image -- leaves and their
 // wave table, matrix-node descriptors, and per node launch its generic nodes
 // with their wave table and its streaming tasks (grouped by summed-index
@@ -524,7 +552,7 @@ extern "C" wmc_status wmc_serve_register(wmc_server *v, const wmc_plan_t *plan, 
         s.nt = (int64_t)std::max<size_t>(plan->T.size(), 1);
         s.meta_bytes = sal(sizeof(wmc_meta) * (uint64_t)s.nt, 256);
         s.arena_bytes = sal(std::max<uint64_t>(plan->arena_bytes, 256), 256);
-        s.footprint = s.meta_bytes + s.arena_bytes;
+        s.list_footprint = s.footprint = s.meta_bytes + s.arena_bytes;
         s.nslices = (int64_t)1 << plan->sliced.size();
         // staging per request and step: its weights (first step), a work
         // entry, a clear range or a finish entry, and its records
@@ -539,8 +567,8 @@ extern "C" wmc_status wmc_serve_register(wmc_server *v, const wmc_plan_t *plan, 
         std::vector<uint8_t> img;
         const FusedProgram &fused = plan->fused;
         const FusedProgram list = wmc_program_of(*plan, false);
-        SProg general = serve_program(*plan, list, img);
-        s.max_step_bytes = staging(general);
+        s.list = serve_program(*plan, list, img);
+        s.list_step_bytes = s.max_step_bytes = staging(s.list);
         if (s.footprint > v->regions_bytes || s.max_step_bytes > v->step_cap) {
             wmc_set_error("wmc_serve_register: structure needs %llu bytes of region and %llu of staging",
                           (unsigned long long)s.footprint, (unsigned long long)s.max_step_bytes);
@@ -548,38 +576,47 @@ extern "C" wmc_status wmc_serve_register(wmc_server *v, const wmc_plan_t *plan, 
         }
         if (v->inflight) HIP_TRY(hipEventSynchronize(v->ev[v->parity]));
         // descriptors are resident: they leave the budget for requests
-        auto upload = [&](SProg &g) -> wmc_status {
+        // (the fused programs' from the pool's end, so that the room is in one
+        // piece when they leave)
+        auto reserve = [&](SProg &g, bool top = false) {
             g.img_bytes = sal(std::max<uint64_t>(img.size(), 256), 256);
             const uint64_t peak = v->peak_used;
-            if (!region_alloc(v, g.img_bytes, &g.img_off)) {
-                wmc_set_error("wmc_serve_register: no room for the structure's %llu bytes of descriptors",
-                              (unsigned long long)g.img_bytes);
-                return WMC_ERR_OUT_OF_MEMORY;
-            }
+            if (!region_alloc(v, g.img_bytes, &g.img_off, top)) return false;
             v->used_bytes -= g.img_bytes;
             v->peak_used = peak;
             v->structure_bytes += g.img_bytes;
-            HIP_TRY(hipMemcpyAsync(v->dev + v->off_regions + g.img_off, img.data(), img.size(), hipMemcpyHostToDevice,
-                                   v->st));
-            HIP_TRY(hipStreamSynchronize(v->st));
-            return WMC_OK;
+            return true;
         };
-        wmc_status us = upload(general);
-        if (us != WMC_OK) return us;
-        if (fused.on) {
+        auto upload = [&](const SProg &g) {
+            const hipError_t e = hipMemcpyAsync(v->dev + v->off_regions + g.img_off, img.data(), img.size(),
+                                                hipMemcpyHostToDevice, v->st);
+            return e != hipSuccess ? e : hipStreamSynchronize(v->st);
+        };
+        if (!reserve(s.list) && !(drop_fused(v) && reserve(s.list))) {
+            wmc_set_error("wmc_serve_register: no room for the structure's %llu bytes of descriptors",
+                          (unsigned long long)s.list.img_bytes);
+            return WMC_ERR_OUT_OF_MEMORY;
+        }
+        const hipError_t he = upload(s.list);
+        if (he == hipSuccess && fused.on) {
             // only where the second image and the larger region leave the
             // budget to the requests
-            SProg g = serve_program(*plan, fused, img);
+            s.fused = serve_program(*plan, fused, img);
             const uint64_t foot = s.meta_bytes + sal(std::max(plan->arena_bytes, fused.arena_bytes), 256);
-            const uint64_t step = std::max(s.max_step_bytes, staging(g));
-            if (step <= v->step_cap / 4 && foot <= v->regions_bytes / 16 &&
-                v->structure_bytes + img.size() + 256 <= v->regions_bytes / 8 && upload(g) == WMC_OK) {
+            const uint64_t step = std::max(s.max_step_bytes, staging(s.fused));
+            s.has_fused = step <= v->step_cap / 4 && foot <= v->regions_bytes / 16 &&
+                          v->structure_bytes + img.size() + 256 <= v->regions_bytes / 8 && reserve(s.fused, true) && upload(s.fused) == hipSuccess;
+            if (s.has_fused) {
                 s.footprint = foot;
                 s.max_step_bytes = step;
-                s.prog.push_back(std::move(g));
+            } else {
+                s.fused = SProg();
             }
         }
-        s.prog.push_back(std::move(general));
+        if (he != hipSuccess) {
+            wmc_set_error("wmc_serve_register: upload of descriptors failed: %s", hipGetErrorString(he));
+            return WMC_ERR_DEVICE;
+        }
         v->S.push_back(std::move(s));
         if (structure_id) *structure_id = (int32_t)v->S.size() - 1;
     } catch (std::bad_alloc &) {
@@ -753,7 +790,7 @@ static wmc_status serve_collect(wmc_server *v) {
         const SStruct &s = v->S[(size_t)r.s];
         if (r.cancelled) {
             respond_cancelled(v, r);
-            region_free(v, r.region, s.footprint);
+            region_free(v, r.region, r.region_bytes);
             v->free_slots.push_back(r.slot);
             continue;
         }
@@ -762,13 +799,13 @@ static wmc_status serve_collect(wmc_server *v) {
             // a chain left its range: once more, on the launch list, in the
             // same slot and region
             r.k = 0;
-            r.prog = s.prog.size() - 1;
+            r.fused = false;
             v->again.push_back(std::move(r));
             continue;
         }
         if (s.root < 0) complete(v, r, true, 0.5, 1);  // the empty product: 1
         else complete(v, r, true, res[r.slot].m, res[r.slot].e);
-        region_free(v, r.region, s.footprint);
+        region_free(v, r.region, r.region_bytes);
         v->free_slots.push_back(r.slot);
     }
     v->finishing.clear();
@@ -809,22 +846,30 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
     for (SReq &r : v->active) expire(r);
     for (SReq &r : v->again) expire(r);
     uint64_t stage_need = 0;
-    for (const SReq &r : v->active) stage_need += v->S[(size_t)r.s].max_step_bytes;
+    auto step_bytes = [&](const SReq &r) {
+        const SStruct &s = v->S[(size_t)r.s];
+        return r.fused ? s.max_step_bytes : s.list_step_bytes;
+    };
+    for (const SReq &r : v->active) stage_need += step_bytes(r);
     // requests to run again hold a slot and a region already
-    while (!v->again.empty()) {
-        const uint64_t need = v->S[(size_t)v->again.front().s].max_step_bytes;
-        if (stage_need + need > v->step_cap) break;
-        stage_need += need;
+    while (!v->again.empty() && stage_need + step_bytes(v->again.front()) <= v->step_cap) {
+        stage_need += step_bytes(v->again.front());
         v->active.push_back(std::move(v->again.front()));
         v->again.pop_front();
     }
     while (v->again.empty() && !v->queue.empty() && !v->free_slots.empty()) {
         SReq &r = v->queue.front();
-        const SStruct &s = v->S[(size_t)r.s];
+        SStruct &s = v->S[(size_t)r.s];
         if (stage_need + s.max_step_bytes > v->step_cap) break;
         uint64_t off;
-        if (!region_alloc(v, s.footprint, &off)) break;
+        if (!region_alloc(v, s.footprint, &off)) {
+            // an idle server without room for it: the fused programs' images
+            // leave
+            if (!v->active.empty() || !v->finishing.empty() || !drop_fused(v) || !region_alloc(v, s.footprint, &off)) break;
+        }
         r.region = off;
+        r.region_bytes = s.footprint;
+        r.fused = s.has_fused;
         r.slot = v->free_slots.back();
         v->free_slots.pop_back();
         r.k = 0;
@@ -869,7 +914,7 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
         }
         const long long mbase = (long long)(r.region / sizeof(wmc_meta));
         const long long abase = (long long)((r.region + s.meta_bytes) / elem);
-        const SProg &g = s.prog[r.prog];
+        const SProg &g = r.fused ? s.fused : s.list;
         const char *base = img + g.img_off;
         const int entry = (int)works.size();
         ServeWork w;

@@ -17,3 +17,27 @@ def test_refused_program_takes_no_memory(precision):
     assert p.program()[1]["n_launches"] == 0 and st["arena_bytes"] <= cap
     _, info = W.Batch([p]).image()
     assert info["arena_elems"] * info["elem"] == st["arena_bytes"]
+
+
+@pytest.mark.gpu
+def test_resident_programs_leave_room_for_a_large_request():
+    """A structure whose region takes all that the launch lists' images leave
+    is served, though the fused programs of structures registered before it
+    were kept in that room; those structures go on being served."""
+    f, g = wl.grid_cnf(10, 20, 0.2, seed=2), wl.grid_cnf(16, 20, 0.1, seed=2)
+    small = [W.Plan(W.Network.from_formula(f), seed=q, precision="fp32") for q in range(5)]
+    large = W.Plan(W.Network.from_formula(g), seed=0, precision="fp32")
+    budget = large.stats()["arena_bytes"] + int(1.3 * sum(len(p.image()[0]) for p in small + [large]))
+    srv = W.Server(precision="fp32", max_slots=8, hbm_budget_bytes=budget, buffer_bytes=budget + (64 << 20))
+    ids = [srv.register(p) for p in small]
+    srv.submit(ids[0], f.weights.reshape(-1), 1)
+    first = srv.wait(5.0)
+    srv.submit(srv.register(large), g.weights.reshape(-1), 2)
+    done = srv.wait(5.0)
+    assert [r.request_id for r in done] == [2]
+    assert abs(done[0].value.log2_abs - W.wmc_contract(large).log2_abs) < 1e-4
+    for q, s in enumerate(ids):
+        srv.submit(s, f.weights.reshape(-1), 10 + q)
+    done = sorted(srv.drain(), key=lambda r: r.request_id)
+    assert [r.request_id for r in done] == list(range(10, 15))
+    assert all(abs(r.value.log2_abs - first[0].value.log2_abs) < 1e-4 for r in done)
