@@ -587,6 +587,11 @@ extern "C" wmc_status wmc_serve_register(wmc_server *v, const wmc_plan_t *plan, 
             v->structure_bytes += g.img_bytes;
             return true;
         };
+        auto release = [&](const SProg &g) {
+            v->used_bytes += g.img_bytes;
+            region_free(v, g.img_off, g.img_bytes);
+            v->structure_bytes -= g.img_bytes;
+        };
         auto upload = [&](const SProg &g) {
             const hipError_t e = hipMemcpyAsync(v->dev + v->off_regions + g.img_off, img.data(), img.size(),
                                                 hipMemcpyHostToDevice, v->st);
@@ -597,7 +602,7 @@ extern "C" wmc_status wmc_serve_register(wmc_server *v, const wmc_plan_t *plan, 
                           (unsigned long long)s.list.img_bytes);
             return WMC_ERR_OUT_OF_MEMORY;
         }
-        const hipError_t he = upload(s.list);
+        hipError_t he = upload(s.list);
         if (he == hipSuccess && fused.on) {
             // only where the second image and the larger region leave the
             // budget to the requests
@@ -605,15 +610,18 @@ extern "C" wmc_status wmc_serve_register(wmc_server *v, const wmc_plan_t *plan, 
             const uint64_t foot = s.meta_bytes + sal(std::max(plan->arena_bytes, fused.arena_bytes), 256);
             const uint64_t step = std::max(s.max_step_bytes, staging(s.fused));
             s.has_fused = step <= v->step_cap / 4 && foot <= v->regions_bytes / 16 &&
-                          v->structure_bytes + img.size() + 256 <= v->regions_bytes / 8 && reserve(s.fused, true) && upload(s.fused) == hipSuccess;
+                          v->structure_bytes + img.size() + 256 <= v->regions_bytes / 8 && reserve(s.fused, true);
             if (s.has_fused) {
                 s.footprint = foot;
                 s.max_step_bytes = step;
+                he = upload(s.fused);
+                if (he != hipSuccess) release(s.fused);
             } else {
                 s.fused = SProg();
             }
         }
         if (he != hipSuccess) {
+            release(s.list);
             wmc_set_error("wmc_serve_register: upload of descriptors failed: %s", hipGetErrorString(he));
             return WMC_ERR_DEVICE;
         }
