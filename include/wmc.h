@@ -187,8 +187,9 @@ typedef struct {
     double bytes_per_slice;     /* sum over nodes of elem_size*(|A|+|B|+|C|) */
     double peak_live_bytes;     /* peak of live tensor bytes (256-byte aligned) over the executed
                                    schedule: a lower bound on arena_bytes */
-    uint64_t arena_bytes;       /* static arena after placement (MemCost, what mem_cap bounds) */
-    uint64_t workspace_bytes;   /* device workspace wmc_contract needs */
+    uint64_t arena_bytes;       /* static arena of the launch list after placement (MemCost, what mem_cap bounds) */
+    uint64_t workspace_bytes;   /* device workspace wmc_contract needs: a fused program's arena counts, which
+                                 * without mem_cap_bytes may be larger (by 64 MiB at most over a slice group) */
     int64_t class_hist[WMC_N_CLASSES];
     int64_t n_launches;         /* kernel launches per slice, node by node */
     double max_node_bytes;      /* largest single-node traffic */

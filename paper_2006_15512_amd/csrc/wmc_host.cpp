@@ -1399,9 +1399,10 @@ static wmc_status finalize_plan(const wmc_network &net, const wmc_plan_options &
     P.arena_stride = align_up(P.arena_bytes, 256);
     P.workspace_bytes = P.off_arena + (uint64_t)P.group * P.arena_stride;
     // the fused program's image shares the descriptor region and its tensors
-    // the arena, which may grow by half unless the caller bounds it; a plan
-    // that fits the static scratch keeps fitting it
-    wmc_fuse(P, o.mem_cap_bytes ? P.arena_bytes : P.arena_bytes + P.arena_bytes / 2);
+    // the arena, which may grow by half and, in all arenas of a group, by
+    // 64 MiB, unless the caller bounds it: a plan that fills the device goes on
+    // fitting it, as one that fits the static scratch does
+    wmc_fuse(P, P.arena_bytes + (o.mem_cap_bytes ? 0 : std::min<uint64_t>(P.arena_bytes / 2, (64ull << 20) / (uint64_t)P.group)));
     if (P.fused.on) {
         // a call looks for slices out of range once per log of them; 1024
         // slices take long enough that the look is nothing (5 ms and more)

@@ -1,5 +1,4 @@
 """What a fused program may take in memory."""
-import numpy as np
 import pytest
 
 import paper_2006_15512_amd as W
@@ -17,6 +16,18 @@ def test_refused_program_takes_no_memory(precision):
     assert p.program()[1]["n_launches"] == 0 and st["arena_bytes"] <= cap
     _, info = W.Batch([p]).image()
     assert info["arena_elems"] * info["elem"] == st["arena_bytes"]
+
+
+def test_programs_add_little_to_a_large_workspace():
+    """Eight arenas side by side, each of which a fused program would take
+    beyond the launch list's: together they stay within 64 MiB more, beside
+    the descriptors."""
+    f = wl.banded_3cnf(185, 621, 31, seed=80)
+    p = W.Plan(W.Network.from_formula(f), seed=1, block=3, rank_cap=21, slice_group=16)
+    st = p.stats()
+    assert st["slice_group"] == 8
+    descriptors = len(p.image()[0]) + len(p.program()[0])
+    assert st["workspace_bytes"] - 8 * st["arena_bytes"] <= (64 << 20) + 2 * descriptors + (1 << 20)
 
 
 @pytest.mark.gpu
