@@ -4,6 +4,10 @@
 // operand, become one chain whose intermediates F_1 .. F_{L-1} stay in LDS
 // (wmc_chain.h).  A node-by-node launch list writes every intermediate to
 // memory and reads it back, and pays one launch per tree level.
+
+// Pricing a chain counts bits throughout; every host that takes this card has
+// the instruction.
+#pragma GCC target("popcnt")
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -25,24 +29,49 @@ const double kTile = 1.3e-6, kStage = 0.5e-6, kRound = 0.8e-6, kRunning = 768;
 const double kTileProducts = 12e9;
 const double kShortTile = 3e-6, kShortStage = 0.4e-6;
 
+// A vector of bounded length without allocations: planning prices hundreds
+// of chains even for a small formula.
+template <typename X, int N>
+struct Few {
+    X v[N];
+    int n = 0;
+    void push_back(X x) { v[n++] = x; }
+    void clear() { n = 0; }
+    size_t size() const { return (size_t)n; }
+    bool empty() const { return n == 0; }
+    X &operator[](size_t i) { return v[i]; }
+    const X &operator[](size_t i) const { return v[i]; }
+    const X &back() const { return v[n - 1]; }
+    const X &front() const { return v[0]; }
+    const X *begin() const { return v; }
+    const X *end() const { return v + n; }
+};
+
 // The variables around one chain, as bits of 64-bit masks.
 struct Chain {
-    std::vector<int32_t> nodes, gs;
+    Few<int32_t, WMC_CHAIN_MAX> nodes, gs;
     int32_t f = -1;
-    std::vector<int32_t> local;                // local id -> variable
+    Few<int32_t, 64> local;                          // local id -> variable
     uint64_t vf = 0;
-    std::vector<uint64_t> vc, vg, kap;         // per stage
+    Few<uint64_t, WMC_CHAIN_MAX> vc, vg, kap;        // per stage
     uint64_t inner = 0, outer = 0;
-    std::vector<int> ebits;                    // per stage: log2 of the tile's outputs
+    Few<int, WMC_CHAIN_MAX> ebits;                   // per stage: log2 of the tile's outputs
     // LDS entries: the outputs of odd and of even stages, the copies of F_0
-    // (-1: read from memory) and of the G_i, and all of them
+    // (-1: read from memory) and of the G_i, and all of them (place_lds)
     int odd = 0, even = 0, fcopy = -1, lds = 0;
-    std::vector<int> gcopy;
+    int gcopy[WMC_CHAIN_MAX] = {};
     double bytes = 0, products = 0;
     bool big = false;                          // many tiles: runs alone, register-tiled
 };
 
 int bits(uint64_t m) { return __builtin_popcountll(m); }
+// 2^n, 0 <= n < 1024
+double power(int n) {
+    const uint64_t u = (uint64_t)(n + 1023) << 52;
+    double x;
+    std::memcpy(&x, &u, sizeof x);
+    return x;
+}
 
 // A chain with more products, or more tiles, runs alone (wmc_chain.h).
 const double kShort = 1048576.0;
@@ -118,64 +147,76 @@ struct Fuser {
         return true;
     }
 
-    // LDS of the chain with the given inner variables (copy_f, copy_g: with
-    // copies of F_0 and of the G_i): every region is a power of two of entries, so that in descending order each starts at a
-    // multiple of its size (addresses combine by XOR).  F_0's copy shares the
-    // even stages' region, which stage 2 is the first to write.
-    bool lds_fits(Chain &h, uint64_t inner, bool copy_f, bool copy_g) const {
+    // LDS entries of the chain with the given inner variables (copy_f,
+    // copy_g: with copies of F_0 and of the G_i) by region, and whether they
+    // fit.  F_0's copy shares the even stages' region, which stage 2 is the
+    // first to write.
+    bool lds_fits(const Chain &h, uint64_t inner, bool copy_f, bool copy_g, int *odd_even = nullptr) const {
         const size_t L = h.nodes.size();
         int odd = 0, even = 0;
         long long total = 0;
-        std::vector<int> g(L);
         for (size_t i = 0; i < L; ++i) {
-            const int eb = bits(inner & h.vc[i]), gb = bits(h.vg[i] & (inner | h.kap[i]));
-            if (eb > WMC_CHAIN_BITS || (copy_g && gb > WMC_CHAIN_BITS)) return false;
+            const int eb = bits(inner & h.vc[i]);
+            if (eb > WMC_CHAIN_BITS) return false;
             if (i + 1 < L) (i % 2 ? even : odd) = std::max(i % 2 ? even : odd, 1 << eb);
-            g[i] = copy_g ? 1 << gb : 0;
-            total += g[i];
+            if (!copy_g) continue;
+            const int gb = bits(h.vg[i] & (inner | h.kap[i]));
+            if (gb > WMC_CHAIN_BITS) return false;
+            total += 1 << gb;
         }
-        int f = 0;
         if (copy_f) {
             const int fb = bits(h.vf & (inner | h.kap[0]));
             if (fb > WMC_CHAIN_BITS) return false;
-            f = 1 << fb;
+            even = std::max(even, 1 << fb);
         }
-        total += odd + std::max(even, f);
+        total += odd + even;
         // the words of a short chain are read from LDS, too
         const long long words =
             CH_WORDS + (long long)L * CS_WORDS + (long long)(L + 2) * WMC_CHAIN_TILE_BITS + (long long)(L + 1) * WMC_CHAIN_BITS;
         if (total * elem + (copy_g ? words * 4 + 1024 : 0) > (copy_g ? WMC_CHAIN_LDS_SHORT : WMC_CHAIN_LDS)) return false;
-        std::vector<std::pair<int, int>> r = {{odd, -1}, {std::max(even, f), -2}};
-        for (size_t i = 0; i < L; ++i) r.push_back({g[i], (int)i});
+        if (odd_even) {
+            odd_even[0] = odd;
+            odd_even[1] = even;
+        }
+        return true;
+    }
+
+    // Places the regions of an evaluated chain: every one is a power of two of
+    // entries, so that in descending order each starts at a multiple of its
+    // size (addresses combine by XOR).
+    void place_lds(Chain &h) const {
+        const size_t L = h.nodes.size();
+        int oe[2] = {0, 0};
+        const bool copy_f = !h.big && lds_fits(h, h.inner, true, true, oe);
+        if (!copy_f) lds_fits(h, h.inner, false, !h.big, oe);
+        std::vector<std::pair<int, int>> r = {{oe[0], -1}, {oe[1], -2}};
+        for (size_t i = 0; i < L; ++i) r.push_back({h.big ? 0 : 1 << bits(h.vg[i] & (h.inner | h.kap[i])), (int)i});
         std::stable_sort(r.begin(), r.end(), [](auto &x, auto &y) { return x.first > y.first; });
-        h.gcopy.assign(L, 0);
         int at = 0;
         for (auto &x : r) {
-            (x.second == -1 ? h.odd : x.second == -2 ? h.even : h.gcopy[(size_t)x.second]) = at;
+            (x.second == -1 ? h.odd : x.second == -2 ? h.even : h.gcopy[x.second]) = at;
             at += x.first;
         }
         h.fcopy = copy_f ? h.even : -1;
         h.lds = at;
-        return true;
     }
 
     // Chooses the inner variables of the chain and prices it; false if the
     // tiles do not fit the LDS.  Short chains copy their operands to LDS; for
     // chains of many tiles the tile size of the least cost is taken.
     bool evaluate(Chain &h) {
-        if (evaluate_to(h, WMC_CHAIN_BITS, false) && h.products <= kShort && bits(h.outer) <= WMC_CHAIN_TILE_BITS) {
-            lds_fits(h, h.inner, true, true) || lds_fits(h, h.inner, false, true);
-            return true;
-        }
         Chain best;
-        for (int t = 8; t <= WMC_CHAIN_BITS; ++t)
-            if (evaluate_to(h, t, true) && (best.nodes.empty() || price(h) < price(best))) best = h;
+        if (evaluate_to(h, false, best) && h.products <= kShort && bits(h.outer) <= WMC_CHAIN_TILE_BITS) return true;
+        evaluate_to(h, true, best);
         if (best.nodes.empty()) return false;
-        h = std::move(best);
+        h = best;
         return true;
     }
 
-    bool evaluate_to(Chain &h, int most, bool big) {
+    // The largest tiles of a short chain into h; of a chain of many tiles the
+    // least dear of those that first reach 2^8 ... 2^WMC_CHAIN_BITS outputs of
+    // a stage, into best.
+    bool evaluate_to(Chain &h, bool big, Chain &best) {
         const size_t L = h.nodes.size();
         h.big = big;
         const std::vector<int32_t> &out = T[(size_t)h.nodes.back()].layout;
@@ -204,25 +245,39 @@ struct Fuser {
         }
         // tiles of at least one entry per thread, larger ones while enough
         // tiles remain to fill the device
+        int reached = 7;
+        auto offer = [&] {
+            if (measure(h, in) && (best.nodes.empty() || price(h) < price(best))) best = h;
+        };
         for (int32_t v : out) {
             const uint64_t b = 1ull << id_of[(size_t)v];
             if (in & b) continue;
             int t = 0;
             for (size_t i = 0; i < L; ++i) t = std::max(t, bits(in & h.vc[i]));
-            if (t >= most || (t >= WMC_CHAIN_LANE_BIG && bits(vl & ~in) <= 10)) break;
+            if (big && t > reached) {
+                reached = t;
+                offer();
+            }
+            if (t >= WMC_CHAIN_BITS || (t >= WMC_CHAIN_LANE_BIG && bits(vl & ~in) <= 10)) break;
             if (!take(b)) break;
         }
+        if (big) offer();
+        return measure(h, in);
+    }
+
+    bool measure(Chain &h, uint64_t in) const {
+        const size_t L = h.nodes.size();
+        const uint64_t vl = h.vc.back();
         h.inner = in;
         h.outer = vl & ~in;
         h.ebits.clear();
         h.products = 0;
-        h.bytes = (double)elem * (std::ldexp(1.0, bits(h.vf) + bits(h.outer & ~h.vf)) + std::ldexp(1.0, bits(vl)));
+        h.bytes = (double)elem * (power(bits(h.vf) + bits(h.outer & ~h.vf)) + power(bits(vl)));
         for (size_t i = 0; i < L; ++i) {
             h.ebits.push_back(bits(in & h.vc[i]));
-            h.products += std::ldexp(1.0, bits(h.outer) + h.ebits.back() + bits(h.kap[i]));
-            h.bytes += (double)elem * std::ldexp(1.0, bits(h.vg[i]));
+            h.products += power(bits(h.outer) + h.ebits.back() + bits(h.kap[i]));
+            h.bytes += (double)elem * power(bits(h.vg[i]));
         }
-        lds_fits(h, in, false, !big);
         return bits(h.outer) <= 28;
     }
 
@@ -276,8 +331,8 @@ struct Fuser {
         };
         auto offset = [](int p) { return p < 0 ? 0u : 1u << p; };
         while (F.words.size() % 4) F.words.push_back(0);
-        t.nodes = h.nodes;
-        t.g = h.gs;
+        t.nodes.assign(h.nodes.begin(), h.nodes.end());
+        t.g.assign(h.gs.begin(), h.gs.end());
         t.f = h.f;
         t.desc = (unsigned)F.words.size();
         t.tile_bits = bits(h.outer);
@@ -438,13 +493,22 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
                 cost[i + 1] = one;
                 from[i + 1] = (int)i;
             }
+            // no chain costs less than a short one of one tile: where even that
+            // would be no gain, none is built
+            auto gains = [&](size_t j) {
+                return cost[i] + kLaunch + kShortTile + kShortStage * (double)(j - i + 1) < cost[j + 1];
+            };
+            size_t end = std::min(m, i + WMC_CHAIN_MAX);
+            while (end > i + 1 && !gains(end - 1)) --end;
             Chain h;
-            if (!fu.begin(h, path[i])) continue;
+            if (end == i + 1 || !fu.begin(h, path[i])) continue;
             int most = fu.rank(path[i]);
-            for (size_t j = i + 1; j < m && (int)h.nodes.size() < WMC_CHAIN_MAX; ++j) {
-                if (!fu.extend(h, path[j]) || !fu.evaluate(h)) break;
+            for (size_t j = i + 1; j < end; ++j) {
+                if (!fu.extend(h, path[j])) break;
                 most = std::max(most, fu.rank(path[j]));
                 if (most < 6) continue;  // a handful of entries: left to the batched small nodes
+                if (!gains(j)) continue;
+                if (!fu.evaluate(h)) break;
                 const double c = cost[i] + fu.price(h);
                 if (c < cost[j + 1]) {
                     cost[j + 1] = c;
@@ -461,6 +525,7 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
             bool ok = fu.begin(h, path[i]);
             for (size_t q = i + 1; q < j && ok; ++q) ok = fu.extend(h, path[q]);
             if (!ok || !fu.evaluate(h)) continue;
+            fu.place_lds(h);
             for (int32_t q : h.nodes) chain_of[(size_t)q] = (int32_t)chains.size();
             chains.push_back(std::move(h));
         }
@@ -499,8 +564,9 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
     auto inputs = [&](const Item &it, std::vector<int32_t> &in) {
         in.clear();
         if (it.chain >= 0) {
-            in = chains[(size_t)it.chain].gs;
-            in.push_back(chains[(size_t)it.chain].f);
+            const Chain &h = chains[(size_t)it.chain];
+            in.assign(h.gs.begin(), h.gs.end());
+            in.push_back(h.f);
         } else {
             in.push_back(P.T[(size_t)it.node].a);
             in.push_back(P.T[(size_t)it.node].b);
