@@ -16,6 +16,7 @@
 // roots with one kernel.  The whole sequence can be captured once as a HIP
 // graph and replayed.
 #include <array>
+#include <deque>
 #include <memory>
 #include <mutex>
 
@@ -164,17 +165,19 @@ static uint64_t bal(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::vector<int64_t> &iplan,
                        const std::vector<int64_t> &abase, const std::vector<int64_t> &mbase) {
     BatchFused &F = B.fused;
-    std::vector<FusedProgram> prog;
+    std::deque<FusedProgram> lists;  // of plans without one
+    std::vector<const FusedProgram *> prog;
     size_t kmax = 0;
     for (int64_t i = 0; i < B.n; ++i) {
-        prog.push_back(wmc_program_of(*plans[i]));
-        kmax = std::max(kmax, prog.back().launches.size());
+        if (!plans[i]->fused.on) lists.push_back(wmc_program_of(*plans[i]));
+        prog.push_back(plans[i]->fused.on ? &plans[i]->fused : &lists.back());
+        kmax = std::max(kmax, prog.back()->launches.size());
     }
     const size_t ni = iplan.size();
     // leaves keep the launch lists' numbering; only their places differ
     F.leaves = B.leaves;
     for (size_t j = 0, q = 0; j < ni; ++j) {
-        const FusedProgram &G = prog[(size_t)iplan[j]];
+        const FusedProgram &G = *prog[(size_t)iplan[j]];
         for (const LeafDesc &d : G.leaves) F.leaves[q++].out = d.out + abase[j];
         const wmc_plan_t &P = *plans[iplan[j]];
         F.root_off.push_back(P.root < 0 ? 0 : (long long)(G.off[(size_t)P.root] + abase[j]));
@@ -190,7 +193,7 @@ static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::
         std::vector<ChainRec> wide, big;
         S.rec_first = (int64_t)F.recs.size();
         for (size_t j = 0; j < ni; ++j) {
-            const FusedProgram &G = prog[(size_t)iplan[j]];
+            const FusedProgram &G = *prog[(size_t)iplan[j]];
             if (k >= G.launches.size()) continue;
             const FusedLaunch &L = G.launches[k];
             for (int32_t q = 0; q < L.node_count && L.type != FUSED_GEMM; ++q) {
