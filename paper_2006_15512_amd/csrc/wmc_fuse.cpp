@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <numeric>
 
 #include "wmc_internal.h"
@@ -794,15 +795,20 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
     const uint64_t arena = std::max(P.arena_bytes, F.arena_bytes) / (uint64_t)P.elem;
     for (size_t t = 0; t < F.off.size(); ++t)
         if (F.off[t] >= 0 && (uint64_t)F.off[t] + (1ull << rank((int32_t)t)) > arena) return fail("tensor outside the arena");
+    std::map<unsigned, unsigned> used;  // words of the chain at a word
     for (const ChainTask &t : F.chains) {
         const unsigned *w = F.words.data() + t.desc;
+        if (t.desc + (uint64_t)CH_WORDS > F.words.size()) return fail("chain header");
+        const uint64_t have = F.words.size() - t.desc;
         const unsigned L = w[CH_STAGES], ob = w[CH_TILE_BITS];
         if (L < 1 || L > WMC_CHAIN_MAX || L != t.nodes.size() || (int)w[CH_TC] != t.nodes.back() || (int)w[CH_TF] != t.f)
             return fail("chain header");
         if (F.off[(size_t)t.f] < 0 || F.off[(size_t)t.nodes.back()] < 0) return fail("chain operand is not stored");
         const unsigned stride = t.big ? CS_WORDS_BIG : CS_WORDS;
         const unsigned *tiles = w + w[CH_TILES];
-        if (w[CH_TILES] != CH_WORDS + L * stride) return fail("tile lists");
+        if (w[CH_TILES] != CH_WORDS + L * stride || ob > 28 || w[CH_TILES] + (L + 2) * ob > have) return fail("tile lists");
+        unsigned &words = used[t.desc];
+        words = w[CH_TILES] + (L + 2) * ob;
         unsigned long long of = 0, oc = 0;
         for (unsigned b = 0; b < ob; ++b) {
             of |= tiles[b];
@@ -819,6 +825,11 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
             unsigned long long all = tiles_or;
             if (x[CX_BITS] > WMC_CHAIN_BITS || x[CX_LOW] > x[CX_BITS]) return false;
             all |= (1ull << x[CX_LOW]) - 1ull;
+            if (x[CX_LOW] < x[CX_BITS]) {
+                const uint64_t last = (uint64_t)x[CX_LIST] + x[CX_BITS] - x[CX_LOW];
+                if (x[CX_LIST] < w[CH_TILES] + (L + 2) * ob || last > have) return false;
+                words = std::max(words, (unsigned)last);
+            }
             for (unsigned b = x[CX_LOW]; b < x[CX_BITS]; ++b) all |= w[x[CX_LIST] + b - x[CX_LOW]];
             return (all >> rank(tensor)) == 0 && inside(x[CX_LDS], (1ull << x[CX_BITS]) - 1ull, end);
         };
@@ -890,10 +901,14 @@ bool wmc_validate_fused(const wmc_plan_t &P, std::string *why) {
         }
     }
     for (const ChainRec &r : F.recs) {
+        // the chain's words end before the next chain's begin
+        const auto at = used.find(r.desc);
+        if (at == used.end()) return fail("workgroup record");
+        const auto next = std::next(at);
+        const uint64_t end = next == used.end() ? F.words.size() : next->first;
         const unsigned ob = F.words[r.desc + CH_TILE_BITS];
-        const unsigned L = F.words[r.desc + CH_STAGES];
-        if (r.jbits > ob || r.blk >> (ob - r.jbits) || r.words < CH_WORDS + L * CS_WORDS + (L + 2) * ob ||
-            r.words > 3u << WMC_CHAIN_LANE || r.desc + r.words > F.words.size())
+        if (r.jbits > ob || r.blk >> (ob - r.jbits) || r.words < at->second || r.words > 3u << WMC_CHAIN_LANE ||
+            r.desc + (uint64_t)r.words > end)
             return fail("workgroup record");
     }
     return true;
