@@ -245,10 +245,12 @@ wmc_status wmc_plan_image(const wmc_plan_t *plan, void *dst, uint64_t dst_bytes,
 /* The program wmc_contract runs when consecutive nodes of the plan are fused
  * into chains: [leaf descriptors][node descriptors][matrix-node
  * descriptors][chain words (u32)][workgroup records (4 x u32)][8 x int32 per
- * launch: type (0 step of small nodes and chains, 1 one node alone, 2 one
- * matrix node), first node, nodes, first chain, chains, matrix node, first
- * record, records][first word of each chain (u32)][arena offset of each
- * tensor (int64, -1: never stored)].  info[0..8] = {n_leaves, n_nodes,
+ * launch: type (0 step of small nodes and short chains, 1 one node alone, 2
+ * one matrix node, 3 one chain of many tiles), first node, nodes, first chain,
+ * chains, matrix node, first record, records][first word of each chain
+ * (u32)][arena offset of each tensor (int64, -1: never stored)].  A chain's
+ * words are a header of 48, then per stage 28 words in a short chain and 64
+ * in a chain of many tiles, then the offsets of the tile index bits.  info[0..8] = {n_leaves, n_nodes,
  * n_gemms, n_words, n_records, n_launches, n_chains, n_tensors,
  * arena_elems}; n_launches 0: the plan's launch list runs as it is. */
 wmc_status wmc_plan_program(const wmc_plan_t *plan, void *dst, uint64_t dst_bytes, uint64_t *needed,
@@ -343,8 +345,7 @@ enum {
     WMC_KERNEL_STREAM2 = 6,       /* k_stream2: register-tiled streaming node */
     WMC_KERNEL_STREAM2_SPLIT = 7, /* k_stream2_split: summed index split over lane groups */
     WMC_KERNEL_FINISH = 8,        /* k_finish: slice accumulation */
-    WMC_KERNEL_STREAM2_VEC = 9,   /* k_stream2_vec: K = 1 streaming node, output pairs per thread */
-    WMC_KERNEL_CHAIN = 10         /* k_chain, k_chain_big: fused nodes (wmc_plan_program; not in launch lists) */
+    WMC_KERNEL_STREAM2_VEC = 9    /* k_stream2_vec: K = 1 streaming node, output pairs per thread */
 };
 wmc_status wmc_plan_kernels(const wmc_plan_t *plan, int32_t *kernel, int64_t cap, int64_t *n_out);
 
@@ -373,7 +374,9 @@ typedef struct wmc_batch wmc_batch;
                                  and replay it (captured on a private stream) */
 #define WMC_BATCH_PERSISTENT 4u /* every merged step in one cooperative launch: one workgroup
                                    per compute unit walks the steps, a grid-wide barrier
-                                   between them; results as without it, bit for bit. Batches
+                                   between them, node by node; results as without it, bit for
+                                   bit unless a node holds entries in denormal numbers (which
+                                   a fused program need not). Batches
                                    with matrix nodes run as without it. Takes precedence over
                                    WMC_BATCH_GRAPH. Slower than graph replay on batches of
                                    small formulas (the barriers and the low occupancy cost
@@ -382,6 +385,8 @@ typedef struct wmc_batch wmc_batch;
                                    barrier wait times out (20 s) */
 
 wmc_status wmc_batch_create(const wmc_plan_t *const *plans, int64_t n, wmc_batch **out);
+/* n_launches: kernels one wmc_batch_contract launches (without
+ * WMC_BATCH_PERSISTENT, and if no instance leaves its chains' range). */
 wmc_status wmc_batch_info(const wmc_batch *b, uint64_t *workspace_bytes, int64_t *n_launches,
                           int64_t *n_instances);
 /* weights: the instances' weight vectors concatenated (2 * sum of n_vars

@@ -550,7 +550,7 @@ def plan_launches(plan: Plan):
 
 
 KERNEL_NAMES = ["k_begin", "k_leaves", "k_nodes", "k_gemm_p", "k_gemm", "k_stream_mfma", "k_stream2",
-                "k_stream2_split", "k_finish", "k_stream2_vec", "k_chain"]
+                "k_stream2_split", "k_finish", "k_stream2_vec"]
 
 
 def plan_kernels(plan: Plan) -> np.ndarray:

@@ -66,7 +66,6 @@ __global__ void k_finish_batch(const T *__restrict__ arena, const long long *__r
 // unit can share in one (every workgroup of a launch reserves the most any of
 // them needs), chains of many tiles in one, streaming tasks in one, matrix
 // nodes one by one.
-const int kBatchLds = 19 * 1024;
 struct BatchStep {
     int64_t rec_first = 0, rec_count = 0, wide_first = 0, wide_count = 0, big_first = 0, big_count = 0;
     int lds = 0, wide_lds = 0, big_lds = 0;
@@ -215,7 +214,7 @@ static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::
                 const unsigned words = G.recs[(size_t)r].words;
                 const unsigned at = wmc_shift_chain(G, t, words, (long long)abase[j], (int)mbase[j], F.words);
                 const int lds = t.lds + (t.big ? 0 : (int)((words * 4 + 1023) / 1024 * 1024 / (unsigned)B.elem));
-                const bool is_wide = !t.big && lds * B.elem > kBatchLds;
+                const bool is_wide = !t.big && lds * B.elem > WMC_CHAIN_LDS_NARROW;
                 for (; r < L.rec_first + L.rec_count && G.recs[(size_t)r].desc == t.desc; ++r) {
                     ChainRec x = G.recs[(size_t)r];
                     x.desc = at;
@@ -288,6 +287,23 @@ static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::
 static bool batch_growth_ok(uint64_t list_bytes, uint64_t bytes) {
     const uint64_t most = std::max<uint64_t>(64ull << 20, std::min<uint64_t>(list_bytes / 4, 1ull << 30));
     return bytes <= list_bytes + most;
+}
+
+// Bytes of the merged fused programs' image, before it is built.
+static uint64_t fused_image_bytes(const wmc_plan_t *const *plans, int64_t n) {
+    uint64_t bytes = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        const wmc_plan_t &P = *plans[i];
+        const FusedProgram &F = P.fused;
+        const bool on = F.on;
+        uint64_t waves = (uint64_t)P.leaf_work / WMC_WAVE;
+        for (const NodeDesc &d : on ? F.nodes : P.nodes) waves += bal(1ull << d.rc, WMC_WAVE) / WMC_WAVE;
+        bytes += (sizeof(LeafDesc) * P.leaves.size() + sizeof(NodeDesc) * (on ? F.nodes : P.nodes).size() +
+                  sizeof(GemmDesc) * P.gemms.size() + sizeof(unsigned) * F.words.size() + sizeof(ChainRec) * F.recs.size() +
+                  sizeof(int) * waves)
+                 << P.sliced.size();
+    }
+    return bytes;
 }
 
 // A batch of checked plans; null if `fuse` and the fused programs would take
@@ -455,16 +471,15 @@ static std::unique_ptr<wmc_batch> make_batch(const wmc_plan_t *const *plans, int
     B->off_tables = off;
     off += bal(sizeof(int) * std::max<size_t>(B->tables.size(), 1), 256);
     B->desc_bytes = off - B->off_leaf;
-    const uint64_t list_off = off;
+    const uint64_t list_bytes = off + (uint64_t)list_elems * (uint64_t)B->elem;
+    if (fuse && !batch_growth_ok(list_bytes, list_bytes + fused_image_bytes(plans, n))) return nullptr;
     if (fuse) fuse_batch(*B, plans, iplan, abase, mbase);
     if (B->fused.on) {
         B->off_fused = off;
         off += bal(B->fused.image.size(), 256);
         B->off_live = off;
         off += bal((uint64_t)B->meta_total, 256);
-        if (!batch_growth_ok(list_off + (uint64_t)list_elems * (uint64_t)B->elem,
-                             off + (uint64_t)arena_elems * (uint64_t)B->elem))
-            return nullptr;
+        if (!batch_growth_ok(list_bytes, off + (uint64_t)arena_elems * (uint64_t)B->elem)) return nullptr;
     }
     B->off_arena = off;
     B->arena_bytes = (uint64_t)arena_elems * (uint64_t)B->elem;
@@ -532,7 +547,15 @@ extern "C" wmc_status wmc_batch_info(const wmc_batch *b, uint64_t *workspace_byt
         return WMC_ERR_INVALID_ARGUMENT;
     }
     if (workspace_bytes) *workspace_bytes = b->workspace_bytes;
-    if (n_launches) *n_launches = (int64_t)b->launches.size() + 2;
+    if (n_launches) {
+        *n_launches = (int64_t)b->launches.size() + 2;
+        if (b->fused.on) {
+            *n_launches = 2 + !b->fused.leaves.empty();
+            for (const BatchStep &S : b->fused.steps)
+                *n_launches += (S.big_count > 0) + (S.task_nk[4] > 0) + (S.wide_count > 0) +
+                               (S.rec_count > 0 || S.node_count > 0) + (int64_t)S.gemms.size();
+        }
+    }
     if (n_instances) *n_instances = b->n;
     return WMC_OK;
 }

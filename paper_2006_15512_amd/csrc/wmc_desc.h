@@ -110,6 +110,12 @@ struct GemmDesc {
 // lattice FP64: 54.6 ms at 30 KB, 48.7 at 38, 42.8 at 50, 42.9 at 72).
 #define WMC_CHAIN_LDS_SHORT (38 * 1024)
 #define WMC_CHAIN_LDS (50 * 1024)
+// Where many short chains share a launch (batches, serving), those above this
+// have a launch of their own: every workgroup of a launch reserves the most
+// any of them needs, and eight of 256 threads fill a compute unit's wave
+// slots at 19 KB each (512-instance batch FP64: 4.2 ms in one launch, 3.7 in
+// two).
+#define WMC_CHAIN_LDS_NARROW (19 * 1024)
 #define WMC_CHAIN_TILE_BITS 11  // largest tile index of a short chain
 // log2 of the bound of a chain's stored magnitudes.  Every operand entry is
 // below 1 as it is read, so F_i stays below 2^(lift + summed variables up to

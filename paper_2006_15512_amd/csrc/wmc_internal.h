@@ -86,7 +86,7 @@ struct FusedLaunch {
     int32_t chain_first = 0, chain_count = 0;
     int32_t gemm = -1;
     int32_t lds = 0;                      // entries of the storage type
-    int32_t rec_first = 0, rec_count = 0; // solo launch: workgroup records
+    int32_t rec_first = 0, rec_count = 0; // workgroup records of the chains, in their order
     int64_t tab = -1;                     // wave -> node table, -1 where the kernel searches
 };
 

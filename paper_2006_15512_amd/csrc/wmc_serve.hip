@@ -66,7 +66,6 @@ struct SLaunch {
 // workgroups on a compute unit, short ones that need more LDS, and ones of
 // many tiles.
 enum { SCHAIN_SHORT = 0, SCHAIN_WIDE, SCHAIN_BIG, SCHAIN_KINDS };
-const int kServeLds = 19 * 1024;
 
 // One program of a structure, its descriptors resident.
 struct SProg {
@@ -464,7 +463,7 @@ static SProg serve_program(const wmc_plan_t &plan, const FusedProgram &F, std::v
                 const ChainRec &x = F.recs[(size_t)r];
                 const int lds = t.lds * plan.elem + (t.big ? 0 : (int)((x.words * 4 + 1023) / 1024 * 1024));
                 sl.chains.push_back({words_off + sizeof(unsigned) * (uint64_t)x.desc, x.blk, x.jbits, x.words,
-                                     t.big ? SCHAIN_BIG : lds > kServeLds ? SCHAIN_WIDE : SCHAIN_SHORT, lds});
+                                     t.big ? SCHAIN_BIG : lds > WMC_CHAIN_LDS_NARROW ? SCHAIN_WIDE : SCHAIN_SHORT, lds});
             }
         }
         std::vector<NodeDesc> generic(F.nodes.begin() + Ln.node_first, F.nodes.begin() + Ln.node_first + Ln.node_count);

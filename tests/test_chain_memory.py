@@ -30,6 +30,22 @@ def test_programs_add_little_to_a_large_workspace():
     assert st["workspace_bytes"] - 8 * st["arena_bytes"] <= (64 << 20) + 2 * descriptors + (1 << 20)
 
 
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_batch_counts_the_launches_it_makes(precision):
+    """The fused programs' launches where they run, the launch lists' where
+    the programs' image would take more than a quarter of the workspace (a
+    plan of 1024 small slices)."""
+    f = wl.banded_3cnf(60, 180, 15, seed=5)
+    p = W.Plan(W.Network.from_formula(f), seed=0, precision=precision)
+    n = p.program()[1]["n_launches"]
+    assert 0 < n < p.stats()["n_launches"] - 3
+    assert n + 3 <= W.Batch([p]).n_launches <= 2 * n + 3
+    p = W.Plan(W.Network.from_formula(f), seed=0, precision=precision, rank_cap=8)
+    b = W.Batch([p])
+    assert p.n_slices == 1024 and p.program()[1]["n_launches"] > 0
+    assert b.n_launches >= p.stats()["n_launches"]
+
+
 @pytest.mark.gpu
 def test_resident_programs_leave_room_for_a_large_request():
     """A structure whose region takes all that the launch lists' images leave
