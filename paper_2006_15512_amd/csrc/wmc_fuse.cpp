@@ -663,8 +663,15 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
                 if (t.big) L.type = FUSED_CHAIN;
                 // workgroups: one tile each up to the launch's share of the
                 // device, then equal runs of consecutive tiles; dealt so
-                // that each XCD (workgroup index modulo 8) walks one slab
-                const int cap_bits = P.group >= 32 ? 6 : P.group >= 8 ? 8 : P.group >= 2 ? 10 : 11;
+                // that each XCD (workgroup index modulo 8) walks one slab.
+                // The share: about 2^11 workgroups over all slices of a group
+                // fill the device and leave each several tiles to spread its
+                // start over.  Min-fill 24x24 lattice FP64, ms at 2^7 / 2^8 /
+                // 2^10 / 2^11 / 2^12 workgroups per slice: 1 slice 165 / 101 /
+                // 75.2 / 73.5 / 75.8, 4 slices 55.6 / 53.5 / 50.7 / 51.2 / 54.3,
+                // 16 slices 44.6 / 43.1 / 43.5 / 48.2 / 48.0, 64 slices 41.4 /
+                // 40.4 / 41.4 / 42.7 / 46.0
+                const int cap_bits = P.group >= 8 ? 8 : P.group >= 2 ? 10 : 11;
                 const int jb = t.big ? std::max(0, t.tile_bits - cap_bits) : 0;
                 const unsigned n = 1u << (t.tile_bits - jb);
                 for (unsigned b = 0; b < n; ++b)
