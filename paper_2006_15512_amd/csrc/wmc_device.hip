@@ -134,7 +134,13 @@ static void fused_launches(const wmc_plan_t &P, char *ws, T *arena, wmc_meta *me
             launched = launch_node<T>(P, node_kernel<T>(P, d, mat, &sa, &ma), d, mat, mat ? Gd + Ln.gemm : nullptr, sa,
                                       ma, arena, meta, st, sg, nz);
         }
-        if (!launched) {
+        const int *tab = Ln.tab >= 0 ? TB + Ln.tab : nullptr;
+        if (!launched && !Ln.rec_count) {
+            // nodes without chains: k_nodes' workgroups of 256 threads put a
+            // node of 2^13 outputs on twice as many compute units
+            hipLaunchKernelGGL(k_nodes<T>, dim3(grid_for(Ln.node_work), 1, nz), dim3(WMC_BLOCK), 0, st,
+                               D + Ln.node_first, Ln.node_count, (long long)Ln.node_work, arena, meta, sg, tab);
+        } else if (!launched) {
             FusedStepArgs a{};
             a.recs = (const ChainRec *)(img + F.o_recs) + Ln.rec_first;
             a.words = (const unsigned *)(img + F.o_words);
@@ -142,7 +148,7 @@ static void fused_launches(const wmc_plan_t &P, char *ws, T *arena, wmc_meta *me
             a.nodes = D + Ln.node_first;
             a.nnodes = Ln.node_count;
             a.node_work = Ln.node_work;
-            a.wave_node = Ln.tab >= 0 ? TB + Ln.tab : nullptr;
+            a.wave_node = tab;
             a.nblocks = Ln.node_count ? chain_node_blocks<WMC_CHAIN_LANE>(Ln.node_work) : 0;
             if (Ln.type == FUSED_CHAIN) launch_chain_big<T>(a, Ln.lds, arena, meta, st, sg, nz);
             else launch_fused_step<T, WMC_CHAIN_LANE>(a, Ln.lds, arena, meta, st, sg, nz);
