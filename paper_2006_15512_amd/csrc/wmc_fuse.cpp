@@ -295,9 +295,11 @@ struct Fuser {
     // the others of their level: in a plan of large tensors a level more or
     // less is nothing, in a small one it is what the time goes to.
     double price_node(int32_t c) const {
+        return (T[(size_t)c].cls == WMC_CLASS_SMALL ? level : kLaunch) + slices * node_bytes(c) / kBytes;
+    }
+    double node_bytes(int32_t c) const {
         const TNode &C = T[(size_t)c];
-        const double b = std::ldexp(1.0, rank(C.a)) + std::ldexp(1.0, rank(C.b)) + std::ldexp(1.0, rank(c));
-        return (C.cls == WMC_CLASS_SMALL ? level : kLaunch) + slices * (double)elem * b / kBytes;
+        return (double)elem * (std::ldexp(1.0, rank(C.a)) + std::ldexp(1.0, rank(C.b)) + std::ldexp(1.0, rank(c)));
     }
 
     int lift(const Chain &h) const {
@@ -603,6 +605,22 @@ void wmc_fuse(wmc_plan_t &P, uint64_t max_arena) {
             if (--it.pending == 0) (it.small ? ready_small : ready_big).push_back(item_of[(size_t)up]);
         }
         steps.push_back(std::move(step));
+    }
+
+    // A small plan keeps its launch list, too, if chains neither save a tenth of
+    // its launches, nor eight, nor a twentieth of its time in bytes: the larger
+    // image then costs more than they save.  Row-by-row lattices in blocks of 5
+    // and 6 that saved 0 to 3 launches of 23 to 96 ran at 0.96 to 1.00 of the
+    // list's speed; those in blocks of 3 that saved 10 and more of 82 to 131 at
+    // 1.04 to 1.06, and plans of a dozen launches that saved two at 1.01 to 1.06.
+    if (fu.total <= 1e-3) {
+        const double n = (double)(P.launches.size() - 1), less = n - (double)steps.size();
+        double bytes = 0;
+        for (const Chain &h : chains) {
+            for (int32_t c : h.nodes) bytes += fu.node_bytes(c);
+            bytes -= h.bytes;
+        }
+        if (less < 0.1 * n && less < 8 && fu.slices * bytes / kBytes < 0.05 * (n * kLaunch + fu.total)) return;
     }
 
     // placement: a tensor lives from its writer's launch to its reader's

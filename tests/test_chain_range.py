@@ -261,7 +261,7 @@ def test_counts_in_range_on_device():
 def test_chains_that_feed_matrix_nodes(precision, small):
     """Chain outputs read by nodes with K >= 16, which multiply them as stored."""
     for f, kw in ((wl.banded_3cnf(80, 280, 18, seed=2), dict(block=4)),
-                  (wl.grid_cnf(9, 13, 0.1, seed=7), dict(kind="order", order=wl.row_major_order(9, 13), block=4))):
+                  (wl.banded_3cnf(150, 520, 18, seed=3), dict(block=4))):
         rng = np.random.default_rng(1)
         f = f.with_weights(rng.uniform(0.1, 0.9, (f.n, 2)) * np.where(rng.random((f.n, 1)) < 0.4, [1.0, small], [1, 1]))
         p = W.Plan(W.Network.from_formula(f), seed=0, precision=precision, **kw)
@@ -399,3 +399,13 @@ def test_requests_that_run_again_fit_the_staging(step_kib):
     for r in done:
         k = kind[r.request_id]
         assert same(r.value, *refs[k], tolerance(plans[k])), r.request_id
+
+
+@pytest.mark.parametrize("rows,cols,ternary,seed,block,fused", [
+    (14, 15, 0.122, 890, 6, False), (6, 16, 0.105, 606, 6, False), (6, 12, 0.155, 246, 5, False),
+    (13, 15, 0.1, 7, 3, True), (9, 13, 0.1, 7, 2, True)])
+def test_small_plan_keeps_its_launch_list_unless_chains_save_launches(rows, cols, ternary, seed, block, fused):
+    """Row by row: matrix nodes leave chains only at the ends of the sweep."""
+    f = wl.grid_cnf(rows, cols, ternary, seed=seed)
+    p = W.Plan(W.Network.from_formula(f), kind="order", order=wl.row_major_order(rows, cols), block=block)
+    assert (p.program()[1]["n_launches"] > 0) == fused
