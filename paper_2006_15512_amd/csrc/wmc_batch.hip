@@ -61,11 +61,11 @@ __global__ void k_finish_batch(const T *__restrict__ arena, const long long *__r
     out[i].e = bad ? WMC_BATCH_RERUN : e;
 }
 
-// A merged step of the fused programs: short chains and small nodes in one
-// launch, short chains that need more LDS than eight workgroups of a compute
+// A merged step of the fused programs: short chains in one launch, with the
+// small nodes unless there are streaming tasks, short chains that need more LDS than eight workgroups of a compute
 // unit can share in one (every workgroup of a launch reserves the most any of
-// them needs), chains of many tiles in one, streaming tasks in one, matrix
-// nodes one by one.
+// them needs), chains of many tiles in one, streaming tasks and small nodes
+// in one, matrix nodes one by one.
 struct BatchStep {
     int64_t rec_first = 0, rec_count = 0, wide_first = 0, wide_count = 0, big_first = 0, big_count = 0;
     int lds = 0, wide_lds = 0, big_lds = 0;
@@ -73,6 +73,8 @@ struct BatchStep {
     int64_t task_first = 0, btask_off = 0;
     std::array<int, 5> task_nk{{0, 0, 0, 0, 0}};
     std::vector<int> gemms;
+    // small nodes share a launch with streaming tasks, or else with chains
+    bool nodes_join_chains() const { return rec_count > 0 && task_nk[4] == 0; }
 };
 
 // The instances' fused programs merged by launch index, with an image of
@@ -552,8 +554,8 @@ extern "C" wmc_status wmc_batch_info(const wmc_batch *b, uint64_t *workspace_byt
         if (b->fused.on) {
             *n_launches = 2 + !b->fused.leaves.empty();
             for (const BatchStep &S : b->fused.steps)
-                *n_launches += (S.big_count > 0) + (S.task_nk[4] > 0) + (S.wide_count > 0) +
-                               (S.rec_count > 0 || S.node_count > 0) + (int64_t)S.gemms.size();
+                *n_launches += (S.big_count > 0) + (S.wide_count > 0) + (S.rec_count > 0) + (int64_t)S.gemms.size() +
+                               (S.task_nk[4] > 0 || (S.node_count > 0 && !S.nodes_join_chains()));
         }
     }
     if (n_instances) *n_instances = b->n;
@@ -646,22 +648,30 @@ static void batch_fused_launches(const wmc_batch &B, char *ws, hipStream_t st) {
         a.words = (const unsigned *)(img + F.o_words);
         a.cblocks = (unsigned)S.big_count;
         if (S.big_count) launch_chain_big<T>(a, S.big_lds, arena, meta, st);
-        if (S.task_nk[4] > 0) {
-            StepArgs t{};
+        StepArgs t{};
+        if (S.task_nk[4] > 0)
             step_stream_part(t, (const StreamTask *)(img + F.o_tasks) + S.task_first, F.tasks.data() + S.task_first,
                              S.task_nk.data(), tabs + S.btask_off);
-            launch_step<T>(t, arena, meta, st);
+        if (S.node_count && !S.nodes_join_chains()) {
+            t.nodes = (const NodeDesc *)(img + F.o_node) + S.node_first;
+            t.nnodes = (int)S.node_count;
+            t.node_work = S.node_work;
+            t.wave_node = tabs + S.wave_off;
+            t.nblocks = grid_for(S.node_work);
         }
+        launch_step<T>(t, arena, meta, st);
         a.recs = (const ChainRec *)(img + F.o_recs) + S.wide_first;
         a.cblocks = (unsigned)S.wide_count;
         launch_fused_step<T, WMC_CHAIN_LANE_MANY>(a, S.wide_lds, arena, meta, st);
         a.recs = (const ChainRec *)(img + F.o_recs) + S.rec_first;
         a.cblocks = (unsigned)S.rec_count;
-        a.nodes = (const NodeDesc *)(img + F.o_node) + S.node_first;
-        a.nnodes = (int)S.node_count;
-        a.node_work = S.node_work;
-        a.wave_node = tabs + S.wave_off;
-        a.nblocks = S.node_count ? chain_node_blocks<WMC_CHAIN_LANE_MANY>(S.node_work) : 0;
+        if (S.nodes_join_chains()) {
+            a.nodes = (const NodeDesc *)(img + F.o_node) + S.node_first;
+            a.nnodes = (int)S.node_count;
+            a.node_work = S.node_work;
+            a.wave_node = tabs + S.wave_off;
+            a.nblocks = S.node_count ? chain_node_blocks<WMC_CHAIN_LANE_MANY>(S.node_work) : 0;
+        }
         launch_fused_step<T, WMC_CHAIN_LANE_MANY>(a, S.lds, arena, meta, st);
         for (int g : S.gemms)
             launch_gemm<T>(F.gemms[(size_t)g], (const GemmDesc *)(img + F.o_gemm) + g, arena, meta, st,
