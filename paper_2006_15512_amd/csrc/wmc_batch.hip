@@ -90,6 +90,8 @@ struct BatchFused {
     std::vector<int> tables, mask_first, masks;
     std::vector<long long> root_off;
     std::vector<BatchStep> steps;
+    int64_t n_launches = 0;
+    double us = 0;  // estimate of a replayed batch
     // offsets from the image's start
     uint64_t o_leaf = 0, o_node = 0, o_gemm = 0, o_tasks = 0, o_words = 0, o_recs = 0, o_tables = 0, o_mask_first = 0,
              o_masks = 0, o_roots = 0, o_rootoff = 0, o_leaf_eta = 0;
@@ -161,6 +163,37 @@ struct wmc_batch {
 
 static uint64_t bal(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 
+// Microseconds of a replayed batch, on its launch lists and on its fused
+// programs.  A merged launch takes what it costs to launch, its slowest
+// thread (up to 8 summed entries in a row, further ones overlap; the stages of
+// its longest chain) and its share of what all instances move and multiply.
+// Many small formulas, or many slices, fill the device node by node, and
+// chains then cost more instructions than they save bytes.  Fitted to 24
+// batches of 1 to 512 formulas and tried on 30 others, in both precisions.
+// List to fused time measured (FP64, FP32): 512 banded formulas 1.17, 1.28;
+// one 16x18 lattice 1.83, 1.84; 20 banded formulas of 123 variables 1.85, 1.53;
+// 64 lattices row by row in blocks of 2 1.29, 1.09; against 200 formulas of 12
+// variables 0.81, 0.94; 12 lattices 12x14 in blocks of 3 0.72, 0.66; 96 slices
+// of two banded formulas 0.83, 0.84; 48 formulas in blocks of 1 to 4 0.89, 0.81.
+// Fused programs run where they are estimated at least 7% faster: of the 54
+// none that lost more than 2% does, and of the gains six of 3 to 14% are
+// given up.
+const double kBatchFixed = 30.0, kBatchMargin = 1.07;
+static double list_us(double launches, double bytes, int elem, double sum_k) {
+    return kBatchFixed + 3.3 * launches + 0.215e-6 * bytes + 0.56e-6 * bytes / elem + 0.84 * sum_k;
+}
+static double fused_us(double launches, double bytes, double sum_k, double sum_l, double stages, double products,
+                       double big_stages) {
+    return kBatchFixed + 5.1 * launches + 0.2e-6 * bytes + 0.83 * sum_k + 0.59 * sum_l + 0.75e-3 * stages +
+           0.68e-6 * products + 1.4e-3 * big_stages;
+}
+static double node_bytes(const NodeDesc &d, int elem) {
+    int ra = d.nk, rb = d.nk;
+    for (int q = 0; q < d.nra; ++q) ra += (int)((d.ra[q] >> 8) & 255u);
+    for (int q = 0; q < d.nrb; ++q) rb += (int)((d.rb[q] >> 8) & 255u);
+    return (double)elem * (std::ldexp(1.0, ra) + std::ldexp(1.0, rb) + std::ldexp(1.0, d.rc));
+}
+
 // Merges the plans' fused programs (iplan, ieta: plan and slice of each
 // instance; abase, mbase: its arena and meta base).
 static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::vector<int64_t> &iplan,
@@ -188,7 +221,10 @@ static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::
     F.mask_first.push_back((int)F.masks.size());
     F.tables.assign(B.tables.begin() + B.leaf_tab_off, B.tables.begin() + B.leaf_tab_off + B.leaf_work / WMC_WAVE);
     std::vector<int> tab;
+    F.n_launches = 2 + !F.leaves.empty();
+    double bytes = 0, sum_k = 0, sum_l = 0, stages = 0, products = 0, big_stages = 0;
     for (size_t k = 0; k < kmax; ++k) {
+        int most_nk = -1, longest = 0;
         BatchStep S;
         std::vector<NodeDesc> small, stream;
         std::vector<ChainRec> wide, big;
@@ -201,12 +237,15 @@ static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::
                 NodeDesc d = G.nodes[(size_t)(L.node_first + q)];
                 for (long long *o : {&d.a, &d.b, &d.c}) *o += abase[j];
                 for (int *t : {&d.ta, &d.tb, &d.tc}) *t += (int)mbase[j];
+                most_nk = std::max(most_nk, d.nk);
+                bytes += node_bytes(d, B.elem);
                 (L.type == FUSED_NODE ? stream : small).push_back(d);
             }
             if (L.type == FUSED_GEMM) {
                 GemmDesc g = G.gemms[(size_t)L.gemm];
                 for (long long *o : {&g.a, &g.b, &g.c}) *o += abase[j];
                 for (int *t : {&g.ta, &g.tb, &g.tc}) *t += (int)mbase[j];
+                bytes += node_bytes(G.nodes[(size_t)L.node_first], B.elem);
                 S.gemms.push_back((int)F.gemms.size());
                 F.gemms.push_back(g);
             }
@@ -222,6 +261,10 @@ static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::
                     x.desc = at;
                     (t.big ? big : is_wide ? wide : F.recs).push_back(x);
                 }
+                const double st = std::ldexp((double)t.nodes.size(), t.tile_bits);
+                longest = std::max(longest, (int)t.nodes.size());
+                if (t.big) big_stages += st;
+                else stages += st, products += t.work;
                 int &most = t.big ? S.big_lds : is_wide ? S.wide_lds : S.lds;
                 most = std::max(most, lds);
             }
@@ -258,8 +301,13 @@ static void fuse_batch(wmc_batch &B, const wmc_plan_t *const *plans, const std::
         block_task_table(tasks, nkf, tab);
         F.tables.insert(F.tables.end(), tab.begin(), tab.end());
         F.tasks.insert(F.tasks.end(), tasks.begin(), tasks.end());
+        F.n_launches += (S.big_count > 0) + (S.wide_count > 0) + (S.rec_count > 0) + (int64_t)S.gemms.size() +
+                        (S.task_nk[4] > 0 || (S.node_count > 0 && !S.nodes_join_chains()));
+        sum_k += most_nk < 0 ? 0.0 : std::ldexp(1.0, std::min(most_nk, 3));
+        sum_l += longest;
         F.steps.push_back(std::move(S));
     }
+    F.us = fused_us((double)F.n_launches, bytes, sum_k, sum_l, stages, products, big_stages);
     uint64_t o = 0;
     auto part = [&](uint64_t &at, const void *src, size_t bytes) {
         at = o;
@@ -309,7 +357,7 @@ static uint64_t fused_image_bytes(const wmc_plan_t *const *plans, int64_t n) {
 }
 
 // A batch of checked plans; null if `fuse` and the fused programs would take
-// too much memory.
+// too much memory or not be faster.
 static std::unique_ptr<wmc_batch> make_batch(const wmc_plan_t *const *plans, int64_t n, bool fuse) {
     std::unique_ptr<wmc_batch> B(new wmc_batch());
     B->precision = plans[0]->precision;
@@ -482,6 +530,18 @@ static std::unique_ptr<wmc_batch> make_batch(const wmc_plan_t *const *plans, int
         B->off_live = off;
         off += bal((uint64_t)B->meta_total, 256);
         if (!batch_growth_ok(list_bytes, off + (uint64_t)arena_elems * (uint64_t)B->elem)) return nullptr;
+        double bytes = 0, sum_k = 0;
+        for (int64_t j = 0; j < ni; ++j) bytes += plans[iplan[(size_t)j]]->info.bytes_per_slice;
+        for (size_t k = 1; k < B->launches.size(); ++k) {
+            const Launch &Ln = B->launches[k];
+            int most_nk = -1;
+            for (int32_t q = 0; q < Ln.count && Ln.type != LAUNCH_GEMM; ++q)
+                most_nk = std::max(most_nk, B->nodes[(size_t)(Ln.first + q)].nk);
+            for (int g = 0; g < 4; ++g)
+                if (B->task_nk[k][(size_t)g] < B->task_nk[k][(size_t)g + 1]) most_nk = std::max(most_nk, g);
+            sum_k += most_nk < 0 ? 0.0 : std::ldexp(1.0, std::min(most_nk, 3));
+        }
+        if (kBatchMargin * B->fused.us > list_us((double)B->launches.size() + 2, bytes, B->elem, sum_k)) return nullptr;
     }
     B->off_arena = off;
     B->arena_bytes = (uint64_t)arena_elems * (uint64_t)B->elem;
@@ -550,13 +610,7 @@ extern "C" wmc_status wmc_batch_info(const wmc_batch *b, uint64_t *workspace_byt
     }
     if (workspace_bytes) *workspace_bytes = b->workspace_bytes;
     if (n_launches) {
-        *n_launches = (int64_t)b->launches.size() + 2;
-        if (b->fused.on) {
-            *n_launches = 2 + !b->fused.leaves.empty();
-            for (const BatchStep &S : b->fused.steps)
-                *n_launches += (S.big_count > 0) + (S.wide_count > 0) + (S.rec_count > 0) + (int64_t)S.gemms.size() +
-                               (S.task_nk[4] > 0 || (S.node_count > 0 && !S.nodes_join_chains()));
-        }
+        *n_launches = b->fused.on ? b->fused.n_launches : (int64_t)b->launches.size() + 2;
     }
     if (n_instances) *n_instances = b->n;
     return WMC_OK;

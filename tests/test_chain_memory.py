@@ -46,6 +46,20 @@ def test_batch_counts_the_launches_it_makes(precision):
     assert b.n_launches >= p.stats()["n_launches"]
 
 
+@pytest.mark.parametrize("formulas,kw,fused", [
+    (lambda: [wl.random_kcnf(12, 40, seed=i) for i in range(100)], {}, False),
+    (lambda: [wl.grid_cnf(12, 14, 0.1, seed=i) for i in range(12)], dict(block=3), False),
+    (lambda: [wl.banded_3cnf(110, 380, 25, seed=i) for i in (2, 3)], dict(block=3, rank_cap=17), False),
+    (lambda: [wl.batch_instance(i) for i in range(24)], {}, True),
+    (lambda: [wl.grid_cnf(16, 18, 0.1, seed=1)], dict(block=2), True)])
+def test_batch_runs_chains_only_where_they_pay(formulas, kw, fused):
+    """Batches that fill the device node by node keep their launch lists."""
+    plans = [W.Plan(W.Network.from_formula(f), seed=0, **kw) for f in formulas()]
+    assert any(p.program()[1]["n_launches"] for p in plans)
+    b = W.Batch(plans)
+    assert (b.n_launches < b.image()[1]["n_launches"] + 2) == fused
+
+
 @pytest.mark.gpu
 def test_resident_programs_leave_room_for_a_large_request():
     """A structure whose region takes all that the launch lists' images leave
