@@ -637,7 +637,8 @@ def main():
     log("config 3 FP64 on the seed-0 tree (no tree choice)")
     s0 = solo(W, torch, "banded300", "fp64", max(3, args.steps // 2), 1, 0, probes, tree_seed=0)
     seed0 = {"solves_s": s0["solves_s"], "ms_per_step": s0["ms_per_step"], "n_slices": s0["n_slices"],
-             "algorithmic_gbs": s0.get("algorithmic_gbs"), "roofline_frac": s0["roofline"]["frac"],
+             "algorithmic_gbs": s0.get("algorithmic_gbs"), "node_by_node_gbs": s0.get("node_by_node_gbs"),
+             "roofline_frac": s0["roofline"]["frac"],
              "roofline_kernel": s0["roofline"]["kernel"], "rel_err_vs_oracle": s0.get("rel_err_vs_oracle")}
     log("config 2 (row-major sweep, min-fill sliced)")
     c2 = solo(W, torch, "grid24", "fp64", args.steps, args.warmup, 0, probes)
