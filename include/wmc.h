@@ -385,7 +385,10 @@ typedef struct wmc_batch wmc_batch;
                                    barrier wait times out (20 s) */
 
 wmc_status wmc_batch_create(const wmc_plan_t *const *plans, int64_t n, wmc_batch **out);
-/* n_launches: kernels one wmc_batch_contract launches (without
+/* A batch runs its plans' fused programs where they are estimated faster than
+ * the launch lists and add at most a quarter of the workspace (1 GiB in large
+ * batches; 64 MiB are always allowed).
+ * n_launches: kernels one wmc_batch_contract launches (without
  * WMC_BATCH_PERSISTENT, and if no instance leaves its chains' range). */
 wmc_status wmc_batch_info(const wmc_batch *b, uint64_t *workspace_bytes, int64_t *n_launches,
                           int64_t *n_instances);
@@ -411,9 +414,11 @@ wmc_status wmc_batch_image(const wmc_batch *b, void *dst, uint64_t dst_bytes, ui
 /* Each request is the paper's execution stage (Algorithm 2) on a registered
  * plan with the request's weights W (Definition 1); requests share launches.
  * A registered structure's descriptors are uploaded once, into the request
- * region pool (they stay resident and count against it); a step uploads
- * only one small work entry per running request and the weights of newly
- * admitted ones.
+ * region pool (they stay resident and count against it; those of its fused
+ * program are kept only where room allows and are given back when a
+ * registration or a request needs it); a step uploads a small work entry per
+ * running request, one record per workgroup and the weights of newly admitted
+ * requests.
  * A server owns a caller-supplied device buffer: two staging areas for step
  * descriptors (2 * step_bytes), a result table, and the request regions (at
  * most hbm_budget_bytes).  Registered structures are plans of the server's
@@ -428,7 +433,10 @@ wmc_status wmc_batch_image(const wmc_batch *b, void *dst, uint64_t dst_bytes, ui
  * runs the next launch of every admitted request's plan in shared kernels;
  * requests join and leave between steps (continuous batching).  A request's
  * descriptors are its plan's shifted into its region, so its value is the
- * same alone or in any mix.  A server is driven by one thread. */
+ * same alone or in any mix (bit for bit unless a node of the launch list holds
+ * entries in denormal numbers).  A request whose fused program left its range
+ * runs again on its plan's launch list before it answers.  A server is driven
+ * by one thread. */
 typedef struct wmc_server wmc_server;
 
 typedef struct {
