@@ -180,12 +180,12 @@ static uint64_t bal(uint64_t x, uint64_t a) { return (x + a - 1) / a * a; }
 // given up.
 const double kBatchFixed = 30.0, kBatchMargin = 1.07;
 static double list_us(double launches, double bytes, int elem, double sum_k) {
-    return kBatchFixed + 3.3 * launches + 0.215e-6 * bytes + 0.56e-6 * bytes / elem + 0.84 * sum_k;
+    return kBatchFixed + 3.3 * launches + wmc_list_busy_us(bytes, elem) + 0.84 * sum_k;
 }
 static double fused_us(double launches, double bytes, double sum_k, double sum_l, double stages, double products,
                        double big_stages) {
-    return kBatchFixed + 5.1 * launches + 0.2e-6 * bytes + 0.83 * sum_k + 0.59 * sum_l + 0.75e-3 * stages +
-           0.68e-6 * products + 1.4e-3 * big_stages;
+    return kBatchFixed + 5.1 * launches + 0.83 * sum_k + 0.59 * sum_l +
+           wmc_chain_busy_us(bytes, stages, products, big_stages);
 }
 static double node_bytes(const NodeDesc &d, int elem) {
     int ra = d.nk, rb = d.nk;

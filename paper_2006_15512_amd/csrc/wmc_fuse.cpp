@@ -784,6 +784,19 @@ FusedProgram wmc_program_of(const wmc_plan_t &P, bool fused) {
     return F;
 }
 
+double wmc_fused_busy_us(const wmc_plan_t &P) {
+    const FusedProgram &F = P.fused;
+    auto size = [&](int32_t t) { return std::ldexp(1.0, (int)P.T[(size_t)t].layout.size()); };
+    double bytes = 0, stages = 0, products = 0, big_stages = 0;
+    for (const NodeDesc &d : F.nodes) bytes += (double)P.elem * (size(d.ta) + size(d.tb) + size(d.tc));
+    for (const ChainTask &t : F.chains) {
+        const double st = std::ldexp((double)t.nodes.size(), t.tile_bits);
+        if (t.big) big_stages += st;
+        else stages += st, products += t.work;
+    }
+    return wmc_chain_busy_us(bytes, stages, products, big_stages);
+}
+
 unsigned wmc_shift_chain(const FusedProgram &F, const ChainTask &t, unsigned words, long long abase, int mbase,
                          std::vector<unsigned> &out) {
     while (out.size() % 4) out.push_back(0);

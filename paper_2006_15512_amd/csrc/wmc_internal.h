@@ -162,6 +162,16 @@ uint64_t wmc_place(const std::vector<int32_t> &birth, const std::vector<int32_t>
 // max_arena bytes (wmc_fuse.cpp).
 void wmc_fuse(wmc_plan_t &P, uint64_t max_arena);
 bool wmc_validate_fused(const wmc_plan_t &P, std::string *why);
+// Microseconds of a device that other work keeps full: of tensors read and
+// written node by node, and of chains (tiles times stages of short ones, their
+// products, tiles times stages of ones of many tiles; bytes of the nodes
+// beside them).  Fitted to the batches named in wmc_batch.hip.
+inline double wmc_list_busy_us(double bytes, int elem) { return 0.215e-6 * bytes + 0.56e-6 * bytes / elem; }
+inline double wmc_chain_busy_us(double bytes, double stages, double products, double big_stages) {
+    return 0.2e-6 * bytes + 0.75e-3 * stages + 0.68e-6 * products + 1.4e-3 * big_stages;
+}
+// The same of one run of a plan's fused program.
+double wmc_fused_busy_us(const wmc_plan_t &P);
 // P.fused if `fused` and there is one, else the plan's launch list in the
 // same form (no chains).
 FusedProgram wmc_program_of(const wmc_plan_t &P, bool fused = true);

@@ -88,6 +88,7 @@ struct SStruct {
     // again on the former
     SProg list, fused;
     bool has_fused = false;
+    double list_us = 0, fused_us = 0;  // of a request, on a full device
     int32_t root = -1;
     int64_t nt = 0;
     uint64_t meta_bytes = 0, arena_bytes = 0;
@@ -500,6 +501,18 @@ static SProg serve_program(const wmc_plan_t &plan, const FusedProgram &F, std::v
     return s;
 }
 
+// Whether a request runs its structure's fused program, `n` requests running
+// beside it (or waiting for a slot).  A server step costs about 45 us whatever is in it, and
+// 0.2 us (chains: 0.45, a record per workgroup) per request, so few requests
+// gain by fewer steps (row-by-row 10x16 lattice in blocks of 3, FP64, 8
+// requests: 1.55 ms against 2.61); many fill the device, and there the program
+// whose work is less is the faster one (600 requests: 21.5 ms against 19.0,
+// FP32 20.1 against 13.6).
+static bool fused_pays(const SStruct &s, size_t n) {
+    const double step = 45.0 / (double)std::max<size_t>(n, 1);
+    return s.fused_us + (step + 0.45) * (double)s.fused.L.size() <= s.list_us + (step + 0.2) * (double)s.list.L.size();
+}
+
 // Gives back the resident images of the fused programs that no request runs
 // on: they are kept only where nothing else needs the room.
 static bool drop_fused(wmc_server *v) {
@@ -610,6 +623,8 @@ extern "C" wmc_status wmc_serve_register(wmc_server *v, const wmc_plan_t *plan, 
             const uint64_t step = std::max(s.max_step_bytes, staging(s.fused));
             s.has_fused = step <= v->step_cap / 4 && foot <= v->regions_bytes / 16 &&
                           v->structure_bytes + img.size() + 256 <= v->regions_bytes / 8 && reserve(s.fused, true);
+            s.list_us = wmc_list_busy_us(plan->info.bytes_per_slice, plan->elem);
+            s.fused_us = wmc_fused_busy_us(*plan);
             if (s.has_fused) {
                 s.footprint = foot;
                 s.max_step_bytes = step;
@@ -876,12 +891,13 @@ static wmc_status serve_issue_t(wmc_server *v, int h, std::vector<SReq> &finishi
         }
         r.region = off;
         r.region_bytes = s.footprint;
-        r.fused = s.has_fused;
+        r.fused = s.has_fused && fused_pays(s, std::min<size_t>(v->active.size() + v->queue.size(),
+                                                        (size_t)v->opt.max_slots));
         r.slot = v->free_slots.back();
         v->free_slots.pop_back();
         r.k = 0;
         r.t_admit = v->now();
-        stage_need += s.max_step_bytes;
+        stage_need += step_bytes(r);
         if (r.deadline > 0.0) --v->queued_deadlines;  // next_deadline stays a lower bound
         v->active.push_back(std::move(r));
         v->queue.pop_front();

@@ -82,3 +82,21 @@ def test_resident_programs_leave_room_for_a_large_request():
     done = sorted(srv.drain(), key=lambda r: r.request_id)
     assert [r.request_id for r in done] == list(range(10, 15))
     assert all(abs(r.value.log2_abs - first[0].value.log2_abs) < 1e-4 for r in done)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_served_alone_and_in_a_burst(precision):
+    """A structure whose requests run the fused program while they are few and
+    the launch list while they are many: the same values, wmc_contract's."""
+    f = wl.grid_cnf(10, 16, 0.1, seed=2)
+    p = W.Plan(W.Network.from_formula(f), kind="order", order=wl.row_major_order(10, 16), block=3, precision=precision)
+    v = W.wmc_contract(p)
+    srv = W.Server(precision=precision, max_slots=64, hbm_budget_bytes=1 << 31, buffer_bytes=3 << 30)
+    s = srv.register(p)
+    for n in (1, 3, 200, 2):
+        for q in range(n):
+            srv.submit(s, f.weights.reshape(-1), q)
+        done = srv.drain()
+        assert sorted(r.request_id for r in done) == list(range(n))
+        assert all((r.value.mantissa, r.value.exp2) == (v.mantissa, v.exp2) for r in done), n
